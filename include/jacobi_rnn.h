@@ -67,6 +67,8 @@ int rnn_jacobi_max_steps(int32_t H);
  * with p_t = sigmoid(z_t) * d_t, summed over all steps of all sequences:
  *   dW [H, H] = sum p_t h_{t-1}^T,   dU [H, I] = sum p_t x_t^T,   db [H] = sum p_t      (outputs, overwritten)
  *   h [B, T, H] hidden states of the forward pass;  h0 [B, H] or NULL (zeros)
+ * More than 512 rows (B * T) are summed in slices whose sums are added in the order they finish: the last bits of two
+ * calls may differ.
  */
 int rnn_param_grads(const float* z, const float* h, const float* x, const float* d, const float* h0, int32_t B, int32_t T,
                     int32_t H, int32_t I, float* dW, float* dU, float* db, void* stream);

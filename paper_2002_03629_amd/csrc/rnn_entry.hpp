@@ -4,6 +4,10 @@
 #include "../../include/jacobi_rnn.h"
 #include "rnn.hpp"
 
+// rnn_param_grads: up to this many chunks of rows are summed by one workgroup per strip (a chunk takes it ~1.2 us; zeroing
+// the output in a launch of its own, the gap to it and the atomics cost about 8 us)
+constexpr int GRAD_ONE_SLICE = 8;
+
 static int rnn_check_shape(const char* who, int B, int T, int H) {
   if (B < 0 || T < 1 || H < 1) return fail(MADE_ERR_ARG, "%s: B=%d, T=%d, H=%d out of range", who, B, T, H);
   if (H > RNN_MAX_H) return fail(MADE_ERR_ARG, "%s: H=%d, at most %d hidden units are supported", who, H, RNN_MAX_H);
@@ -90,8 +94,26 @@ extern "C" int rnn_param_grads(const float* z, const float* h, const float* x, c
   if (I < 1) return fail(MADE_ERR_ARG, "rnn_param_grads: I=%d must be >= 1", I);
   if (!z || !h || !x || !d || !dW || !dU || !db) return fail(MADE_ERR_ARG, "rnn_param_grads: NULL argument");
   const int CT = (H + 31) / 32;
-  hipLaunchKernelGGL(rnn_param_grads_kernel, dim3(CT * CT), dim3(RNN_WAVES * 64), 0, (hipStream_t)stream, z, h, x, d, h0, B, T,
-                     H, I, dW, dU, db);
+  const long long rows = (long long)B * T, chunks = (rows + GRAD_ROWS - 1) / GRAD_ROWS;
+  // One slice (results stored, no zeroing, no atomics) for up to GRAD_ONE_SLICE chunks, else as many as give every
+  // compute unit a workgroup.
+  long long slices = chunks <= GRAD_ONE_SLICE ? 1 : std::min<long long>(chunks, 256 / CT);
+  const int slice_rows = (int)std::min<long long>((std::max<long long>(chunks, 1) + slices - 1) / slices * GRAD_ROWS, 1 << 30);
+  slices = std::max<long long>(1, (rows + slice_rows - 1) / slice_rows);
+  hipStream_t s = (hipStream_t)stream;
+  if (slices > 1) {
+    const int n_w = H * H, n_u = H * I;
+    hipLaunchKernelGGL(rnn_grads_zero_kernel, dim3((std::max(std::max(n_w, n_u), H) + 255) / 256), dim3(256), 0, s, dW, dU, db, n_w, n_u, H);
+  }
+  const dim3 grid(CT, (unsigned)slices, I / GRAD_SLOTS + 1), block(RNN_WAVES * 64);
+#define JM_GRADS(N) hipLaunchKernelGGL(rnn_param_grads_kernel<N>, grid, block, 0, s, z, h, x, d, h0, rows, T, H, I, slice_rows, dW, dU, db)
+  switch (CT) {
+    case 1: JM_GRADS(1); break;
+    case 2: JM_GRADS(2); break;
+    case 3: JM_GRADS(3); break;
+    default: JM_GRADS(4); break;
+  }
+#undef JM_GRADS
   HIP_TRY(hipGetLastError());
   return MADE_OK;
 }

@@ -174,3 +174,21 @@ def test_rnn_full_batch():
     B.rnn_backward_sequential(dev(c.W), dev(c.z32), dev(c.g32), w.B, w.T, w.H, d)
     torch.cuda.synchronize()
     assert rel_err(d.cpu().numpy(), d_ref) <= F32_TOL
+
+
+@pytest.mark.parametrize("B_,T,H,I", [(1, 1, 1, 1), (1, 63, 31, 7), (2, 32, 32, 8), (13, 5, 33, 6), (1, 512, 64, 1), (27, 19, 65, 2),
+                                      (3, 171, 96, 16), (4, 200, 97, 1), (180, 100, 128, 3)])
+def test_param_grads_slices_and_strips(B_, T, H, I):
+    """Edges of the gradient kernel: chunks of 64 rows, one slice (up to 512 rows) and several, strips of 32 units, the
+    eight [1, x] columns per block.  fp32 sums of R rows: about sqrt(R) ulp each way, 2e-6 of the largest entry at most."""
+    progress(f"rnn gradients B={B_} T={T} H={H} I={I}")
+    r = np.random.default_rng(17)
+    z, h, d = (r.standard_normal((B_, T, H)).astype(np.float32) for _ in range(3))
+    x, h0 = r.standard_normal((B_, T, I)).astype(np.float32), r.standard_normal((B_, H)).astype(np.float32)
+    for init in (None, h0):
+        dW, dU, db = (torch.full(s, 7.0, dtype=torch.float32, device="cuda") for s in ((H, H), (H, I), (H,)))
+        B.rnn_param_grads(dev(z), dev(h), dev(x), dev(d), None if init is None else dev(init), B_, T, H, I, dW, dU, db)
+        torch.cuda.synchronize()
+        ref = R.param_grads(*(a.astype(np.float64) for a in (z, h, x, d)), None if init is None else init.astype(np.float64))
+        for got, want in zip((dW, dU, db), ref):
+            assert rel_err(got.cpu().numpy(), want) <= 2e-6 * max(1.0, np.sqrt(B_ * T) / 20)
