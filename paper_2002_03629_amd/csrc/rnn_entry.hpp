@@ -8,6 +8,15 @@
 // the output in a launch of its own, the gap to it and the atomics cost about 8 us)
 constexpr int GRAD_ONE_SLICE = 8;
 
+// LAUNCH(CT) with CT = the number of 32-unit tiles H units take
+#define JM_RNN_BY_WIDTH(H, LAUNCH)       \
+  switch (((H) + 31) / 32) {             \
+    case 1: LAUNCH(1); break;            \
+    case 2: LAUNCH(2); break;            \
+    case 3: LAUNCH(3); break;            \
+    default: LAUNCH(4); break;           \
+  }
+
 static int rnn_check_shape(const char* who, int B, int T, int H) {
   if (B < 0 || T < 1 || H < 1) return fail(MADE_ERR_ARG, "%s: B=%d, T=%d, H=%d out of range", who, B, T, H);
   if (H > RNN_MAX_H) return fail(MADE_ERR_ARG, "%s: H=%d, at most %d hidden units are supported", who, H, RNN_MAX_H);
@@ -26,8 +35,10 @@ extern "C" int rnn_forward(const float* W, const float* U, const float* b, const
   if (I < 1) return fail(MADE_ERR_ARG, "rnn_forward: I=%d must be >= 1", I);
   if (B == 0) return MADE_OK;   // (an empty batch has nothing to point at)
   if (!W || !U || !b || !x || !z || !h) return fail(MADE_ERR_ARG, "rnn_forward: NULL argument");
-  const int Hp = round_up(H, 32);
-  hipLaunchKernelGGL(rnn_forward_kernel, dim3(B), dim3(2 * Hp), 0, (hipStream_t)stream, W, U, b, x, h0, z, h, T, H, I);
+#define JM_FORWARD(N) hipLaunchKernelGGL((H == 32 * N ? rnn_forward_kernel<N, true> : rnn_forward_kernel<N, false>), dim3(B), dim3(RnnStep<N>::THREADS), 0, \
+                                         (hipStream_t)stream, W, U, b, x, h0, z, h, T, H, I)
+  JM_RNN_BY_WIDTH(H, JM_FORWARD);
+#undef JM_FORWARD
   HIP_TRY(hipGetLastError());
   return MADE_OK;
 }
@@ -37,8 +48,10 @@ extern "C" int rnn_backward_sequential(const float* W, const float* z, const flo
   TRY(rnn_check_shape("rnn_backward_sequential", B, T, H));
   if (B == 0) return MADE_OK;
   if (!W || !z || !g || !d) return fail(MADE_ERR_ARG, "rnn_backward_sequential: NULL argument");
-  const int Hp = round_up(H, 32);
-  hipLaunchKernelGGL(rnn_backward_seq_kernel, dim3(B), dim3(2 * Hp), 0, (hipStream_t)stream, W, z, g, d, T, H);
+#define JM_BACKWARD(N) hipLaunchKernelGGL((H == 32 * N ? rnn_backward_seq_kernel<N, true> : rnn_backward_seq_kernel<N, false>), dim3(B), \
+                                          dim3(RnnStep<N>::THREADS), 0, (hipStream_t)stream, W, z, g, d, T, H)
+  JM_RNN_BY_WIDTH(H, JM_BACKWARD);
+#undef JM_BACKWARD
   HIP_TRY(hipGetLastError());
   return MADE_OK;
 }
@@ -107,12 +120,7 @@ extern "C" int rnn_param_grads(const float* z, const float* h, const float* x, c
   }
   const dim3 grid(CT, (unsigned)slices, I / GRAD_SLOTS + 1), block(RNN_WAVES * 64);
 #define JM_GRADS(N) hipLaunchKernelGGL(rnn_param_grads_kernel<N>, grid, block, 0, s, z, h, x, d, h0, rows, T, H, I, slice_rows, dW, dU, db)
-  switch (CT) {
-    case 1: JM_GRADS(1); break;
-    case 2: JM_GRADS(2); break;
-    case 3: JM_GRADS(3); break;
-    default: JM_GRADS(4); break;
-  }
+  JM_RNN_BY_WIDTH(H, JM_GRADS);
 #undef JM_GRADS
   HIP_TRY(hipGetLastError());
   return MADE_OK;

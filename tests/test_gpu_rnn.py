@@ -192,3 +192,50 @@ def test_param_grads_slices_and_strips(B_, T, H, I):
         ref = R.param_grads(*(a.astype(np.float64) for a in (z, h, x, d)), None if init is None else init.astype(np.float64))
         for got, want in zip((dW, dU, db), ref):
             assert rel_err(got.cpu().numpy(), want) <= 2e-6 * max(1.0, np.sqrt(B_ * T) / 20)
+
+
+@pytest.mark.parametrize("B_,T,H,I", [(1, 1, 1, 1), (2, 3, 31, 5), (1, 4, 32, 1), (3, 5, 33, 2), (1, 7, 64, 1), (2, 9, 95, 3), (1, 8, 96, 1),
+                                      (1, 2, 97, 1), (2, 131, 127, 1), (1, 65, 128, 6)])
+def test_recurrences_at_tile_edges(B_, T, H, I):
+    """The step kernels at the edges of their 32-unit widths and of the groups of four steps.  F32_TOL as elsewhere."""
+    progress(f"rnn recurrences B={B_} T={T} H={H} I={I}")
+    w = dataclasses.replace(S.rnn_workload("rnn_small"), B=B_, T=T, H=H, I=I, w_std=min(0.2, 1.2 / np.sqrt(H)))
+    c = Case(w)
+    z, h, d = (torch.empty((B_, T, H), dtype=torch.float32, device="cuda") for _ in range(3))
+    h0 = np.random.default_rng(5).uniform(0, 1, (B_, H)).astype(np.float32)
+    for init in (None, h0):
+        B.rnn_forward(dev(c.W), dev(c.U), dev(c.b), dev(c.x), None if init is None else dev(init), B_, T, H, I, z, h)
+        torch.cuda.synchronize()
+        z_ref, h_ref = R.rnn_forward(c.W64, c.U.astype(np.float64), c.b.astype(np.float64), c.x, init)
+        assert rel_err(z.cpu().numpy(), z_ref) <= F32_TOL and rel_err(h.cpu().numpy(), h_ref) <= F32_TOL
+    B.rnn_backward_sequential(dev(c.W), dev(c.z32), dev(c.g32), B_, T, H, d)
+    torch.cuda.synchronize()
+    assert rel_err(d.cpu().numpy(), c.oracle_backprop()) <= F32_TOL
+
+
+def test_activations_over_their_range():
+    """softplus and sigmoid from one step of the recurrences with W = 0 (z = b), from underflow to overflow and a NaN:
+    relative error of a few ulp (exp2, log2 and reciprocal of the hardware are good to an ulp each)."""
+    progress("rnn activations")
+    H = 128
+    v = np.concatenate([np.linspace(-110, 110, 90), np.linspace(-1, 1, 30), [0.0, -0.0, 1e-30, -1e-30, 17.3, 88.8, np.inf, np.nan]]).astype(np.float32)
+    W, U, x = np.zeros((H, H), np.float32), np.zeros((H, 1), np.float32), np.zeros((1, 2, 1), np.float32)
+    z, h, d = (torch.empty((1, 2, H), dtype=torch.float32, device="cuda") for _ in range(3))
+    B.rnn_forward(dev(W), dev(U), dev(v), dev(x), None, 1, 1, H, 1, z, h)
+    torch.cuda.synchronize()
+    got = h.cpu().numpy()[0, 0].astype(np.float64)
+    with np.errstate(over="ignore"):
+        want = np.where(v > 40, v.astype(np.float64), np.log1p(np.exp(v.astype(np.float64))))
+        sig = 1.0 / (1.0 + np.exp(-v.astype(np.float64)))
+    fine = np.isfinite(v) & (v > -87)            # (below: the result is denormal or zero)
+    assert np.abs(got[fine] / want[fine] - 1).max() <= 8 * 2.0 ** -24 and (got[v <= -87] <= 2e-38).all()
+    assert np.isnan(got[-1]) and got[-2] == np.inf
+    # d_0 = W^T (sigmoid(z_1) d_1) with W = 1, d_1 = g_1 = (only unit i non-zero would take 128 calls): the sum over units
+    one = np.ones((H, H), np.float32)
+    zz = np.stack([v, v])[None].astype(np.float32)
+    zz[..., -2:] = -100.0
+    g = np.stack([np.zeros(H, np.float32), np.ones(H, np.float32)])[None]
+    B.rnn_backward_sequential(dev(one), dev(zz), dev(g), 1, 2, H, d)
+    torch.cuda.synchronize()
+    total = sig[:-2].sum()
+    assert np.abs(d.cpu().numpy()[0, 0] / total - 1).max() <= 128 * 2.0 ** -24
