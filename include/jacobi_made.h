@@ -269,7 +269,7 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   batch <= 2048 from ONE cooperative launch that keeps a workgroup per CU resident and separates layers by
  *   a grid-wide barrier; 0 = one kernel launch per layer and pass.  Same results either way; on MI355X the
  *   per-layer launches are currently the faster of the two at batch 128, hence the default.
- *   MADE_OPT_FROZEN_POSITIONS (default 1; 0 or 1): models with 256 classes per position (fused output kernel): a pass
+ *   MADE_OPT_FROZEN_POSITIONS (default 1; 0 or 1): categorical models whose draw is fused into the output kernel: a pass
  *   of jacobi_sample / gs_jacobi_sample evaluates only the output positions behind the lowest position that the
  *   pass before changed in any sample still active.  The positions up to there read the inputs they read in that
  *   pass and would draw the same symbols (Proposition 1's frozen prefix, measured per pass instead of bounded by the
@@ -301,9 +301,9 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   at most 1024 units wide (1.2-1.3x; on wider layers a phase of this kernel costs more than a launch); 2 = whenever
  *   the batch fits (2048 samples).  Same symbols and pass counts as the per-layer launches.  The kernel checks that its workgroups sit on the XCDs it assumes and are
  *   all resident; if not it backs out, and this and every later call on the model take the per-layer launches.
- *   MADE_OPT_FUSED_CATEGORICAL (default 1): for C = 256, draw the Gumbel-max symbols inside the output layer's
- *   kernel (logits stay in registers); 0 = write the logits to scratch memory and draw in a second kernel, as
- *   models with other C always do.
+ *   MADE_OPT_FUSED_CATEGORICAL (default 1): draw the Gumbel-max symbols inside the output layer's kernel (C = 256:
+ *   always, logits stay in registers; other C: batches below the two tile-batch options, logits stay in LDS); 0 = write
+ *   the logits to scratch memory and draw in a second kernel.
  *   MADE_OPT_CHAINS (default 1, range 1..8): the batch is cut into this many contiguous sub-batches of whole
  *   32-sample tiles, each iterated on its own internal stream (samples are independent systems), so that the
  *   chains' dependent kernel launches can overlap.  The caller's stream waits for all of them before the call

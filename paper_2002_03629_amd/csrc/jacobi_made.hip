@@ -25,6 +25,7 @@
 #include "kernels.hpp"
 #include "resident.hpp"
 #include "onehot.hpp"
+#include "categorical_any.hpp"
 
 using namespace jm;
 
@@ -1029,7 +1030,7 @@ struct SampleIO {          // what the sampling epilogue reads and writes
   uint8_t* x;              // symbols; for a model with real states this is a float [N, D] buffer
   int t_lo, t_hi;
   RetireArgs retire;       // retire.enabled = 0: no stop test after this pass (sequential sampling)
-  const int* t_first_ptr = nullptr;   // 256-class output kernel: first position to evaluate / where the lowest changed
+  const int* t_first_ptr = nullptr;   // categorical output kernels: first position to evaluate / where the lowest changed
   int* first_changed = nullptr;       // position is recorded (see CatArgs)
   unsigned* lazy_mask = nullptr;   // Bernoulli MLP: changed rows go here as bits and the next pass derives its list from
                                    // them (see DeriveArgs); retire.enabled is 0 then
@@ -1211,6 +1212,28 @@ static int run_hidden(made_model* m, const RowSet& rs, const int* unit_limit, in
   return MADE_OK;
 }
 
+// Whether a pass over (at most) n samples of a categorical MLP draws its symbols inside the output layer's kernel.  256
+// classes: always.  Other class counts: on the lists that the 32 x 32 tile kernels would serve; longer ones multiply on
+// the large tiles and draw from logits in memory.  (512 positions of 64 classes, 100 samples: 1135 us a call with the
+// draw in a kernel of its own, 400 us with it fused.)
+static bool fused_draw(const made_model* m, int n) {
+  if (m->arch != 0 || m->real || m->C == 1 || !m->fused_categorical) return false;
+  return m->C == CAT_C || n < std::min(m->mid_batch, m->big_batch);
+}
+
+// Positions per workgroup of categorical_any_kernel for a launch over n_pos positions and pair_tiles sample tiles of 64.
+static int cat_any_positions(int C, int n_pos, int pair_tiles) {
+  // (a run that starts anywhere in a tile stays within eight tiles if it has at most 225 rows)
+  int p = std::max(1, std::min(CAT_ANY_POS, (C % TILE == 0 ? CAT_ANY_FULL : CAT_ANY_FULL - TILE + 1) / C));
+  p = std::min(p, n_pos);
+  // Shorter runs as long as the launch does not give every compute unit two workgroups (they then share a tile among
+  // several waves, each with a part of K).  A whole call, runs as long as possible / at least 512 workgroups / 1024:
+  // 512 positions of 64 classes, 100 samples 414 / 401 / 450 us; 300 of 37, 50 samples 171 / 143 / 135 us; 100 of 7,
+  // 16 samples 298 / 190 / 187 us.
+  while (p > 1 && (long long)((n_pos + p - 1) / p) * pair_tiles < 512) p = (p + 1) / 2;
+  return p;
+}
+
 // Output layer + draw for positions [t_lo, t_hi).  whole = evaluate every output tile regardless.
 static int run_output_sample(made_model* m, const RowSet& rs, const SampleIO& io, bool whole, int k_limit,
                              hipStream_t s, bool by_pos = false, const PartialSums* ps = nullptr) {
@@ -1262,7 +1285,7 @@ static int run_output_sample(made_model* m, const RowSet& rs, const SampleIO& io
     }
     launch_layer<EPI_BERNOULLI>(m, m->L, a, tile_hi - tile_lo, row_tiles, s);
     m->stats[2]++;
-  } else if (C == CAT_C && m->fused_categorical) {
+  } else if (fused_draw(m, rs.n_rows)) {
     CatArgs c;
     memset(&c, 0, sizeof c);
     c.A = a.A;
@@ -1289,7 +1312,19 @@ static int run_output_sample(made_model* m, const RowSet& rs, const SampleIO& io
     c.first_changed = io.first_changed;
     c.retire = io.retire;
     prof_mark(m, m->L, false, s);
-    if (m->dtype == MADE_BF16)
+    if (C != CAT_C) {
+      CatAnyArgs ca;
+      ca.c = c;
+      ca.C = C;
+      ca.out_cols = m->D * C;
+      ca.pos_per_wg = cat_any_positions(C, c.n_pos, c.pair_tiles);
+      ca.groups = (c.n_pos + ca.pos_per_wg - 1) / ca.pos_per_wg;
+      const dim3 grid((ca.groups + XCDS - 1) / XCDS * XCDS * c.pair_tiles);
+      if (m->dtype == MADE_BF16)
+        hipLaunchKernelGGL((categorical_any_kernel<bf16_t>), grid, dim3(CAT_ANY_WAVES * 64), 0, s, ca);
+      else
+        hipLaunchKernelGGL((categorical_any_kernel<float>), grid, dim3(CAT_ANY_WAVES * 64), 0, s, ca);
+    } else if (m->dtype == MADE_BF16)
       hipLaunchKernelGGL((categorical_output_kernel<bf16_t>), dim3(c.n_pos * c.pair_tiles), dim3(CAT_WAVES * 64), 0, s, c);
     else
       hipLaunchKernelGGL((categorical_output_kernel<float>), dim3(c.n_pos * c.pair_tiles), dim3(CAT_WAVES * 64), 0, s, c);
@@ -1834,11 +1869,10 @@ static int enqueue_pass(made_model* m, Chain& c, const Block& blk, const float* 
     io.retire.last_pass = (k == blk.cap);
     io.retire.flag_unconverged = flag_unconverged;
     io.retire.enabled = lazy_out ? 0 : 1;
-    // Frozen positions (256-class output kernel): pass k starts at the position behind the lowest one pass k - 1
+    // Frozen positions (kernels that draw inside the output layer): pass k starts at the position behind the lowest one pass k - 1
     // changed (word (k - 1) & 1; a block's first pass finds 0 there), records the lowest position it changes in word
     // 2 + (k & 1), and its tail turns that into the start of pass k + 1 and re-arms the other recording word.
-    c.frozen = m->frozen_positions && m->arch == 0 && m->C == CAT_C && m->fused_categorical && !m->real &&
-               n_bound < m->retire_split;
+    c.frozen = m->frozen_positions && fused_draw(m, n_bound) && n_bound < m->retire_split;
     if (c.frozen) {
       int* fw = c.done_ctr + FROZEN_WORDS;
       io.t_first_ptr = fw + ((k - 1) & 1);
