@@ -325,8 +325,10 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   hidden units in bf16; not 2 x 2000).  0 = never; 1 = whenever the model fits; 2 = where it pays: for
  *   gs_jacobi_sample (short passes, otherwise dominated by dependent launches: 2x and more), not for jacobi_sample
  *   (a whole-network pass streams every visible weight through one compute unit: at best even with the per-layer
- *   launches that use all of them).  Same symbols and pass counts as the per-layer path except possibly where a
- *   decision margin vanishes (see resident.hpp).
+ *   launches that use all of them).  With 2, gs_jacobi_sample on blocks of at most 32 positions and 64 units per layer
+ *   (where MADE_OPT_XCD_RESIDENT is 1) and sequential_sample in mode 1 first try the kernel that walks the positions
+ *   block by block in one launch (column.hpp: models of up to three hidden layers that fit LDS with 4 samples).  Same
+ *   symbols and pass counts as the per-layer path except possibly where a decision margin vanishes (see resident.hpp).
  *   MADE_OPT_PREFIX_CACHE (default 1): GS-Jacobi on the masked MLP keeps the activations of the hidden units whose
  *   inputs all lie before the current block (degree <= block start: they are final) after the block's first
  *   pass and only re-evaluates the units behind them (1); 0 re-evaluates every visible unit in every pass.  2: in

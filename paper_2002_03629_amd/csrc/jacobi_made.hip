@@ -26,6 +26,7 @@
 #include "resident.hpp"
 #include "onehot.hpp"
 #include "categorical_any.hpp"
+#include "column.hpp"
 
 using namespace jm;
 
@@ -271,6 +272,13 @@ struct made_model {
                                               // derives a pass's list in its first kernel instead of in the previous one's tail
   int use_xcd = 1;                            // made_set_option(MADE_OPT_XCD_RESIDENT): 0 never, 1 where it pays, 2 whenever possible
   int xcd_grid = 0;                           // workgroups of xcd_sampler_kernel (0 = not usable on this device / model)
+  // block-wise forward substitution (column_sampler_kernel): LDS layout, 0 bytes = this model does not fit
+  int col_lds_bytes = 0, col_lds_clear = 0, col_lds_red = 0;
+  int col_lds_act[COL_MAX_L + 1] = {}, col_lds_w[COL_MAX_L + 1] = {}, col_lds_cnt[COL_MAX_L] = {};
+  int* col_bounds = nullptr;                  // device: block boundaries of sequential sampling
+  int col_blocks = 0;
+  unsigned long long* col_ctr = nullptr;
+  volatile unsigned long long* col_host = nullptr;
   // sample-resident kernel (resident_sampler_kernel): LDS layout, 0 bytes = this model does not fit
   int use_resident = 2;                       // made_set_option(MADE_OPT_RESIDENT): 0 never, 1 whenever it fits, 2 where it pays
   int res_lds_bytes = 0, res_lds_enc = 0, res_lds_clear = 0;
@@ -469,6 +477,9 @@ extern "C" int made_free(made_model* m) {
     for (void* p : cv.act)
       if (p) (void)hipFree(p);
   }
+  if (m->col_bounds) (void)hipFree(m->col_bounds);
+  if (m->col_ctr) (void)hipFree(m->col_ctr);
+  if (m->col_host) (void)hipHostFree((void*)m->col_host);
   if (m->res_ctr) (void)hipFree(m->res_ctr);
   if (m->res_host) (void)hipHostFree((void*)m->res_host);
   for (hipEvent_t e : m->ev_pool) (void)hipEventDestroy(e);
@@ -608,6 +619,72 @@ static int validate_config(const made_config* cfg, const int32_t* const* degrees
   }
   if (!W[cfg->n_hidden]) return fail(MADE_ERR_ARG, "made_init: W[%d] (output layer) is NULL", cfg->n_hidden);
   return MADE_OK;
+}
+
+template <typename F>
+static void column_kernel(const made_model* m, bool seq, F&& f) {
+  auto pick = [&](auto t) {
+    using T = decltype(t);
+    if (m->L == 1) seq ? f(column_sampler_kernel<T, 1, true>) : f(column_sampler_kernel<T, 1, false>);
+    else if (m->L == 2) seq ? f(column_sampler_kernel<T, 2, true>) : f(column_sampler_kernel<T, 2, false>);
+    else seq ? f(column_sampler_kernel<T, 3, true>) : f(column_sampler_kernel<T, 3, false>);
+  };
+  if (m->dtype == MADE_BF16) pick(bf16_t{}); else pick(float{});
+}
+
+// units of one layer whose degree (1-based) lies in [a, b), at most over the layers
+static int column_units(const made_model* m, int a, int b) {
+  int most = 0;
+  for (int l = 0; l < m->L; ++l) most = std::max(most, m->cnt_lt[l][b] - m->cnt_lt[l][a]);
+  return most;
+}
+
+// Whether and how column_sampler_kernel can hold this model: LDS layout, and the blocks of sequential sampling (as many
+// positions as the lanes of a wave have units for).  A model it cannot hold keeps the other paths.
+static void plan_column(made_model* m) {
+  const int L = m->L, D = m->D;
+  if (m->C != 1 || m->real || L > COL_MAX_L) return;
+  const int es = (int)elem_size(m);
+  int off = 0;
+  for (int l = 0; l <= L; ++l) {
+    m->col_lds_act[l] = off;
+    off += m->layers[l].in_pad * COL_S * es;
+  }
+  for (int l = 0; l <= L; ++l) {
+    m->col_lds_w[l] = off;
+    off += (l == 0 ? COL_POS * COL_UNITS : l < L ? COL_UNITS * COL_UNITS : COL_UNITS * COL_POS) * (int)sizeof(float);
+  }
+  m->col_lds_clear = off;
+  m->col_lds_red = off;
+  off += COL_WAVES * COL_S * (COL_UNITS * L + COL_POS) * (int)sizeof(float);
+  for (int l = 0; l < L; ++l) {
+    m->col_lds_cnt[l] = off;
+    off += ((D + 2) * (int)sizeof(int) + 15) & ~15;
+  }
+  const int statics = 256;                               // the kernel's own small LDS arrays
+  if (off + statics > 160 * 1024) return;                // LDS of a gfx950 compute unit
+  std::vector<int> bounds(1, 0);
+  for (int a = 0; a < D; a = bounds.back()) {
+    int b = a + 1;
+    while (b < D && b - a < COL_POS && column_units(m, a, b + 1) <= COL_UNITS) ++b;
+    if (column_units(m, a, b) > COL_UNITS) break;        // (more units of one degree than a wave has lanes)
+    bounds.push_back(b);
+  }
+  hipError_t e = hipSuccess;
+  for (int seq = 0; seq < 2; ++seq)
+    column_kernel(m, seq != 0, [&](auto* kernel) {
+      if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, off);
+    });
+  if (e == hipSuccess) e = hipMalloc((void**)&m->col_ctr, 4 * sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMemset(m->col_ctr, 0, 4 * sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipHostMalloc((void**)&m->col_host, 4 * sizeof(unsigned long long), hipHostMallocDefault);
+  if (e == hipSuccess && bounds.back() == D) {
+    e = hipMalloc((void**)&m->col_bounds, bounds.size() * sizeof(int));
+    if (e == hipSuccess) e = hipMemcpy(m->col_bounds, bounds.data(), bounds.size() * sizeof(int), hipMemcpyHostToDevice);
+    if (e == hipSuccess) m->col_blocks = (int)bounds.size() - 1;
+  }
+  if (e == hipSuccess) m->col_lds_bytes = off;
+  (void)hipGetLastError();
 }
 
 extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, const float* const* W,
@@ -847,6 +924,7 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
     }
     (void)hipGetLastError();
   }
+  plan_column(m);
   *out = m;
   return MADE_OK;
 }
@@ -1226,7 +1304,7 @@ static int cat_any_positions(int C, int n_pos, int pair_tiles) {
   // (a run that starts anywhere in a tile stays within eight tiles if it has at most 225 rows)
   int p = std::max(1, std::min(CAT_ANY_POS, (C % TILE == 0 ? CAT_ANY_FULL : CAT_ANY_FULL - TILE + 1) / C));
   p = std::min(p, n_pos);
-  // Shorter runs as long as the launch does not give every compute unit two workgroups (they then share a tile among
+  // Shorter runs as long as the launch has fewer than two workgroups per compute unit to spread (they then share a tile among
   // several waves, each with a part of K).  A whole call, runs as long as possible / at least 512 workgroups / 1024:
   // 512 positions of 64 classes, 100 samples 414 / 401 / 450 us; 300 of 37, 50 samples 171 / 143 / 135 us; 100 of 7,
   // 16 samples 298 / 190 / 187 us.
@@ -2219,6 +2297,67 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
   return MADE_OK;
 }
 
+// GS-Jacobi (block > 0) or lean sequential sampling (block = 0) in one launch of column_sampler_kernel.  Sets *done when
+// the call was served this way.  GS-Jacobi blocks have to fit the kernel's lanes: at most COL_POS positions, at most
+// COL_UNITS units of a layer.  Measured (784 positions, 2 x 2000 units, bf16, us per call): blocks of 16, batch 128:
+// 446 against 1209 in xcd_sampler_kernel; batch 1 / 1024 / 8192: 449 / 449 / 3418 against 1154 / 2224 / 7496 in that
+// kernel or per-layer launches; sequential, batch 128 / 8192: 577 / 4582 against 10166 / 42015 in per-layer launches.
+static int run_column(made_model* m, const float* noise, int N, const uint8_t* x_init, uint8_t* x, int block,
+                      int32_t* iters_out, hipStream_t s, bool* done) {
+  *done = false;
+  if (m->arch != 0 || m->use_resident != 2 || m->col_lds_bytes <= 0) return MADE_OK;
+  const bool seq = block == 0;
+  if (seq ? m->col_blocks == 0 : block > COL_POS) return MADE_OK;
+  for (int a = 0; !seq && a < m->D; a += block)
+    if (column_units(m, a, std::min(a + block, m->D)) > COL_UNITS) return MADE_OK;
+  ColumnArgs p;
+  memset(&p, 0, sizeof p);
+  for (int l = 0; l <= m->L; ++l) {
+    p.W[l] = m->layers[l].W;
+    p.bias[l] = m->layers[l].bias;
+    p.k_chunks[l] = m->layers[l].k_chunks;
+    p.lds_act[l] = m->col_lds_act[l];
+    p.lds_w[l] = m->col_lds_w[l];
+    if (l < m->L) {
+      p.cnt_lt[l] = m->layers[l].cnt_lt;
+      p.lds_cnt[l] = m->col_lds_cnt[l];
+    }
+  }
+  p.lds_red = m->col_lds_red;
+  p.lds_clear = m->col_lds_clear;
+  p.bounds = seq ? m->col_bounds : nullptr;
+  p.n_blocks = seq ? m->col_blocks : (m->D + block - 1) / block;
+  p.block = block;
+  p.D = m->D;
+  p.N = N;
+  p.noise = noise;
+  p.x_init = x_init;
+  p.x = x;
+  p.iters = iters_out ? iters_out : m->ws.iters;
+  p.ctr = m->col_ctr;
+  p.host = (unsigned long long*)m->col_host;
+  prof_mark(m, m->L + 1, false, s);
+  column_kernel(m, seq, [&](auto* kernel) {
+    hipLaunchKernelGGL(kernel, dim3((N + COL_S - 1) / COL_S), dim3(COL_WAVES * 64), (size_t)m->col_lds_bytes, s, p);
+  });
+  prof_mark(m, m->L + 1, true, s);
+  HIP_TRY(hipGetLastError());
+  m->stats[2] = 1;
+  m->ws.pending = true;
+  m->ws.pending_stream = s;
+  *done = true;
+  if (seq && !m->profiling) return MADE_OK;      // (nothing to report: the caller's stream orders the result)
+  HIP_TRY(hipStreamSynchronize(s));
+  m->ws.pending = false;
+  m->stats[3] = 1;
+  prof_collect(m);
+  if (!seq) {
+    m->stats[0] = (int64_t)m->col_host[0];
+    m->stats[1] = (int64_t)m->col_host[1];
+  }
+  return MADE_OK;
+}
+
 extern "C" int sequential_sample(made_model* m, const float* noise, int32_t N, int32_t mode, uint8_t* x_out,
                                  void* stream) {
   TRY(check_call(m, noise, N, x_out, "sequential_sample"));
@@ -2229,6 +2368,13 @@ extern "C" int sequential_sample(made_model* m, const float* noise, int32_t N, i
   m->ev_layer.clear();
   TRY(settle(m, s));
   TRY(ensure_workspace(m, N, true));
+  bool done = false;
+  if (mode == 1) TRY(run_column(m, noise, N, nullptr, x_out, 0, nullptr, s, &done));
+  if (done) {
+    m->stats[0] = m->D;
+    m->stats[1] = (int64_t)m->D * N;
+    return MADE_OK;
+  }
   std::vector<Block> blocks;
   blocks.reserve(m->D);
   for (int p = 0; p < m->D; ++p) {  // p = 0-based position, its 1-based index is t = p + 1
@@ -2541,6 +2687,8 @@ extern "C" int gs_jacobi_sample(made_model* m, const float* noise, int32_t N, co
   TRY(ensure_workspace(m, N, true));
   bool done = false;
   TRY(run_persistent(m, noise, N, x_init, x_out, block, m->D, false, iters_out, s, &done));
+  if (done) return MADE_OK;
+  if (m->use_xcd == 1) TRY(run_column(m, noise, N, x_init, x_out, block, iters_out, s, &done));
   if (done) return MADE_OK;
   // (measured: the XCD-resident kernel is the faster of the two whole-call kernels up to ~256 samples, the
   // sample-resident one -- where the model fits it -- beyond)

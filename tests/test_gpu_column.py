@@ -1,0 +1,88 @@
+"""GS-Jacobi and the lean sequential sampler in the one-launch kernel that walks the positions block by block, at the
+sizes where its blocks change shape: one sample to several workgroups, one to three hidden layers, sparse and crowded
+degrees (blocks cut short by the units of a degree), positions that are no multiple of a block.  Judged by the
+oracle's fixed-point certificate and its sequential run, pass counts by the oracle's GS-Jacobi, and against the
+per-layer launches."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import made_oracle as O
+from paper_2002_03629_amd import binding as B
+from paper_2002_03629_amd import synth as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,hidden,N,dtype,blocks", [
+    (64, [256], 16, "f32", (4, 16)), (50, [77, 45], 1, "f32", (1, 7, 32)), (100, [203, 150], 37, "bf16", (3, 32)),
+    (33, [500], 5, "bf16", (2,)), (130, [96, 160, 64], 6, "bf16", (8, 31)), (20, [700, 30], 4, "f32", (1,)),
+    (40, [3, 2], 9, "bf16", (5, 32)), (300, [1000, 900], 130, "bf16", (16,)), (2, [5], 3, "f32", (1, 2))])
+def test_block_substitution(D, hidden, N, dtype, blocks):
+    w = S.Workload(f"col{D}", D, 1, hidden, dtype, N, "random", "fan_in", S.SEED_BASE + 700 + D, gain=2.5)
+    net = S.make_network(w, with_bias=True)
+    noise = S.make_noise(w)
+    ref = O.build_model(net.D, net.C, net.degrees, net.W, net.b, "bf16" if dtype == "bf16" else None)
+    xs, margin = O.sequential_sample(ref, noise)
+    clear = margin.min(axis=1) >= 1e-3
+    u = torch.from_numpy(noise).cuda()
+    x0 = np.random.default_rng(D).integers(0, 2, size=(N, D)).astype(np.uint8)
+    h = B.model_from_network(net)
+    try:
+        def call(block, init=None):
+            x = torch.full((N, D), 9, dtype=torch.uint8, device="cuda")
+            it = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+            if block:
+                B.gs_jacobi_sample(h, u, N, None if init is None else torch.from_numpy(init).cuda(), block, x, it)
+            else:
+                B.sequential_sample(h, u, N, 1, x)
+            torch.cuda.synchronize()
+            x = x.cpu().numpy()
+            ok, at = O.fixed_point_check(ref, x, noise)
+            assert (ok | (at < 1e-3)).all(), block
+            assert (x[clear] == xs[clear]).all(), block
+            return x, it.cpu().numpy(), B.made_last_stats(h)
+
+        for block in (0,) + blocks:
+            x, it, st = call(block)
+            assert st["kernels"] == 1, (block, st)
+            if block:
+                r = O.gs_jacobi_reference(ref, noise, block)
+                calm = r[3] >= 1e-3
+                assert (it[calm] == r[1][calm]).all(), block
+                assert st["sample_passes"] == it.sum()
+                xi, iti, _ = call(block, x0)
+                B.made_set_option(h, B.MADE_OPT_RESIDENT, 0)
+                B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+                xl, itl, stl = call(block, x0)
+                assert stl["kernels"] > 1
+                B.made_set_option(h, B.MADE_OPT_RESIDENT, 2)
+                B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 1)
+                assert (xi[clear] == xl[clear]).all()
+    finally:
+        B.made_free(h)
+
+
+def test_too_many_units_of_one_degree_take_the_other_paths():
+    """70 units of one degree are more than the kernel's lanes: same results, more launches."""
+    D, N = 12, 5
+    w = S.Workload("crowded", D, 1, [90], "f32", N, "random", "fan_in", S.SEED_BASE + 799, gain=2.0)
+    net = S.make_network(w, with_bias=True)
+    net.degrees[0][:70] = 4
+    noise = S.make_noise(w)
+    ref = O.build_model(net.D, net.C, net.degrees, net.W, net.b, None)
+    xs, margin = O.sequential_sample(ref, noise)
+    clear = margin.min(axis=1) >= 1e-3
+    h = B.model_from_network(net)
+    try:
+        u = torch.from_numpy(noise).cuda()
+        x = torch.empty((N, D), dtype=torch.uint8, device="cuda")
+        B.sequential_sample(h, u, N, 1, x)
+        torch.cuda.synchronize()
+        assert B.made_last_stats(h)["kernels"] > 1
+        assert (x.cpu().numpy()[clear] == xs[clear]).all()
+        B.gs_jacobi_sample(h, u, N, None, 4, x)
+        torch.cuda.synchronize()
+        assert (x.cpu().numpy()[clear] == xs[clear]).all()
+    finally:
+        B.made_free(h)
