@@ -1203,6 +1203,22 @@ static LayerArgs base_args(const made_model* m, int l, const void* A, const RowS
   return a;
 }
 
+// One-hot first layer: chunks of 256 units, one to a workgroup, so that a batch of a hundred samples fills the chip and a
+// wave's rows come two to a load (a whole call, 512 positions of 64 classes, 1024 units, 100 / 8 samples: 325 / 199 us
+// against 408 / 276 with pairs of 512-unit chunks; 512 of 256, 2048 units, 128 / 20 samples: 1443 / 689 against 1483 / 813).
+// Layers wider than that keep the pairs: enough workgroups as it is, and whole-KB requests carry the stream (1024 of 256,
+// 4096 units, 64 samples: 1462 us against 1498).  By the layer's width alone: the order of a sum is then the same in all
+// passes of a call.
+constexpr int ONEHOT_NARROW_UNITS = 2048;
+template <typename T>
+static void launch_onehot(const OnehotArgs& g, int n_rows, hipStream_t s) {
+  const int units = g.unit_end - g.unit_begin, rows = std::max(n_rows, 1);
+  if (g.pitch <= ONEHOT_NARROW_UNITS)
+    hipLaunchKernelGGL((onehot_first_layer_kernel<T, 32, false>), dim3((units + 255) / 256, rows), dim3(ONEHOT_THREADS), 0, s, g);
+  else
+    hipLaunchKernelGGL((onehot_first_layer_kernel<T, 64, true>), dim3(((units + 511) / 512 + 1) / 2, rows), dim3(ONEHOT_THREADS), 0, s, g);
+}
+
 // Hidden layers for the samples of `rs`.  unit_limit[l] < 0 means the whole layer; otherwise only the
 // first unit_limit[l] (degree-sorted) units are evaluated, reading only the first in_limit inputs.
 // unit_first (optional): units below unit_first[l] are frozen -- their inputs are final and their activations
@@ -1271,12 +1287,9 @@ static int run_hidden(made_model* m, const RowSet& rs, const int* unit_limit, in
         g.unit_end = tiles * TILE;
         g.out = a.out;
         g.out_chunks = a.out_chunks;
-        const int chunks = (g.unit_end - g.unit_begin + ONEHOT_UNITS - 1) / ONEHOT_UNITS;
         prof_mark(m, 0, false, s);
-        if (m->dtype == MADE_BF16)
-          hipLaunchKernelGGL(onehot_first_layer_kernel<bf16_t>, dim3((chunks + 1) / 2, std::max(rs.n_rows, 1)), dim3(ONEHOT_THREADS), 0, s, g);
-        else
-          hipLaunchKernelGGL(onehot_first_layer_kernel<float>, dim3((chunks + 1) / 2, std::max(rs.n_rows, 1)), dim3(ONEHOT_THREADS), 0, s, g);
+        if (m->dtype == MADE_BF16) launch_onehot<bf16_t>(g, rs.n_rows, s);
+        else launch_onehot<float>(g, rs.n_rows, s);
         prof_mark(m, 0, true, s);
         m->stats[2]++;
       }
