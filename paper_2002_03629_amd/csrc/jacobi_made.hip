@@ -27,6 +27,7 @@
 #include "onehot.hpp"
 #include "categorical_any.hpp"
 #include "column.hpp"
+#include "quad_tile.hpp"
 
 using namespace jm;
 
@@ -250,13 +251,12 @@ struct made_model {
                                               // 2 also the frozen inputs' partial sums, for lists of partial_batch samples on
                                               // (measured slower than 1 at every batch up to 32768: not the default)
   int partial_batch = 1024;                   // made_set_option(MADE_OPT_PARTIAL_SUM_BATCH)
-  int big_batch = 16384;                      // 256 x 256 tiles from here on: measured 5-12 % faster than 128 x 128 on the
-                                              // hidden layers from 16384 samples on, slower below (too few workgroups) and
-  bool big_output = false;                    // slower at every batch on the sampling layer (its epilogue needs a second
-                                              // workgroup on the compute unit to hide behind), which therefore stays on
-                                              // 128 x 128 unless made_set_option(MADE_OPT_BIG_TILE_BATCH) names a batch
-  int mid_batch = 1536;                       // made_set_option(MADE_OPT_MID_TILE_BATCH): 128 x 128 tiles from here up to
-                                              // big_batch; measured crossover with the 32 x 32 tiles near 1536
+  int big_batch = 16384;                      // batches from which 256 x 256 / 128 x 128 tiles are considered (see tile_edge).
+  int mid_batch = 1536;                       // The sampling layer takes the 256 x 256 ones only where
+  bool big_output = false;                    // made_set_option(MADE_OPT_BIG_TILE_BATCH) names a batch: its epilogue needs a
+                                              // second workgroup on the compute unit to hide behind
+  int widest_tiles = 0;                       // n_tiles of the widest layer
+  bool mid_set = false;                       // the caller named mid_batch: 128 x 128 tiles from there on whatever the grid
   int n_chains = 1;                           // made_set_option(MADE_OPT_CHAINS)
   int retire_split = 2048;                    // made_set_option(MADE_OPT_RETIRE_SPLIT); +4 % at batch 2048, +9 % at 4096 over the fused tail
   int fused_categorical = 1;                  // made_set_option(MADE_OPT_FUSED_CATEGORICAL)
@@ -573,6 +573,7 @@ extern "C" int made_set_option(made_model* m, int32_t option, int32_t value) {
   if (option == MADE_OPT_MID_TILE_BATCH) {
     if (value < 1) return fail(MADE_ERR_ARG, "made_set_option: MADE_OPT_MID_TILE_BATCH=%d must be >= 1", value);
     m->mid_batch = value;
+    m->mid_set = true;
     return MADE_OK;
   }
   if (option == MADE_OPT_RETIRE_SPLIT) {
@@ -735,6 +736,7 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
       ly.k_chunks = ly.in_pad / chunk_elems(m);
       ly.out_pad = round_up(ly.out_dim, 64);
       ly.n_tiles = ly.out_pad / TILE;
+      m->widest_tiles = std::max(m->widest_tiles, ly.n_tiles);
 
       // storage order of the output units and their degree threshold
       std::vector<int> perm(ly.out_dim), out_deg(ly.out_dim);
@@ -1163,23 +1165,72 @@ static void launch_big_t(LayerArgs a, int n_tiles, int n_rows_max, hipStream_t s
   hipLaunchKernelGGL((masked_layer_big_kernel<T, EPI, W>), dim3(groups * XCDS * other), dim3(256), 0, s, a);   // (static LDS: 128 / 64 KB)
 }
 
+template <typename T, int EPI>
+static void launch_quad_t(LayerArgs a, int n_tiles, hipStream_t s) {
+  a.n_launch_tiles = n_tiles;
+  a.row_tiles = (a.n_rows + QUAD - 1) / QUAD;
+  const int groups = ((n_tiles + 1) / 2 + XCDS - 1) / XCDS;
+  hipLaunchKernelGGL((masked_layer_quad_kernel<T, EPI>), dim3(groups * XCDS * a.row_tiles), dim3(256), 0, s, a);
+}
+
+// Which tile a layer of n_tiles 32-unit tiles is multiplied on at (up to) n_rows samples: 32, 64, 128 or 256.  A larger
+// tile reads less from L2 per product and leaves fewer workgroups, so the line is drawn by the workgroups a launch would
+// have.  Measured on whole Jacobi calls, us (bf16 unless said otherwise; D / hidden widths):
+//   32 against 64, from 176 workgroups of 64 x 64 on: 784 / 2 x 2000, batch 620 / 1000 / 1500: 185 / 255 / 338 against
+//     171 / 212 / 264; 1000 / 2 x 1200, batch 512 (152 workgroups) / 620 / 1000: 138 / 166 / 201 against 149 / 160 / 171.
+//     fp32 spends its time in the matrix cores and only loses parallelism: 784 / 2 x 2000, batch 1000: 591 against 652.
+//   64 against 128, from 200 paired workgroups of 128 x 128 on: 784 / 2 x 2000, batch 2000 / 4000 / 6500: 308 / 472 / 686
+//     against 417 / 407 / 494; 300 / 500, batch 4000 / 16000: 177 / 386 against 388 / 483; 200 / 250, 12000: 281 / 415.
+//     fp32 (32 against 128), from 320 on: 784 / 2 x 2000, batch 2048 / 4000 / 8000: 992 / 1713 / 3244 against 1673 / 2030 /
+//     2597.  Networks no wider than one 128-unit column are bound by the samples' own traffic and take the wide tile
+//     from a batch on: 64 / 120, batch 4500 / 8000 / 16000: 126 / 156 / 220 against 124 / 145 / 158; fp32 8000 / 16000:
+//     192 / 278 against 212 / 227.
+//   128 against 256, from 480 paired workgroups of 256 x 256 on: 784 / 2 x 2000, batch 20000 / 28000 / 32768: 1248 / 1676 /
+//     1847 against 1434 / 1709 / 1802; 1000 / 2 x 1200, 32768 (384 workgroups): 1745 / 1911.
+// A threshold that the caller sets applies as it is.
+static int tile_edge(const made_model* m, int epi, int n_tiles, int n_rows) {
+  const bool bf16 = m->dtype == MADE_BF16;
+  const auto paired = [&](int t) {         // workgroups of masked_layer_big_kernel with t x t tiles of 32
+    return (long long)(((n_tiles + t - 1) / t + 1) / 2) * ((n_rows + t * TILE - 1) / (t * TILE));
+  };
+  if (n_rows >= m->big_batch && (m->big_output || (epi == EPI_RELU && paired(8) >= 480))) return 256;
+  if (n_rows >= m->mid_batch &&
+      (m->mid_set || paired(4) >= (bf16 ? 200 : 320) || (m->widest_tiles <= 4 && n_rows >= (bf16 ? 6144 : 12288))))
+    return 128;
+  if ((epi == EPI_RELU || epi == EPI_BERNOULLI) && bf16 && n_rows > DERIVE_MAX_ROWS &&
+      (long long)((n_tiles + 1) / 2) * ((n_rows + QUAD - 1) / QUAD) >= 176)
+    return 64;
+  return 32;
+}
+
+// Whether every layer of an MLP takes the 32 x 32 or 64 x 64 tiles at n_rows samples (what those kernels alone can do:
+// activations by list position)
+static bool small_tiles(const made_model* m, int n_rows) {
+  for (int l = 0; l <= m->L; ++l)
+    if (tile_edge(m, l < m->L ? EPI_RELU : EPI_BERNOULLI, m->layers[l].n_tiles, n_rows) > 64) return false;
+  return true;
+}
+
 template <int EPI>
 static void launch_layer(made_model* m, int layer, const LayerArgs& a, int n_tiles, int row_tiles, hipStream_t s) {
   prof_mark(m, layer, false, s);
   // (launches that start behind cached partial sums cover few units: they stay on the 32 x 32 tiles, whose grids are
   // the larger ones there, and only that kernel takes k_begin / partial)
   const bool small_only = a.partial != nullptr || a.k_begin > 0;
-  const bool big = !small_only && a.n_rows >= m->big_batch && (EPI == EPI_RELU || m->big_output);
-  const bool mid = !small_only && !big && a.n_rows >= m->mid_batch;
-  if (m->dtype == MADE_BF16) {
-    if (big) launch_big_t<bf16_t, EPI, 4>(a, n_tiles, a.n_rows, s);
-    else if (mid) launch_big_t<bf16_t, EPI, 2>(a, n_tiles, a.n_rows, s);
-    else launch_layer_t<bf16_t, EPI>(a, n_tiles, row_tiles, s);
-  } else {
-    if (big) launch_big_t<float, EPI, 4>(a, n_tiles, a.n_rows, s);
-    else if (mid) launch_big_t<float, EPI, 2>(a, n_tiles, a.n_rows, s);
-    else launch_layer_t<float, EPI>(a, n_tiles, row_tiles, s);
-  }
+  const int edge = small_only ? 32 : tile_edge(m, EPI, n_tiles, a.n_rows);
+  const auto launch = [&](auto t) {
+    using T = decltype(t);
+    if (edge == 256) launch_big_t<T, EPI, 4>(a, n_tiles, a.n_rows, s);
+    else if (edge == 128) launch_big_t<T, EPI, 2>(a, n_tiles, a.n_rows, s);
+    else if constexpr (EPI == EPI_RELU || EPI == EPI_BERNOULLI) {
+      if (edge == 64) launch_quad_t<T, EPI>(a, n_tiles, s);
+      else launch_layer_t<T, EPI>(a, n_tiles, row_tiles, s);
+    } else {
+      launch_layer_t<T, EPI>(a, n_tiles, row_tiles, s);
+    }
+  };
+  if (m->dtype == MADE_BF16) launch(bf16_t());
+  else launch(float());
   prof_mark(m, layer, true, s);
 }
 
@@ -1227,7 +1278,7 @@ static void launch_onehot(const OnehotArgs& g, int n_rows, hipStream_t s) {
 // then runs the output layer the same way.  Only for whole-layer passes on the 32 x 32 tile kernels.
 static bool hidden_by_position(const made_model* m, const RowSet& rs, bool limited) {
   return m->arch == 0 && !limited && !m->onehot && (m->C == 1 || m->real) && rs.rows != nullptr &&
-         rs.n_rows < std::min(m->big_batch, m->mid_batch);
+         small_tiles(m, rs.n_rows);
 }
 
 // Where a forward pass keeps the network input and the hidden activations: the model's workspace (NULL), or
@@ -2087,7 +2138,7 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
     // (On the batches the large tile kernels serve, writing the activations costs what the layer costs: batch 32768,
     // 131 MB of scattered 8-byte stores, 115 us against a ~100 us launch.  There the layer is launched.)
     if (m->zero_start_fill && !x_init && m->C == 1 && !m->real && !m->onehot && blocks.size() == 1 && !blocks[0].limited &&
-        blocks[0].stop_test && c.count < std::min(m->mid_batch, m->big_batch)) {
+        blocks[0].stop_test && small_tiles(m, c.count)) {
       r.h0_bias = m->layers[0].bias;
       r.h0_out = w.act[0];
       r.h0_chunks = m->layers[1].k_chunks;

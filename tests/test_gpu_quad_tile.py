@@ -1,0 +1,62 @@
+"""Masked layers on 64 x 64 tiles, where their tiles come out ragged: odd numbers of unit tiles, rows that fill no
+tile, rows of noise and symbols that no 16-byte load may take, windows of positions that start and end inside a run of
+four, several hidden layers (activations by sample and by list position).  Judged by the oracle: hidden activations
+within bf16 rounding, symbols by the fixed-point certificate (positions whose decision margin is below 1e-3 exempt)."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import GpuModel, dev, oracle_models
+from oracle import made_oracle as O
+from paper_2002_03629_amd import binding as B
+from paper_2002_03629_amd import synth as S
+
+pytestmark = pytest.mark.gpu
+
+
+def make(D, hidden, N):
+    w = S.Workload(f"quad{D}", D, 1, hidden, "bf16", N, "random", "fan_in", S.SEED_BASE + 1100 + D + N, gain=2.5)
+    net = S.make_network(w, with_bias=True)
+    return net, oracle_models(net)[1], S.make_noise(w)
+
+
+def certify(ref, x, noise, what):
+    ok, margin = O.fixed_point_check(ref, x, noise)
+    assert (ok | (margin < 1e-3)).all(), what
+
+
+@pytest.mark.parametrize("D,hidden,N", [(1050, [1100], 641), (1056, [1100, 1057], 704), (999, [1250, 1100], 1027),
+                                        (96, [130], 6017), (330, [600, 40], 2300)])
+def test_jacobi(D, hidden, N):
+    net, ref, noise = make(D, hidden, N)
+    x0 = np.random.default_rng(D).integers(0, 2, size=(N, D)).astype(np.uint8)
+    with GpuModel(net) as g:
+        for init, chains in ((None, 1), (x0, 1), (x0, 2)):
+            B.made_set_option(g.h, B.MADE_OPT_CHAINS, chains)
+            x, it = g.jacobi(noise, init)
+            certify(ref, x, noise, (D, init is None, chains))
+            assert it.min() >= 1 and it.max() <= D
+        B.made_set_option(g.h, B.MADE_OPT_CHAINS, 1)
+        # the same rows at addresses that are multiples of 4 only
+        pad = torch.empty(N * D + 1, device="cuda")
+        pad[1:] = dev(noise).flatten()
+        xs = torch.empty(N * D + 1, dtype=torch.uint8, device="cuda")
+        B.jacobi_sample(g.h, pad[1:].view(N, D), N, dev(x0), 0, xs[1:].view(N, D), None)
+        certify(ref, xs[1:].view(N, D).cpu().numpy(), noise, (D, "unaligned"))
+        # a hidden unit is a bf16 of an fp32 sum: half an ulp of it, 2^-9, where both round the same way, one ulp else
+        for l in range(len(hidden)):
+            act = g.activations(x, l)
+            want = O.encode(x, net.C, False) if l == 0 else g.activations(x, l - 1)
+            want = np.maximum(want.astype(np.float64) @ ref.WM[l].T + ref.b[l], 0)
+            assert np.abs(act - want).max() <= 2.0 ** -8 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("D,hidden,N,block", [(330, [1100], 2300, 299), (650, [700, 650], 2051, 301)])
+def test_windows_of_positions(D, hidden, N, block):
+    net, ref, noise = make(D, hidden, N)
+    with GpuModel(net) as g:
+        B.made_set_option(g.h, B.MADE_OPT_CHAINS, 1)
+        for cache in (0, 1):
+            B.made_set_option(g.h, B.MADE_OPT_PREFIX_CACHE, cache)
+            x, _ = g.gs_jacobi(noise, block)
+            certify(ref, x, noise, (D, block, cache))
