@@ -274,13 +274,13 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   pass before changed in any sample still active.  The positions up to there read the inputs they read in that
  *   pass and would draw the same symbols (Proposition 1's frozen prefix, measured per pass instead of bounded by the
  *   pass count): same results, same pass counts, fewer of the output layer's weights streamed in the late passes.
- *   MADE_OPT_LAZY_STOP_TEST (default 1; 0 or 1): jacobi_sample of a Bernoulli model on at most 256 samples (per-layer
- *   launches): the sampling kernel of a pass only records which samples changed, and every workgroup of the next
+ *   MADE_OPT_LAZY_STOP_TEST (default 1; 0 or 1): jacobi_sample of a Bernoulli model and jacobi_sample_real on at most 256
+ *   samples (per-layer launches): the sampling kernel of a pass only records which samples changed, and every workgroup of the next
  *   pass's first kernel derives that pass's list of active samples from the record -- in the memory round trip in
  *   which it would otherwise read the list -- instead of the previous pass's last workgroup compacting it in a tail
  *   of three dependent round trips.  Same results and pass counts; 0 keeps the tail.
  *   MADE_OPT_ZERO_START (default 1; 0 or 1): jacobi_sample of a Bernoulli model with x_init = NULL (one chain, per-layer
- *   launches, batches below the MADE_OPT_MID_TILE_BATCH / MADE_OPT_BIG_TILE_BATCH thresholds): the first hidden layer of
+ *   launches, batches whose layers run on the 32 x 32 or 64 x 64 tiles): the first hidden layer of
  *   the first pass multiplies an all-zero input, so the kernel that sets the call up writes its activations, ReLU(bias),
  *   itself, and the first pass starts at the second hidden layer: one launch less per call, same results bit for bit.
  *   0 = launch the layer.
@@ -309,14 +309,13 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   chains' dependent kernel launches can overlap.  The caller's stream waits for all of them before the call
  *   returns.  With one host thread enqueuing, more chains mean proportionally more launches; at batch 128 on
  *   MI355X that costs more than the overlap gains, hence the default of a single chain.
- *   MADE_OPT_MID_TILE_BATCH (default 1536, >= 1) and MADE_OPT_BIG_TILE_BATCH (>= 1): batches (chains) of at least
- *   MID samples run the masked layers with 128 x 128 workgroup tiles staged through LDS instead of 32 x 32 tiles,
- *   those of at least BIG samples with 256 x 256 tiles (the same kernel with four times the accumulators and LDS,
- *   one workgroup per compute unit instead of two).  On the D = 784, 2 x 2000 network the 32 x 32 and 128 x 128
- *   tiles cross over near 1536 samples.  By default the hidden layers take the 256 x 256 tiles from 16384 samples on
- *   (measured 5-12 % faster there, up to 2.5x slower below 8192, where they leave compute units idle) and the
- *   sampling layer never does (slower at every batch: 0.196 against 0.175 ms at 32768); setting
- *   MADE_OPT_BIG_TILE_BATCH applies the given threshold to every layer.
+ *   MADE_OPT_MID_TILE_BATCH (>= 1) and MADE_OPT_BIG_TILE_BATCH (>= 1): batches (chains) of at least MID samples run
+ *   the masked layers with 128 x 128 workgroup tiles staged through LDS, those of at least BIG samples with 256 x 256
+ *   tiles (the same kernel with four times the accumulators and LDS, one workgroup per compute unit instead of two).
+ *   Until set, the library chooses by the workgroups a launch would have: 32 x 32 tiles, 64 x 64 ones (bf16, more than
+ *   256 samples), 128 x 128 from 1536 and 256 x 256 from 16384 samples on where they fill the chip (D = 784, 2 x 2000:
+ *   64 x 64 from about 600 samples, 128 x 128 from about 3000, 256 x 256 on the hidden layers from about 30000).  The
+ *   sampling layer takes the 256 x 256 tiles only where the option names a batch.
  *   MADE_OPT_CONV_ROWS (default 4; 2 or 4): image rows per workgroup of the convolutional model's k x k layers.
  *   MADE_OPT_RESIDENT (default 2; 0, 1 or 2): the sample-resident kernel serves jacobi_sample / gs_jacobi_sample of
  *   Bernoulli models in ONE launch: a workgroup keeps 32 samples' iterate and hidden activations in its LDS for the

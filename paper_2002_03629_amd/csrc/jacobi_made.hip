@@ -1112,7 +1112,7 @@ struct SampleIO {          // what the sampling epilogue reads and writes
   RetireArgs retire;       // retire.enabled = 0: no stop test after this pass (sequential sampling)
   const int* t_first_ptr = nullptr;   // categorical output kernels: first position to evaluate / where the lowest changed
   int* first_changed = nullptr;       // position is recorded (see CatArgs)
-  unsigned* lazy_mask = nullptr;   // Bernoulli MLP: changed rows go here as bits and the next pass derives its list from
+  unsigned* lazy_mask = nullptr;   // MLP, binary or real states: changed rows go here as bits and the next pass derives its list from
                                    // them (see DeriveArgs); retire.enabled is 0 then
 };
 
@@ -1403,6 +1403,7 @@ static int run_output_sample(made_model* m, const RowSet& rs, const SampleIO& io
     a.t_lo = io.t_lo;
     a.t_hi = io.t_hi;
     a.retire = io.retire;
+    a.lazy_mask = io.lazy_mask;
     prof_mark(m, m->L, false, s);
     if (m->dtype == MADE_BF16) launch_layer_t<bf16_t, EPI_LOGISTIC>(a, tile_hi - tile_lo, row_tiles, s);
     else launch_layer_t<float, EPI_LOGISTIC>(a, tile_hi - tile_lo, row_tiles, s);
@@ -2126,9 +2127,9 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
     r.iters = w.call_iters;
     r.done_ctr = c.done_ctr;
     r.flags = w.flags;
-    // (conditions of the tail-less stop test: Algorithm 1 of a Bernoulli MLP on one chain whose list fits one
-    // workgroup's threads and whose layers run on the 32 x 32 tile kernel)
-    c.lazy = m->lazy_retire && m->C == 1 && !m->real && blocks.size() == 1 && blocks[0].stop_test && !blocks[0].limited &&
+    // (conditions of the tail-less stop test: Algorithm 1 of a Bernoulli MLP, or of one with real states, on one chain
+    // whose list fits one workgroup's threads and whose layers run on the 32 x 32 tile kernel)
+    c.lazy = m->lazy_retire && (m->C == 1 || m->real) && blocks.size() == 1 && blocks[0].stop_test && !blocks[0].limited &&
              c.count <= DERIVE_MAX_ROWS && c.count < std::min(m->mid_batch, m->big_batch) && c.count < m->retire_split;
     r.lazy_masks = c.lazy ? w.lazy_masks : nullptr;
     r.frozen_words = c.done_ctr + FROZEN_WORDS;
@@ -2148,7 +2149,7 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
     // A call of the tail-less kind is short (cfg2: 18 launches of ~5 us each) and bound by what the host pays per
     // launch: on request it is recorded once and replayed as one graph launch (see CallGraph).  The first call with
     // a key runs launch by launch and tells how many passes to record.
-    if (m->call_graph && c.lazy && !m->profiling && s != nullptr) {   // (the null stream cannot be captured)
+    if (m->call_graph && c.lazy && !m->real && !m->profiling && s != nullptr) {   // (the null stream cannot be captured)
       for (CallGraph& g : m->graphs)
         if (g.noise == noise && g.x_init == x_init && g.x == x && g.iters == w.call_iters && g.stream == s && g.N == N &&
             g.cap == blocks[0].cap && g.pin_base == c.pin_base && g.flag_unconverged == flag_unconverged)

@@ -257,7 +257,7 @@ struct LayerArgs {
   float* xr;             // [sample, D] real states, updated in place
   float eps;
   RetireArgs retire;
-  unsigned* lazy_mask;   // EPI_BERNOULLI: changed rows are recorded as bits here instead of in `changed` (see DeriveArgs)
+  unsigned* lazy_mask;   // EPI_BERNOULLI, EPI_LOGISTIC: changed rows are recorded as bits here instead of in `changed` (see DeriveArgs)
   DeriveArgs derive;     // EPI_RELU, first layer of a pass: the list comes from the previous pass's mask words
 };
 
@@ -712,7 +712,7 @@ __device__ __forceinline__ void compute_tile(const LayerArgs& a, int rel_tile, i
 
   JM_TSTAMP(2, 1);
   __shared__ unsigned tile_mask_s;     // rows of this tile with a changed symbol (lazy stop test)
-  if (EPI == EPI_BERNOULLI && threadIdx.x == 0) tile_mask_s = 0;
+  if ((EPI == EPI_BERNOULLI || EPI == EPI_LOGISTIC) && threadIdx.x == 0) tile_mask_s = 0;
   // acc[i] is the tile element (row = 8*(i/4) + 4*h + i%4, col = r): rows come from A = samples
 #pragma unroll
   for (int i = 0; i < 16; ++i) part[wave][(i >> 2) * 8 + h * 4 + (i & 3)][r] = acc[i];
@@ -759,8 +759,12 @@ __device__ __forceinline__ void compute_tile(const LayerArgs& a, int rel_tile, i
       cnt += __shfl_xor(cnt, 4);
       cnt += __shfl_xor(cnt, 8);
       cnt += __shfl_xor(cnt, 16);
-      if (cc == 0 && cnt > 0)
-        count_old[j] = __hip_atomic_fetch_add(&a.changed[(size_t)sample * CHG], cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (cc == 0 && cnt > 0) {
+        if (a.lazy_mask)
+          atomicOr(&tile_mask_s, 1u << rr);
+        else
+          count_old[j] = __hip_atomic_fetch_add(&a.changed[(size_t)sample * CHG], cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
     } else {  // EPI_BERNOULLI: x_t = 1 iff u_t < sigmoid(z_t); count changes per sample
       int cnt = 0;
       if (row_ok && col_live) {
@@ -792,7 +796,7 @@ __device__ __forceinline__ void compute_tile(const LayerArgs& a, int rel_tile, i
 #pragma unroll
     for (int j = 0; j < EPT; ++j) asm volatile("" ::"v"(count_old[j]));
   }
-  if constexpr (EPI == EPI_BERNOULLI && !XCD_LOCAL) {
+  if constexpr ((EPI == EPI_BERNOULLI || EPI == EPI_LOGISTIC) && !XCD_LOCAL) {
     if (a.lazy_mask) {   // (uniform) one update per tile; the next kernel reads it, so nobody waits for it here
       __syncthreads();
       if (threadIdx.x == 0 && tile_mask_s)
