@@ -2655,6 +2655,21 @@ __device__ __forceinline__ void call_reset(const CallReset& r) {
   }
 }
 
+// Zeros over `bytes` bytes at any address, 16 at a time between the ragged ends.
+__device__ __forceinline__ void fill_zero(void* dst, size_t bytes, size_t tid, size_t stride) {
+  uint8_t* p = (uint8_t*)dst;
+  size_t head = (size_t)(-(uintptr_t)p & 15);
+  if (head > bytes) head = bytes;
+  const size_t mid = (bytes - head) / 16, tail = (bytes - head) % 16;
+  for (size_t i = tid; i < mid; i += stride) ((uint4*)(p + head))[i] = make_uint4(0, 0, 0, 0);
+  if (tid < head) p[tid] = 0;
+  if (tid < tail) p[head + 16 * mid + tid] = 0;
+}
+
+// Start of a call: symbols = x_init (or zeros) and their network encoding.  From zeros, binary symbols encode to zeros
+// and both arrays are plain fills of whole 32-row groups (whose padding holds zeros anyway).  Element by element, with
+// scattered 2-byte stores, the start took 53 us at batch 32768 of 784 positions; with fills the whole call went from
+// 1801 to 1763 us.  (The grid has at least 16 threads, as fill_zero's ragged ends need.)
 template <typename T>
 __global__ void init_state_kernel(const uint8_t* x_init, uint8_t* x, T* enc, int enc_chunks, int N, int D, int C, CallReset reset) {
   const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
@@ -2665,7 +2680,12 @@ __global__ void init_state_kernel(const uint8_t* x_init, uint8_t* x, T* enc, int
   float4 b_first = make_float4(0.f, 0.f, 0.f, 0.f);
   if (tid < items) b_first = *(const float4*)(reset.h0_bias + 4 * (int)(tid % quads));
   call_reset(reset);
-  const size_t total = (size_t)N * D;
+  const bool zeros = !x_init && C == 1;
+  if (zeros) {
+    if (x) fill_zero(x, (size_t)N * D, tid, stride);
+    fill_zero(enc, (size_t)((N + 31) / 32) * enc_chunks * 4096, tid, stride);   // (a block of a chunk has 4 KB)
+  }
+  const size_t total = zeros ? 0 : (size_t)N * D;
   for (size_t i = tid; i < total; i += stride) {
     const int n = (int)(i / D), t = (int)(i % D);
     const uint8_t v = x_init ? x_init[i] : 0;
@@ -2761,10 +2781,15 @@ __global__ void jgs_end_kernel(uint8_t* x, const uint8_t* xv, int np, int D, int
 template <typename T>
 __global__ void init_state_real_kernel(const float* x_init, float* x, T* enc, int enc_chunks, int N, int D, CallReset reset) {
   call_reset(reset);
-  const size_t total = (size_t)N * D;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
+  const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+  if (!x_init) {                          // (see init_state_kernel)
+    if (x) fill_zero(x, (size_t)N * D * sizeof(float), tid, stride);
+    fill_zero(enc, (size_t)((N + 31) / 32) * enc_chunks * 4096, tid, stride);
+  }
+  const size_t total = x_init ? (size_t)N * D : 0;
+  for (size_t i = tid; i < total; i += stride) {
     const int n = (int)(i / D), t = (int)(i % D);
-    const float v = x_init ? x_init[i] : 0.f;
+    const float v = x_init[i];
     if (x) x[i] = v;
     enc[frag_offset<T>(n, t, enc_chunks)] = Elem<T>::from_f32(v);
   }
