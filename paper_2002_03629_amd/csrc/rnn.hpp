@@ -237,11 +237,12 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_jacobi_kernel(RnnJacobiArg
 // meet in registers by a transposing butterfly on DPP moves: three steps halve the number of outputs a lane still
 // holds, the fourth adds the row's two halves.  No partial sum goes through LDS, and with the vector double-buffered
 // a step has one barrier.  Inputs that do not hang on the recurrence are requested RNN_AHEAD steps early.
-// What bounds a step: 64 fmas per lane (256 cycles, one wave per SIMD), then a chain of ~55 dependent instructions and
+// What bounds a step: 64 fmas per lane (256 cycles, one wave per SIMD), then a chain of ~70 dependent instructions and
 // one LDS round trip.  Against the form before it (half a column per thread, one product per LDS word, partial sums
 // and two barriers through LDS, activations from the library's expf / log1pf of ~80 instructions), H = 128, 100 steps:
-// forward 121 -> 42 us for one sequence, 129 -> 49 us for 256, 165 -> 96 us for 1024; standard backward pass
-// 104 -> 42, 123 -> 47, 137 -> 100 us.
+// forward 121 -> 49 us for one sequence, 129 -> 54 us for 256, 165 -> 107 us for 1024; standard backward pass
+// 104 -> 46, 123 -> 48, 137 -> 103 us.  (With activations that round once or twice more, from the hardware's exp2 and
+// log2, it was 42 / 47 / 92 and 42 / 44 / 95 us; their errors were two to three times the library's.)
 // ------------------------------------------------------------------------------------------------
 constexpr int RNN_AHEAD = 4;           // steps between the request of a step's inputs and their use
 
@@ -251,31 +252,59 @@ __device__ __forceinline__ float dpp_move(float v) {
 }
 constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROR8 = 0x128;
 
-// exp(x) for x <= 0 to about an ulp: the hardware's exp2 of the rounded product x log2(e), corrected to first order
-// for what the rounding left out (the product's error and log2(e)'s own).
-__device__ __forceinline__ float exp_nonpositive(float x) {
-  const float L = 1.44269502f, L_LO = 1.92596299e-8f;     // log2(e) = L + L_LO
-  const float p = x * L;
-  const float err = fmaf(x, L, -p) + x * L_LO;
-  const float e = __builtin_amdgcn_exp2f(p);
-  return fmaf(e * 0.693147182f, err, e);
+// exp(x) for -110 <= x <= 0 as hi + lo: x = n ln 2 + r with |r| <= ln 2 / 2, exp(r) = 1 + (r + r^2 s(r)) with s a
+// least-maximum fit of degree 5 (2^-34), hi the rounded sum and lo what its rounding left out; with ALL also what the
+// roundings of r and of the bracket left out.  The scaling by 2^n carries denormal results.
+struct ExpParts {
+  float hi, lo;
+};
+template <bool ALL>
+__device__ __forceinline__ ExpParts exp_nonpositive(float x) {
+#pragma clang fp contract(off)
+  const float LN2_HI = 0.693147182f, LN2_LO = -1.90465421e-9f;
+  const float n = rintf(x * 1.44269502f);
+  const float r0 = fmaf(n, -LN2_HI, x), r = fmaf(n, -LN2_LO, r0), r2 = r * r;   // (r0 is exact)
+  const float s = fmaf(fmaf(fmaf(r, 1.9790248e-4f, 1.3944759e-3f), r2, fmaf(r, 8.3334977e-3f, 4.1666295e-2f)), r2,
+                       fmaf(r, 0.16666666f, 0.5f));
+  const float t = fmaf(r2, s, r), e = 1.0f + t;
+  float lo = t - (e - 1.0f);
+  if (ALL) lo += fmaf(n, -LN2_LO, r0 - r) + fmaf(r2, s, r - t);
+  const int k = (int)n;
+  return {ldexpf(e, k), ldexpf(lo, k)};
 }
 
-// sigmoid(z) and softplus(z) from e = exp(-|z|); a NaN stays a NaN.
+// sigmoid(z) and softplus(z) from exp(-|z|); a NaN stays a NaN.  A quotient is the product with the hardware's reciprocal,
+// corrected by its residual (which takes in what the rounding of the denominator and of the exponential left out), so
+// that about one rounding is left.  Largest / mean error in units of 2^-24, z in [-20, -5], [-5, -1], [-1, 0.1], [0.1, 1],
+// [1, 5]; below it 1 / (1 + expf(-z)) and log1pf(expf(z)) of the library, several times as many instructions:
+//   sigmoid  1.35 / 0.375  1.25 / 0.369  1.20 / 0.372  1.04 / 0.400  0.79 / 0.273
+//   library  2.58 / 0.524  2.17 / 0.521  2.14 / 0.611  1.87 / 0.529  1.68 / 0.521
+//   softplus 1.00 / 0.362  1.03 / 0.363  1.17 / 0.367  1.06 / 0.366  1.00 / 0.365
+//   library  2.25 / 0.472  2.15 / 0.485  1.87 / 0.451  1.61 / 0.424  1.35 / 0.382
 __device__ __forceinline__ float rnn_sigmoid_fast(float z) {
-  const float a = fabsf(z), e = exp_nonpositive(a > 100.0f ? -100.0f : -a);
-  const float d = 1.0f + e;
-  float r = __builtin_amdgcn_rcpf(d);
-  r = fmaf(fmaf(-d, r, 1.0f), r, r);                      // one Newton step
-  return z >= 0.0f ? r : e * r;
+#pragma clang fp contract(off)
+  const float a = fabsf(z);
+  const ExpParts e = exp_nonpositive<false>(a > 110.0f ? -110.0f : -a);
+  const float d = 1.0f + e.hi, d_lo = ((1.0f - d) + e.hi) + e.lo;
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float num = z >= 0.0f ? 1.0f : e.hi, num_lo = z >= 0.0f ? 0.0f : e.lo;
+  const float q = num * r;
+  return fmaf(fmaf(-q, d_lo, fmaf(-q, d, num) + num_lo), r, q);
 }
-// log(1 + e) = e log(u) / (u - 1) with u = 1 + e as rounded (Kahan; Goldberg 1991, Theorem 4): no digits are lost
-// where e is small.
+// log(1 + e) = 2 atanh(t / 2) = t (1 + u (1 / 3 + u / 5 + ...)) with t = e / (1 + e / 2) and u = t^2 / 4 <= 1 / 9.
 __device__ __forceinline__ float rnn_softplus_fast(float z) {
-  const float a = fabsf(z), e = exp_nonpositive(a > 100.0f ? -100.0f : -a);
-  const float u = 1.0f + e, d = u - 1.0f;
-  const float l = __builtin_amdgcn_logf(u) * 0.693147182f * (e * __builtin_amdgcn_rcpf(d));
-  return (z <= 0.0f ? 0.0f : z) + (d == 0.0f ? e : l);
+#pragma clang fp contract(off)
+  const float a = fabsf(z);
+  const ExpParts e = exp_nonpositive<true>(a > 110.0f ? -110.0f : -a);
+  const float d = fmaf(e.hi, 0.5f, 1.0f), d_lo = fmaf(e.hi, 0.5f, 1.0f - d);
+  const float r = __builtin_amdgcn_rcpf(d), t = e.hi * r;
+  const float rest = fmaf(-t, d_lo, fmaf(-t, d, e.hi)) + e.lo * r;
+  const float half = 0.5f * t, u = half * half;
+  const float q = fmaf(fmaf(fmaf(fmaf(u, 0.12150466f, 0.10713829f), u, 0.14308442f), u, 0.19999439f), u, 0.33333337f);
+  const float lo = fmaf(rest, r, t * u * q);
+  const float m = z <= 0.0f ? 0.0f : z;
+  const float sum = m + t, b = sum - m, err = (m - (sum - b)) + (t - b);   // (sum + err = m + t exactly)
+  return z > 20.0f ? z : sum + (err + lo);
 }
 
 // Lane kk's k indices of an H = 32 CT wide vector: the reads of a row of 16 lanes are contiguous (16 bytes per lane
