@@ -472,23 +472,92 @@ __global__ __launch_bounds__(RnnStep<CT>::THREADS) void rnn_forward_kernel(const
 // with fp32 MFMA; wave w takes column tile w % CT and every (8 / CT)-th part of the chunk's rows.  dU and db ride
 // along on the vector units from the same p (slot 0 of the eight columns of blockIdx.z = 0 is db, the rest inputs).
 // Bound by fp32 MFMA (256 flop per clock and unit) once every compute unit has a slice.  With one slice the results
-// are stored; with several the output is zeroed first and every slice adds its sums (device-scope fp32 atomics).
-// H = 128, 100 steps: 256 sequences 30 us + 5 us of zeroing (28 TFLOP/s), one sequence 9.3 us; with a workgroup per
-// 32 x 32 tile of dW over all rows (16 workgroups, loads waited for one by one) it was 2900 us and 11.8 us.
+// are stored; with several every slice's sums go to a piece of static device memory and a kernel of its own adds them
+// in slice order, so that two calls give the same bits.
+// H = 128, 100 steps: 256 sequences 33 us in all (28.7 us for the product, 29 TFLOP/s, 4 us for the addition, 1.4 us for
+// taking a piece; 30 us when the slices were added by fp32 atomics in order of completion), one sequence 8.8 us; with a
+// workgroup per 32 x 32 tile of dW over all rows (16 workgroups, loads waited for one by one) 2900 us and 11.8 us.
 constexpr int GRAD_ROWS = 64;         // rows per chunk
 constexpr int GRAD_SLOTS = 8;         // columns of [1, x] per blockIdx.z
 
-__global__ void rnn_grads_zero_kernel(float* dW, float* dU, float* db, int n_w, int n_u, int n_b) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n_w) dW[i] = 0.0f;
-  if (i < n_u) dU[i] = 0.0f;
-  if (i < n_b) db[i] = 0.0f;
+// The slices' sums.  There are GRAD_PIECES pieces per GPU, held until the process ends.  A call with several slices takes
+// a free one at its start and gives it back at its end, both on the GPU and in stream order, under a key that no other
+// call in flight has: calls on any streams and threads, recorded ones too, never share a piece.  A call that finds none
+// free adds its slices in one workgroup per strip instead: the same sums in the same order, without the spread over
+// the chip.
+constexpr int GRAD_PIECES = 4;
+constexpr long long GRAD_PIECE_FLOATS = 5 << 18;       // 5 MiB: 64 slices of H = 128, I up to 28
+__device__ float g_grad_piece[GRAD_PIECES][GRAD_PIECE_FLOATS];
+constexpr int GRAD_KEY_SHIFT = 16;
+// 0 = free, else the key of the call that holds the piece << GRAD_KEY_SHIFT + workgroups of its adding kernel that are
+// through with it (at most GRAD_PIECE_FLOATS / 256)
+__device__ unsigned long long g_grad_owner[GRAD_PIECES];
+
+__global__ void rnn_grads_claim_kernel(unsigned long long key) {
+  for (int i = 0; i < GRAD_PIECES; ++i)
+    if (atomicCAS(&g_grad_owner[i], 0ull, key << GRAD_KEY_SHIFT) == 0ull) return;
+}
+// the piece that belongs to the call, or -1
+__device__ __forceinline__ int rnn_grads_piece(unsigned long long key) {
+  int piece = -1;
+#pragma unroll
+  for (int i = 0; i < GRAD_PIECES; ++i)
+    if (__hip_atomic_load(&g_grad_owner[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> GRAD_KEY_SHIFT == key) piece = i;
+  return piece;
+}
+
+// The slices are added in GRAD_GROUPS groups of consecutive ones, the groups' sums then in order: a thread of the adding
+// kernel has all of a group's values (of four outputs) in flight at once.
+constexpr int GRAD_GROUPS = 4;
+__host__ __device__ constexpr int grad_group(int slices) { return (slices + GRAD_GROUPS - 1) / GRAD_GROUPS; }
+__host__ __device__ constexpr long long grad_stride(int H, int I) { return ((long long)H * ((long long)H + I + 1) + 3) / 4 * 4; }
+
+__global__ __launch_bounds__(64 * GRAD_GROUPS) void rnn_grads_add_kernel(unsigned long long key, int slices, int stride, int n_w, int n_u,
+                                                                         int n_b, float* dW, float* dU, float* db) {
+  __shared__ float4 part[GRAD_GROUPS][64];
+  const int piece = rnn_grads_piece(key);
+  if (piece < 0) return;                                 // (the results are in place)
+  const int lane = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = 4 * (blockIdx.x * 64 + lane), group = grad_group(slices);
+  const float4* p = (const float4*)(g_grad_piece[piece] + min(i, stride - 4));
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  const int end = min((g + 1) * group, slices);
+  for (int s = g * group; s < end; s += 16) {
+    float4 q[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) q[k] = p[(size_t)min(s + k, end - 1) * (stride / 4)];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (s + k < end) { v.x += q[k].x; v.y += q[k].y; v.z += q[k].z; v.w += q[k].w; }
+  }
+  part[g][lane] = v;
+  __syncthreads();                                       // (everybody's part has been read)
+  if (threadIdx.x == 64) {                               // the last workgroup frees the piece
+    const unsigned long long n = __hip_atomic_fetch_add(&g_grad_owner[piece], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n + 1 == (key << GRAD_KEY_SHIFT) + gridDim.x)
+      __hip_atomic_store(&g_grad_owner[piece], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (g == 0) {
+#pragma unroll
+    for (int k = 1; k < GRAD_GROUPS; ++k) {
+      const float4 q = part[k][lane];
+      v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
+    }
+    const float o[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = i + e;
+      if (n < n_w + n_u + n_b) *(n < n_w ? dW + n : n < n_w + n_u ? dU + (n - n_w) : db + (n - n_w - n_u)) = o[e];
+    }
+  }
 }
 
 template <int CT>
 __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_param_grads_kernel(const float* z, const float* h, const float* x, const float* d,
                                                                          const float* h0, long long rows, int T, int H, int I,
-                                                                         int slice_rows, float* dW, float* dU, float* db) {
+                                                                         int slice_rows, int slices, unsigned long long key,
+                                                                         float* dW, float* dU, float* db) {
   constexpr int Hp = 32 * CT, NQ = RNN_WAVES / CT;
   constexpr int LDH = Hp % 64 == 32 ? Hp : Hp + 32;       // rows k and k + 1 of a read sit 32 banks apart
   constexpr int STAGE = GRAD_ROWS * (LDH + 32 + GRAD_SLOTS), RED = RNN_WAVES * 32 * 33;
@@ -501,9 +570,6 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_param_grads_kernel(const f
   const int u0 = blockIdx.x * 32;
   const bool gemm = blockIdx.z == 0;
   const int slot0 = blockIdx.z * GRAD_SLOTS;              // slot s of this block: s = 0: ones, else input s - 1
-  const long long r_begin = (long long)blockIdx.y * slice_rows;
-  const int n_rows = (int)max(0LL, min((long long)slice_rows, rows - r_begin));
-  const int t_begin = (int)(r_begin % T);
   const bool vec_ok = (H % 4 == 0) && (((uintptr_t)z | (uintptr_t)h | (uintptr_t)d | (uintptr_t)h0) % 16 == 0);
 
   auto load4 = [&](const float* p, int col, bool ok) {
@@ -519,6 +585,13 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_param_grads_kernel(const f
   };
   float4 hv[CT], zv, dv;
   float xv;
+  long long r_begin;
+  int n_rows, t_begin;                                    // rows of the slice, step of its first one
+  auto start = [&](int slice) {
+    r_begin = (long long)slice * slice_rows;
+    n_rows = (int)max(0LL, min((long long)slice_rows, rows - r_begin));
+    t_begin = (int)(r_begin % T);
+  };
   auto request = [&](int c) {                             // chunk c of the slice -> registers
     if (gemm) {
 #pragma unroll
@@ -542,73 +615,105 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_param_grads_kernel(const f
   };
 
   const int tj = wave % CT, q = wave / CT;                // (CT = 3: two waves without a part)
-  f32x16 acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-  float sums[GRAD_SLOTS];
-#pragma unroll
-  for (int s = 0; s < GRAD_SLOTS; ++s) sums[s] = 0.0f;
   const int unit = tid & 31, part = tid >> 5;             // [1, x] columns: thread (unit, 16th of the chunk's rows)
-  const int n_chunks = (n_rows + GRAD_ROWS - 1) / GRAD_ROWS;
-  if (n_chunks > 0) request(0);
-  for (int c = 0; c < n_chunks; ++c) {
-    __syncthreads();                                      // the chunk before has been read
+  constexpr int EPT = 32 * Hp / (RNN_WAVES * 64);         // elements of dW per thread
+  float sum_w[EPT], sum_x = 0.0f, all_w[EPT], all_x = 0.0f;   // of a slice or a group of slices; of the groups before it
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) sum_w[k] = all_w[k] = 0.0f;
+  const int slice0 = blockIdx.y;
+  start(slice0);
+  request(0);
+  // one workgroup of the strip to a slice, or (no piece) its first one to all of them
+  const int piece = slices > 1 ? rnn_grads_piece(key) : -1;
+  if (piece < 0 && slice0 > 0) return;
+  const int slice1 = piece < 0 ? slices : slice0 + 1, group = grad_group(slices);
+  for (int slice = slice0; slice < slice1; ++slice) {
+    if (slice > slice0) {
+      start(slice);
+      request(0);
+      if (slice % group == 0) {
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) { all_w[k] += sum_w[k]; sum_w[k] = 0.0f; }
+        all_x += sum_x;
+        sum_x = 0.0f;
+      }
+    }
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+    float sums[GRAD_SLOTS];
+#pragma unroll
+    for (int s = 0; s < GRAD_SLOTS; ++s) sums[s] = 0.0f;
+    const int n_chunks = (n_rows + GRAD_ROWS - 1) / GRAD_ROWS;
+    for (int c = 0; c < n_chunks; ++c) {
+      __syncthreads();                                    // the chunk before has been read
+      if (gemm) {
+#pragma unroll
+        for (int k = 0; k < CT; ++k) {
+          const int e = (tid + k * RNN_WAVES * 64) * 4;
+          *(float4*)(Hs + (e / Hp) * LDH + e % Hp) = hv[k];
+        }
+      }
+      *(float4*)(Ps + tid * 4) = make_float4(rnn_sigmoid(zv.x) * dv.x, rnn_sigmoid(zv.y) * dv.y, rnn_sigmoid(zv.z) * dv.z,
+                                             rnn_sigmoid(zv.w) * dv.w);
+      Xs[tid] = xv;
+      __syncthreads();
+      if (c + 1 < n_chunks) request(c + 1);
+      if (gemm && q < NQ) {
+#pragma unroll
+        for (int m = 0; m < GRAD_ROWS / NQ; m += 2) {
+          const int k = q * (GRAD_ROWS / NQ) + m + hh;
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Ps[k * 32 + cl], Hs[k * LDH + 32 * tj + cl], acc, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < GRAD_ROWS / 16; ++m) {
+        const int k = part * (GRAD_ROWS / 16) + m;
+        const float p = Ps[k * 32 + unit];
+#pragma unroll
+        for (int s = 0; s < GRAD_SLOTS; ++s) sums[s] = fmaf(p, Xs[k * GRAD_SLOTS + s], sums[s]);
+      }
+    }
+    // acc[e] = element (row = 8 (e / 4) + 4 hh + e % 4 -> unit of the strip, col = cl -> unit of the column tile)
+    __syncthreads();
     if (gemm) {
 #pragma unroll
-      for (int k = 0; k < CT; ++k) {
-        const int e = (tid + k * RNN_WAVES * 64) * 4;
-        *(float4*)(Hs + (e / Hp) * LDH + e % Hp) = hv[k];
+      for (int e = 0; e < 16; ++e) lds[(wave * 32 + 8 * (e >> 2) + 4 * hh + (e & 3)) * 33 + cl] = acc[e];
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) {
+        const int e = tid + k * RNN_WAVES * 64, i = e / Hp, j = e % Hp;
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NQ; ++w) s += lds[((w * CT + j / 32) * 32 + i) * 33 + j % 32];
+        sum_w[k] += s;
       }
+      __syncthreads();
     }
-    *(float4*)(Ps + tid * 4) = make_float4(rnn_sigmoid(zv.x) * dv.x, rnn_sigmoid(zv.y) * dv.y, rnn_sigmoid(zv.z) * dv.z,
-                                           rnn_sigmoid(zv.w) * dv.w);
-    Xs[tid] = xv;
+#pragma unroll
+    for (int s = 0; s < GRAD_SLOTS; ++s) lds[(part * GRAD_SLOTS + s) * 32 + unit] = sums[s];
     __syncthreads();
-    if (c + 1 < n_chunks) request(c + 1);
-    if (gemm && q < NQ) {
-#pragma unroll
-      for (int m = 0; m < GRAD_ROWS / NQ; m += 2) {
-        const int k = q * (GRAD_ROWS / NQ) + m + hh;
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Ps[k * 32 + cl], Hs[k * LDH + 32 * tj + cl], acc, 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int m = 0; m < GRAD_ROWS / 16; ++m) {
-      const int k = part * (GRAD_ROWS / 16) + m;
-      const float p = Ps[k * 32 + unit];
-#pragma unroll
-      for (int s = 0; s < GRAD_SLOTS; ++s) sums[s] = fmaf(p, Xs[k * GRAD_SLOTS + s], sums[s]);
-    }
-  }
-  const bool add = gridDim.y > 1;
-  auto put = [&](float* p, float v) {
-    if (add) unsafeAtomicAdd(p, v);
-    else *p = v;
-  };
-  // acc[e] = element (row = 8 (e / 4) + 4 hh + e % 4 -> unit of the strip, col = cl -> unit of the column tile)
-  __syncthreads();
-  if (gemm) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) lds[(wave * 32 + 8 * (e >> 2) + 4 * hh + (e & 3)) * 33 + cl] = acc[e];
-    __syncthreads();
-    for (int e = tid; e < 32 * Hp; e += RNN_WAVES * 64) {
-      const int i = e / Hp, j = e % Hp;
+    if (tid < 32 * GRAD_SLOTS) {
       float s = 0.0f;
 #pragma unroll
-      for (int w = 0; w < NQ; ++w) s += lds[((w * CT + j / 32) * 32 + i) * 33 + j % 32];
-      if (u0 + i < H && j < H) put(dW + (size_t)(u0 + i) * H + j, s);
+      for (int w = 0; w < 16; ++w) s += lds[(w * GRAD_SLOTS + (tid >> 5)) * 32 + (tid & 31)];
+      sum_x += s;
     }
-    __syncthreads();
   }
+  // (a piece: [slice][dW, dU, db])
+  float* sums_w = piece < 0 ? dW : g_grad_piece[piece] + slice0 * grad_stride(H, I);
+  float* sums_u = piece < 0 ? dU : sums_w + H * H;
+  float* sums_b = piece < 0 ? db : sums_u + H * I;
+  if (gemm) {
 #pragma unroll
-  for (int s = 0; s < GRAD_SLOTS; ++s) lds[(part * GRAD_SLOTS + s) * 32 + unit] = sums[s];
-  __syncthreads();
+    for (int k = 0; k < EPT; ++k) {
+      const int e = tid + k * RNN_WAVES * 64, i = e / Hp, j = e % Hp;
+      if (u0 + i < H && j < H) sums_w[(size_t)(u0 + i) * H + j] = all_w[k] + sum_w[k];
+    }
+  }
   if (tid < 32 * GRAD_SLOTS) {
-    const int s = tid >> 5, u = u0 + (tid & 31);
-    float tot = 0.0f;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) tot += lds[(w * GRAD_SLOTS + s) * 32 + (tid & 31)];
-    if (u < H && slot0 + s <= I) put(slot0 + s == 0 ? db + u : dU + (size_t)u * I + slot0 + s - 1, tot);
+    const int s = slot0 + (tid >> 5), u = u0 + (tid & 31);
+    if (u < H && s <= I) *(s == 0 ? sums_b + u : sums_u + (size_t)u * I + s - 1) = all_x + sum_x;
   }
 }
 

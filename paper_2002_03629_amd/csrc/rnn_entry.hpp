@@ -4,8 +4,8 @@
 #include "../../include/jacobi_rnn.h"
 #include "rnn.hpp"
 
-// rnn_param_grads: up to this many chunks of rows are summed by one workgroup per strip (a chunk takes it ~1.2 us; zeroing
-// the output in a launch of its own, the gap to it and the atomics cost about 8 us)
+// rnn_param_grads: up to this many chunks of rows are summed by one workgroup per strip (a chunk takes it ~1.2 us; taking a
+// piece and adding the slices in launches of their own, with the gaps to them, takes about 8 us)
 constexpr int GRAD_ONE_SLICE = 8;
 
 // LAUNCH(CT) with CT = the number of 32-unit tiles H units take
@@ -108,20 +108,24 @@ extern "C" int rnn_param_grads(const float* z, const float* h, const float* x, c
   if (!z || !h || !x || !d || !dW || !dU || !db) return fail(MADE_ERR_ARG, "rnn_param_grads: NULL argument");
   const int CT = (H + 31) / 32;
   const long long rows = (long long)B * T, chunks = (rows + GRAD_ROWS - 1) / GRAD_ROWS;
-  // One slice (results stored, no zeroing, no atomics) for up to GRAD_ONE_SLICE chunks, else as many as give every
-  // compute unit a workgroup.
+  // One slice (results stored at once) for up to GRAD_ONE_SLICE chunks, else as many as give every compute unit a
+  // workgroup and fit a piece.
+  const long long stride = grad_stride(H, I);
   long long slices = chunks <= GRAD_ONE_SLICE ? 1 : std::min<long long>(chunks, 256 / CT);
-  const int slice_rows = (int)std::min<long long>((std::max<long long>(chunks, 1) + slices - 1) / slices * GRAD_ROWS, 1 << 30);
+  slices = std::max<long long>(1, std::min(slices, GRAD_PIECE_FLOATS / stride));
+  const long long slice_rows = std::max<long long>(1, (chunks + slices - 1) / slices * GRAD_ROWS);
   slices = std::max<long long>(1, (rows + slice_rows - 1) / slice_rows);
   hipStream_t s = (hipStream_t)stream;
-  if (slices > 1) {
-    const int n_w = H * H, n_u = H * I;
-    hipLaunchKernelGGL(rnn_grads_zero_kernel, dim3((std::max(std::max(n_w, n_u), H) + 255) / 256), dim3(256), 0, s, dW, dU, db, n_w, n_u, H);
-  }
+  static std::atomic<unsigned long long> calls{0};
+  const unsigned long long key = ++calls;
+  if (slices > 1) hipLaunchKernelGGL(rnn_grads_claim_kernel, dim3(1), dim3(1), 0, s, key);
   const dim3 grid(CT, (unsigned)slices, I / GRAD_SLOTS + 1), block(RNN_WAVES * 64);
-#define JM_GRADS(N) hipLaunchKernelGGL(rnn_param_grads_kernel<N>, grid, block, 0, s, z, h, x, d, h0, rows, T, H, I, slice_rows, dW, dU, db)
+#define JM_GRADS(N) hipLaunchKernelGGL(rnn_param_grads_kernel<N>, grid, block, 0, s, z, h, x, d, h0, rows, T, H, I, (int)slice_rows, (int)slices, key, dW, dU, db)
   JM_RNN_BY_WIDTH(H, JM_GRADS);
 #undef JM_GRADS
+  if (slices > 1)
+    hipLaunchKernelGGL(rnn_grads_add_kernel, dim3((unsigned)((stride + 255) / 256)), dim3(64 * GRAD_GROUPS), 0, s, key, (int)slices, (int)stride,
+                       H * H, H * I, H, dW, dU, db);
   HIP_TRY(hipGetLastError());
   return MADE_OK;
 }

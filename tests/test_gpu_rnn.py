@@ -252,3 +252,39 @@ def test_activations_of_special_values():
             got = _activations(v, what) if what == "softplus" else _activations(np.where(np.isnan(v), 0, v), what)
             want = np.where(np.isnan(v) & (what == "sigmoid"), 0.5, want)
             assert np.array_equal(got, want.astype(np.float32), equal_nan=True), (what, got, want)
+
+
+@pytest.mark.parametrize("B_,T,H,I", [(180, 100, 128, 3), (40, 64, 33, 2), (70, 100, 20, 1), (30, 100, 96, 9)])
+def test_param_grads_repeat_bit_for_bit(B_, T, H, I):
+    """Gradients of many rows are summed in slices: the same bits from call to call, from eight streams at once (more
+    calls than there are places for partial sums), and from replays of a recorded call with other calls in between."""
+    progress(f"rnn gradients repeat B={B_} T={T} H={H} I={I}")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    z, h, d = (torch.randn(B_, T, H, generator=gen, device="cuda") for _ in range(3))
+    x, h0 = torch.randn(B_, T, I, generator=gen, device="cuda"), torch.randn(B_, H, generator=gen, device="cuda")
+    outputs = lambda: [torch.full(s, 7.0, device="cuda") for s in ((H, H), (H, I), (H,))]
+    call = lambda out: B.rnn_param_grads(z, h, x, d, h0, B_, T, H, I, *out)
+    first = outputs()
+    call(first)
+    torch.cuda.synchronize()
+    same = lambda out: all(torch.equal(a, b) for a, b in zip(out, first))
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    outs = [[outputs() for _ in range(6)] for _ in streams]
+    torch.cuda.synchronize()
+    for i in range(6):
+        for s, o in zip(streams, outs):
+            with torch.cuda.stream(s):
+                call(o[i])
+    torch.cuda.synchronize()
+    assert all(same(o) for stream in outs for o in stream)
+    recorded, eager = outputs(), outputs()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(recorded)
+    for _ in range(4):
+        for o in recorded + eager:
+            o.fill_(3.0)
+        graph.replay()
+        call(eager)
+        torch.cuda.synchronize()
+        assert same(recorded) and same(eager)
