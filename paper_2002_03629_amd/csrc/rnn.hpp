@@ -389,13 +389,18 @@ __global__ __launch_bounds__(RnnStep<CT>::THREADS) void rnn_backward_seq_kernel(
   float gn[RNN_AHEAD], zn[RNN_AHEAD];
 #pragma unroll
   for (int i = 0; i < RNN_AHEAD; ++i) {
-    const size_t o = (size_t)max(T - 1 - i, 0) * H;
+    const size_t o = (size_t)max(T - 2 - i, 0) * H;
     gn[i] = gs[o];
     zn[i] = zs[o];
   }
-  if (first) v[1][j] = 0.0f;
+  if (first) {                                 // the last state is g, whatever W holds
+    const size_t o = (size_t)(T - 1) * H;
+    const float dj = gs[o];
+    v[1][j] = ok ? rnn_sigmoid_fast(zs[o]) * dj : 0.0f;
+    if (ok) ds[o] = dj;
+  }
   __syncthreads();
-  rnn_steps(T, T - 1, -1, [&](auto I, int t) {
+  rnn_steps(T - 1, T - 2, -1, [&](auto I, int t) {
     constexpr int i = decltype(I)::value;
     const float gt = gn[i], st = rnn_sigmoid_fast(zn[i]);
     const size_t o = (size_t)max(t - RNN_AHEAD, 0) * H;

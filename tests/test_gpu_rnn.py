@@ -288,3 +288,16 @@ def test_param_grads_repeat_bit_for_bit(B_, T, H, I):
         call(eager)
         torch.cuda.synchronize()
         assert same(recorded) and same(eager)
+
+
+@pytest.mark.parametrize("T", [1, 2, 5])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_last_state_does_not_read_the_weights(T, bad):
+    """d_T = g_T in the standard backward pass, also with weights that are infinite or no numbers."""
+    B_, H = 2, 33
+    r = np.random.default_rng(2)
+    z, g = (r.standard_normal((B_, T, H)).astype(np.float32) for _ in range(2))
+    W = np.full((H, H), bad, np.float32)
+    d = torch.empty((B_, T, H), dtype=torch.float32, device="cuda")
+    B.rnn_backward_sequential(dev(W), dev(z), dev(g), B_, T, H, d)
+    assert np.array_equal(d.cpu().numpy()[:, -1], g[:, -1])
