@@ -1171,7 +1171,7 @@ static void launch_quad_t(LayerArgs a, int n_tiles, hipStream_t s) {
   a.n_launch_tiles = n_tiles;
   a.row_tiles = (a.n_rows + QUAD - 1) / QUAD;
   const int groups = ((n_tiles + 1) / 2 + XCDS - 1) / XCDS;
-  hipLaunchKernelGGL((masked_layer_quad_kernel<T, EPI>), dim3(groups * XCDS * a.row_tiles), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((masked_layer_quad_kernel<T, EPI>), dim3(groups * XCDS * a.row_tiles), dim3(NW * 64), 0, s, a);
 }
 
 // Which tile a layer of n_tiles 32-unit tiles is multiplied on at (up to) n_rows samples: 32, 64, 128 or 256.  A larger

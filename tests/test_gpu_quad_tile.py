@@ -60,3 +60,30 @@ def test_windows_of_positions(D, hidden, N, block):
             B.made_set_option(g.h, B.MADE_OPT_PREFIX_CACHE, cache)
             x, _ = g.gs_jacobi(noise, block)
             certify(ref, x, noise, (D, block, cache))
+
+
+@pytest.mark.parametrize("D,hidden,N", [(60, [1100, 1057], 900), (41, [1900], 1100), (30, [700, 2100], 641)])
+def test_real_states_equal_the_sequential_ones_bit_for_bit(D, hidden, N):
+    """Passes of one call run on 64 x 64 or 32 x 32 tiles, by the number of samples still active; with tolerance 0 the
+    states are those of the sequential samplers (whose narrow launches take 32 x 32 tiles) to the last bit, every time."""
+    w = S.Workload(f"quadreal{D}", D, 2, hidden, "bf16", N, "random", "fan_in", S.SEED_BASE + 1400 + D, gain=1.5, real=True)
+    net = S.make_network(w, with_bias=True)
+    noise = dev(np.random.default_rng(D).logistic(size=(N, D)).astype(np.float32))
+    h = B.model_from_network(net)
+    try:
+        want = torch.empty((N, D), device="cuda")
+        B.sequential_sample_real(h, noise, N, 0, want)
+        got = torch.empty((N, D), device="cuda")
+        B.sequential_sample_real(h, noise, N, 1, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        for init in (None, torch.randn(N, D, device="cuda", generator=torch.Generator("cuda").manual_seed(1))):
+            for _ in range(4):
+                B.jacobi_sample_real(h, noise, N, init, 0.0, 0, got)
+                torch.cuda.synchronize()
+                assert torch.equal(got, want), int((got != want).sum())
+        B.gs_jacobi_sample_real(h, noise, N, None, 7, 0.0, got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    finally:
+        B.made_free(h)
