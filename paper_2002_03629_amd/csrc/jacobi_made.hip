@@ -1189,10 +1189,14 @@ static void launch_quad_t(LayerArgs a, int n_tiles, hipStream_t s) {
 //   128 against 256, from 480 paired workgroups of 256 x 256 on: 784 / 2 x 2000, batch 20000 / 28000 / 32768: 1248 / 1676 /
 //     1847 against 1434 / 1709 / 1802; 1000 / 2 x 1200, 32768 (384 workgroups): 1745 / 1911.
 // A threshold that the caller sets applies as it is.
-static int tile_edge(const made_model* m, int epi, int n_tiles, int n_rows) {
+// The 32 and 64 tiles sum in one order, the 128 and 256 ones in another.  With real states, where a change of order moves
+// the states themselves, the line between the two is drawn by the whole layer also for launches that cover a part of it:
+// the two modes of the sequential sampler then give the same bits.
+static int tile_edge(const made_model* m, int epi, int layer, int n_tiles, int n_rows) {
   const bool bf16 = m->dtype == MADE_BF16;
+  const int line_tiles = m->real ? m->layers[layer].n_tiles : n_tiles;
   const auto paired = [&](int t) {         // workgroups of masked_layer_big_kernel with t x t tiles of 32
-    return (long long)(((n_tiles + t - 1) / t + 1) / 2) * ((n_rows + t * TILE - 1) / (t * TILE));
+    return (long long)(((line_tiles + t - 1) / t + 1) / 2) * ((n_rows + t * TILE - 1) / (t * TILE));
   };
   if (n_rows >= m->big_batch && (m->big_output || (epi == EPI_RELU && paired(8) >= 480))) return 256;
   if (n_rows >= m->mid_batch &&
@@ -1208,7 +1212,7 @@ static int tile_edge(const made_model* m, int epi, int n_tiles, int n_rows) {
 // activations by list position)
 static bool small_tiles(const made_model* m, int n_rows) {
   for (int l = 0; l <= m->L; ++l)
-    if (tile_edge(m, l < m->L ? EPI_RELU : EPI_BERNOULLI, m->layers[l].n_tiles, n_rows) > 64) return false;
+    if (tile_edge(m, l < m->L ? EPI_RELU : EPI_BERNOULLI, l, m->layers[l].n_tiles, n_rows) > 64) return false;
   return true;
 }
 
@@ -1218,7 +1222,7 @@ static void launch_layer(made_model* m, int layer, const LayerArgs& a, int n_til
   // (launches that start behind cached partial sums cover few units: they stay on the 32 x 32 tiles, whose grids are
   // the larger ones there, and only that kernel takes k_begin / partial)
   const bool small_only = a.partial != nullptr || a.k_begin > 0;
-  const int edge = small_only ? 32 : tile_edge(m, EPI, n_tiles, a.n_rows);
+  const int edge = small_only ? 32 : tile_edge(m, EPI, layer, n_tiles, a.n_rows);
   const auto launch = [&](auto t) {
     using T = decltype(t);
     if (edge == 256) launch_big_t<T, EPI, 4>(a, n_tiles, a.n_rows, s);

@@ -87,3 +87,22 @@ def test_real_states_equal_the_sequential_ones_bit_for_bit(D, hidden, N):
         assert torch.equal(got, want)
     finally:
         B.made_free(h)
+
+
+@pytest.mark.parametrize("dtype,N", [("bf16", 5300), ("f32", 8300)])
+def test_sequential_modes_of_real_states_on_large_batches(dtype, N):
+    """Whole-layer and narrow launches of the sequential samplers sum in the same order also where whole layers take the
+    128 x 128 tiles: the same states to the last bit."""
+    D = 24
+    w = S.Workload(f"seqreal{dtype}", D, 2, [1100, 1100], dtype, N, "random", "fan_in", S.SEED_BASE + 1450, gain=1.5, real=True)
+    net = S.make_network(w, with_bias=True)
+    noise = dev(np.random.default_rng(D).logistic(size=(N, D)).astype(np.float32))
+    h = B.model_from_network(net)
+    try:
+        out = [torch.empty((N, D), device="cuda") for _ in range(2)]
+        for mode in (0, 1):
+            B.sequential_sample_real(h, noise, N, mode, out[mode])
+        torch.cuda.synchronize()
+        assert torch.equal(*out), int((out[0] != out[1]).sum())
+    finally:
+        B.made_free(h)
