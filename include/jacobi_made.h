@@ -310,8 +310,9 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   returns.  With one host thread enqueuing, more chains mean proportionally more launches; at batch 128 on
  *   MI355X that costs more than the overlap gains, hence the default of a single chain.
  *   MADE_OPT_MID_TILE_BATCH (>= 1) and MADE_OPT_BIG_TILE_BATCH (>= 1): batches (chains) of at least MID samples run
- *   the masked layers with 128 x 128 workgroup tiles staged through LDS, those of at least BIG samples with 256 x 256
- *   tiles (the same kernel with four times the accumulators and LDS, one workgroup per compute unit instead of two).
+ *   the masked layers with 128 x 128 workgroup tiles staged through LDS, smaller ones with 32 x 32 tiles, those of at
+ *   least BIG samples with 256 x 256 tiles (the 128 x 128 kernel with four times the accumulators and LDS, one workgroup
+ *   per compute unit instead of two).
  *   Until set, the library chooses by the workgroups a launch would have: 32 x 32 tiles, 64 x 64 ones (bf16, more than
  *   256 samples), 128 x 128 from 1536 and 256 x 256 from 16384 samples on where they fill the chip (D = 784, 2 x 2000:
  *   64 x 64 from about 600 samples, 128 x 128 from about 3000, 256 x 256 on the hidden layers from about 30000).  The

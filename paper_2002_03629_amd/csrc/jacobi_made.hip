@@ -257,7 +257,7 @@ struct made_model {
   bool big_output = false;                    // made_set_option(MADE_OPT_BIG_TILE_BATCH) names a batch: its epilogue needs a
                                               // second workgroup on the compute unit to hide behind
   int widest_tiles = 0;                       // n_tiles of the widest layer
-  bool mid_set = false;                       // the caller named mid_batch: 128 x 128 tiles from there on whatever the grid
+  bool mid_set = false;                       // the caller named mid_batch: 128 x 128 tiles from there on whatever the grid, 32 x 32 below
   int n_chains = 1;                           // made_set_option(MADE_OPT_CHAINS)
   int retire_split = 2048;                    // made_set_option(MADE_OPT_RETIRE_SPLIT); +4 % at batch 2048, +9 % at 4096 over the fused tail
   int fused_categorical = 1;                  // made_set_option(MADE_OPT_FUSED_CATEGORICAL)
@@ -1188,7 +1188,7 @@ static void launch_quad_t(LayerArgs a, int n_tiles, hipStream_t s) {
 //     192 / 278 against 212 / 227.
 //   128 against 256, from 480 paired workgroups of 256 x 256 on: 784 / 2 x 2000, batch 20000 / 28000 / 32768: 1248 / 1676 /
 //     1847 against 1434 / 1709 / 1802; 1000 / 2 x 1200, 32768 (384 workgroups): 1745 / 1911.
-// A threshold that the caller sets applies as it is.
+// A threshold that the caller sets applies as it is; below a MADE_OPT_MID_TILE_BATCH the tiles are then 32 x 32.
 // The 32 and 64 tiles sum in one order, the 128 and 256 ones in another.  With real states, where a change of order moves
 // the states themselves, the line between the two is drawn by the whole layer also for launches that cover a part of it:
 // the two modes of the sequential sampler then give the same bits.
@@ -1202,7 +1202,7 @@ static int tile_edge(const made_model* m, int epi, int layer, int n_tiles, int n
   if (n_rows >= m->mid_batch &&
       (m->mid_set || paired(4) >= (bf16 ? 200 : 320) || (m->widest_tiles <= 4 && n_rows >= (bf16 ? 6144 : 12288))))
     return 128;
-  if ((epi == EPI_RELU || epi == EPI_BERNOULLI) && bf16 && n_rows > DERIVE_MAX_ROWS &&
+  if ((epi == EPI_RELU || epi == EPI_BERNOULLI) && bf16 && !m->mid_set && n_rows > DERIVE_MAX_ROWS &&
       (long long)((n_tiles + 1) / 2) * ((n_rows + QUAD - 1) / QUAD) >= 176)
     return 64;
   return 32;

@@ -254,9 +254,9 @@ def test_cfg2_batch_8192_stop_test_as_its_own_kernel():
 
 @pytest.mark.parametrize("N", [1535, 1536, 1537, 2047, 2048, 2049, 2600])
 def test_batches_around_the_tile_and_stop_test_thresholds(N):
-    """Library defaults on batches just below, at and above the sizes where the layers move to the LDS-staged
-    128 x 128 tiles (1536) and the stop test becomes a kernel of its own (2048); late passes of the same call fall
-    back below both.  Whole batch by the fixed-point certificate; pass counts against a run that stays on the
+    """Batches just below, at and above the sizes where the layers are told to move to the LDS-staged 128 x 128 tiles
+    (1536, by option) and the stop test becomes a kernel of its own (2048, the default); late passes of the same call
+    fall back below both.  Whole batch by the fixed-point certificate; pass counts against a run that stays on the
     32 x 32 tiles with the fused stop test."""
     import dataclasses
     import gpu_util
@@ -267,7 +267,7 @@ def test_batches_around_the_tile_and_stop_test_thresholds(N):
     old = gpu_util.CHAINS, gpu_util.RETIRE_SPLIT
     try:
         gpu_util.CHAINS, gpu_util.RETIRE_SPLIT = 1, None
-        with GpuModel(net) as g:
+        with GpuModel(net, mid_tile_batch=1536) as g:
             x, it = g.jacobi(noise)
             xb, _ = g.gs_jacobi(noise, 50)
         gpu_util.RETIRE_SPLIT = 1 << 30
@@ -284,8 +284,8 @@ def test_batches_around_the_tile_and_stop_test_thresholds(N):
 
 
 def test_four_chains_of_large_sub_batches():
-    """8200 samples cut into four chains on their own streams: each chain runs the 128 x 128 tiles and its own
-    stand-alone stop test concurrently with the others.  Whole batch by the fixed-point certificate, pass counts
+    """8200 samples cut into four chains on their own streams: each chain runs the 128 x 128 tiles (from 1536 samples on, by
+    option) and its own stand-alone stop test concurrently with the others.  Whole batch by the fixed-point certificate, pass counts
     against the single-chain run."""
     import dataclasses
     import gpu_util
@@ -298,7 +298,7 @@ def test_four_chains_of_large_sub_batches():
         out = []
         for chains in (4, 1):
             gpu_util.CHAINS, gpu_util.RETIRE_SPLIT = chains, None
-            with GpuModel(net) as g:
+            with GpuModel(net, mid_tile_batch=1536) as g:
                 out.append(g.jacobi(noise))
     finally:
         gpu_util.CHAINS, gpu_util.RETIRE_SPLIT = old

@@ -51,6 +51,21 @@ def test_jacobi(D, hidden, N):
             assert np.abs(act - want).max() <= 2.0 ** -8 * np.abs(want).max()
 
 
+@pytest.mark.parametrize("D,hidden,N", [(300, [1100, 1057], 900), (96, [130], 5700), (784, [2000, 2000], 257)])
+def test_same_bits_as_the_32_x_32_tiles(D, hidden, N):
+    """Hidden activations, symbols and pass counts against a model that MADE_OPT_MID_TILE_BATCH keeps on the 32 x 32 tiles."""
+    net, _, noise = make(D, hidden, N)
+    x0 = np.random.default_rng(D).integers(0, 2, size=(N, D)).astype(np.uint8)
+    with GpuModel(net) as g, GpuModel(net, mid_tile_batch=1 << 30) as small:
+        for h in (g.h, small.h):
+            B.made_set_option(h, B.MADE_OPT_CHAINS, 1)
+        for l in range(len(hidden)):
+            assert (g.activations(x0, l) == small.activations(x0, l)).all(), l
+        for init in (None, x0):
+            (x, it), (xs, its) = g.jacobi(noise, init), small.jacobi(noise, init)
+            assert (x == xs).all() and (it == its).all()
+
+
 @pytest.mark.parametrize("D,hidden,N,block", [(330, [1100], 2300, 299), (650, [700, 650], 2051, 301)])
 def test_windows_of_positions(D, hidden, N, block):
     net, ref, noise = make(D, hidden, N)
