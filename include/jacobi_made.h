@@ -315,8 +315,8 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   per compute unit instead of two).
  *   Until set, the library chooses by the workgroups a launch would have: 32 x 32 tiles, 64 x 64 ones (bf16, more than
  *   256 samples), 128 x 128 from 1536 and 256 x 256 from 16384 samples on where they fill the chip (D = 784, 2 x 2000:
- *   64 x 64 from about 600 samples, 128 x 128 from about 3000, 256 x 256 on the hidden layers from about 30000).  The
- *   sampling layer takes the 256 x 256 tiles only where the option names a batch.
+ *   64 x 64 from about 350 samples, 128 x 128 from about 2300).  The sampling layer takes the 256 x 256 tiles only where
+ *   the option names a batch.
  *   MADE_OPT_CONV_ROWS (default 4; 2 or 4): image rows per workgroup of the convolutional model's k x k layers.
  *   MADE_OPT_RESIDENT (default 2; 0, 1 or 2): the sample-resident kernel serves jacobi_sample / gs_jacobi_sample of
  *   Bernoulli models in ONE launch: a workgroup keeps 32 samples' iterate and hidden activations in its LDS for the

@@ -1176,18 +1176,24 @@ static void launch_quad_t(LayerArgs a, int n_tiles, hipStream_t s) {
 
 // Which tile a layer of n_tiles 32-unit tiles is multiplied on at (up to) n_rows samples: 32, 64, 128 or 256.  A larger
 // tile reads less from L2 per product and leaves fewer workgroups, so the line is drawn by the workgroups a launch would
-// have.  Measured on whole Jacobi calls, us (bf16 unless said otherwise; D / hidden widths):
-//   32 against 64, from 176 workgroups of 64 x 64 on: 784 / 2 x 2000, batch 620 / 1000 / 1500: 185 / 255 / 338 against
-//     171 / 212 / 264; 1000 / 2 x 1200, batch 512 (152 workgroups) / 620 / 1000: 138 / 166 / 201 against 149 / 160 / 171.
-//     fp32 spends its time in the matrix cores and only loses parallelism: 784 / 2 x 2000, batch 1000: 591 against 652.
-//   64 against 128, from 200 paired workgroups of 128 x 128 on: 784 / 2 x 2000, batch 2000 / 4000 / 6500: 308 / 472 / 686
-//     against 417 / 407 / 494; 300 / 500, batch 4000 / 16000: 177 / 386 against 388 / 483; 200 / 250, 12000: 281 / 415.
-//     fp32 (32 against 128), from 320 on: 784 / 2 x 2000, batch 2048 / 4000 / 8000: 992 / 1713 / 3244 against 1673 / 2030 /
-//     2597.  Networks no wider than one 128-unit column are bound by the samples' own traffic and take the wide tile
+// have.  Measured in us (bf16 unless said otherwise; D / hidden widths), J on whole Jacobi calls, F on one forward pass
+// (every launch at the full batch):
+//   32 against 64, from 176 workgroups of 64 x 64 on: 784 / 2 x 2000, batch 300 (160 workgroups) / 620 / 1000 / 1500: J 167 /
+//     212 / 263 / 361 against 177 / 194 / 218 / 296; 1000 / 2 x 1200, batch 512 (152) / 620 / 1000: J 166 / 205 / 239 against
+//     172 / 197 / 209.  Not for sampling layers whose rows no 16-byte access may take (D no multiple of 16) with four chunks of
+//     inputs or fewer: half of the eight waves have none, and the wide epilogue is then what counts: 200 / 250, batch
+//     4000 / 16384: J 171 / 325 against 200 / 413.  fp32 spends its time in the matrix cores and only loses parallelism.
+//   64 against 128, from 144 paired workgroups of 128 x 128 on: 784 / 2 x 2000, batch 2048 (128) / 2300 / 3000 / 4096: F 88 / 97 /
+//     117 / 151 against 99 / 100 / 101 / 103; 200 / 2 x 1100 (real states), batch 2048 (80) / 3000 (120) / 4096: J 519 / 638 / 774
+//     against 584 / 645 / 686.  fp32 (32 against 128), from 224 on: 784 / 2 x 2000, batch 3000 (192) / 3500 / 4096: F 376 / 436 /
+//     498 against 414 / 416 / 418; 200 / 2 x 1100, batch 4096 (160) / 6000: J 2677 / 3696 against 3021 / 3398.
+//     A sampling layer of such rows waits until 320: 300 / 500, batch 4000 / 8000 / 16384 (256) / 32768 (512): J 217 / 298 / 470 / 791 against 419 / 495 / 507 / 630.
+//     Networks no wider than one 128-unit column are bound by the samples' own traffic and take the wide tile
 //     from a batch on: 64 / 120, batch 4500 / 8000 / 16000: 126 / 156 / 220 against 124 / 145 / 158; fp32 8000 / 16000:
 //     192 / 278 against 212 / 227.
-//   128 against 256, from 480 paired workgroups of 256 x 256 on: 784 / 2 x 2000, batch 20000 / 28000 / 32768: 1248 / 1676 /
-//     1847 against 1434 / 1709 / 1802; 1000 / 2 x 1200, 32768 (384 workgroups): 1745 / 1911.
+//   128 against 256, where the paired workgroups of 256 x 256 fill nine tenths of their last round over the compute units:
+//     784 / 2 x 2000, batch 16384 (256 workgroups) / 24000 (376) / 32768 (512): J 948 / 1437 / 1865 against 934 / 1556 / 1818;
+//     1000 / 2 x 1200, 16384 (192) / 32768 (384): J 935 / 1689 against 1032 / 1860.
 // A threshold that the caller sets applies as it is; below a MADE_OPT_MID_TILE_BATCH the tiles are then 32 x 32.
 // The 32 and 64 tiles sum in one order, the 128 and 256 ones in another.  With real states, where a change of order moves
 // the states themselves, the line between the two is drawn by the whole layer also for launches that cover a part of it:
@@ -1198,12 +1204,14 @@ static int tile_edge(const made_model* m, int epi, int layer, int n_tiles, int n
   const auto paired = [&](int t) {         // workgroups of masked_layer_big_kernel with t x t tiles of 32
     return (long long)(((line_tiles + t - 1) / t + 1) / 2) * ((n_rows + t * TILE - 1) / (t * TILE));
   };
-  if (n_rows >= m->big_batch && (m->big_output || (epi == EPI_RELU && paired(8) >= 480))) return 256;
+  const long long p8 = paired(8), rounds = (p8 + 255) / 256;
+  if (n_rows >= m->big_batch && (m->big_output || (epi == EPI_RELU && 10 * p8 >= 9 * 256 * rounds))) return 256;
+  const int line = epi == EPI_BERNOULLI && m->D % 16 != 0 ? 320 : bf16 ? 144 : 224;
   if (n_rows >= m->mid_batch &&
-      (m->mid_set || paired(4) >= (bf16 ? 200 : 320) || (m->widest_tiles <= 4 && n_rows >= (bf16 ? 6144 : 12288))))
+      (m->mid_set || paired(4) >= line || (m->widest_tiles <= 4 && n_rows >= (bf16 ? 6144 : 12288))))
     return 128;
   if ((epi == EPI_RELU || epi == EPI_BERNOULLI) && bf16 && !m->mid_set && n_rows > DERIVE_MAX_ROWS &&
-      (long long)((n_tiles + 1) / 2) * ((n_rows + QUAD - 1) / QUAD) >= 176)
+      (epi == EPI_RELU || m->D % 16 == 0 || m->layers[layer].k_chunks > NW / 2) && (long long)((n_tiles + 1) / 2) * ((n_rows + QUAD - 1) / QUAD) >= 176)
     return 64;
   return 32;
 }
