@@ -224,6 +224,7 @@ struct made_model {
   bool onehot = false;                        // categorical symbols enter as one-hot vectors: the first layer is a sum of
                                               // one weight row per position (layers[0].W is [D][C][out_pad], see made_init)
   float call_eps = 0.f;                       // forward-difference tolerance of the current *_real call
+  int call_rows = 0;                          // samples of the current call
   ConvNet conv;
   int D = 0, C = 1, L = 0, dtype = MADE_F32, device = 0;
   std::vector<int> hidden;
@@ -1196,19 +1197,22 @@ static void launch_quad_t(LayerArgs a, int n_tiles, hipStream_t s) {
 //     1000 / 2 x 1200, 16384 (192) / 32768 (384): J 935 / 1689 against 1032 / 1860.
 // A threshold that the caller sets applies as it is; below a MADE_OPT_MID_TILE_BATCH the tiles are then 32 x 32.
 // The 32 and 64 tiles sum in one order, the 128 and 256 ones in another.  With real states, where a change of order moves
-// the states themselves, the line between the two is drawn by the whole layer also for launches that cover a part of it:
-// the two modes of the sequential sampler then give the same bits.
+// the states themselves, the line between the two is drawn by the whole layer and the call's batch, also for launches that
+// cover a part of the layer or of the batch: all samplers then give the same bits, and no pass has to settle again what
+// the passes before it had settled in another order (200 / 2 x 1100, J, against the line at the rows still active: fp32,
+// batch 6000 / 8192: 3400 / 5150 against 3730 / 6700; bf16, batch 4096 / 8192, whose last passes of few samples would be
+// faster on the small tiles: 780 / 1077 against 725 / 1000).
 static int tile_edge(const made_model* m, int epi, int layer, int n_tiles, int n_rows) {
   const bool bf16 = m->dtype == MADE_BF16;
-  const int line_tiles = m->real ? m->layers[layer].n_tiles : n_tiles;
+  const int line_tiles = m->real ? m->layers[layer].n_tiles : n_tiles, line_rows = m->real ? m->call_rows : n_rows;
   const auto paired = [&](int t) {         // workgroups of masked_layer_big_kernel with t x t tiles of 32
-    return (long long)(((line_tiles + t - 1) / t + 1) / 2) * ((n_rows + t * TILE - 1) / (t * TILE));
+    return (long long)(((line_tiles + t - 1) / t + 1) / 2) * ((line_rows + t * TILE - 1) / (t * TILE));
   };
   const long long p8 = paired(8), rounds = (p8 + 255) / 256;
-  if (n_rows >= m->big_batch && (m->big_output || (epi == EPI_RELU && 10 * p8 >= 9 * 256 * rounds))) return 256;
+  if (line_rows >= m->big_batch && (m->big_output || (epi == EPI_RELU && 10 * p8 >= 9 * 256 * rounds))) return 256;
   const int line = epi == EPI_BERNOULLI && m->D % 16 != 0 ? 320 : bf16 ? 144 : 224;
-  if (n_rows >= m->mid_batch &&
-      (m->mid_set || paired(4) >= line || (m->widest_tiles <= 4 && n_rows >= (bf16 ? 6144 : 12288))))
+  if (line_rows >= m->mid_batch &&
+      (m->mid_set || paired(4) >= line || (m->widest_tiles <= 4 && line_rows >= (bf16 ? 6144 : 12288))))
     return 128;
   if ((epi == EPI_RELU || epi == EPI_BERNOULLI) && bf16 && !m->mid_set && n_rows > DERIVE_MAX_ROWS &&
       (epi == EPI_RELU || m->D % 16 == 0 || m->layers[layer].k_chunks > NW / 2) && (long long)((n_tiles + 1) / 2) * ((n_rows + QUAD - 1) / QUAD) >= 176)
@@ -2098,6 +2102,7 @@ static int give_up_waiting(made_model* m, hipStream_t s) {
 static int run_chains(made_model* m, const std::vector<Block>& blocks, const float* noise, const uint8_t* x_init,
                       uint8_t* x, int N, bool flag_unconverged, int32_t* iters_out, hipStream_t s) {
   Workspace& w = m->ws;
+  m->call_rows = N;
   // split the batch into chains of whole 32-sample tiles
   int want = std::max(1, std::min(m->n_chains, (N + TILE - 1) / TILE));
   if (m->arch == 1) want = 1;   // the convolutional trunk always runs the whole batch
@@ -2797,6 +2802,7 @@ extern "C" int made_forward_params(made_model* m, const float* x, int32_t N, flo
   TRY(settle(m, s));
   TRY(ensure_workspace(m, N, false));
   TRY(launch_init_state(m, (const uint8_t*)x, nullptr, N, s));
+  m->call_rows = N;
   RowSet rs{nullptr, nullptr, N};
   TRY(run_hidden(m, rs, nullptr, -1, s));
   LayerArgs a = base_args(m, m->L, m->ws.act[m->L - 1], rs);

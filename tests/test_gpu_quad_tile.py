@@ -105,9 +105,9 @@ def test_real_states_equal_the_sequential_ones_bit_for_bit(D, hidden, N):
 
 
 @pytest.mark.parametrize("dtype,N", [("bf16", 5300), ("f32", 8300)])
-def test_sequential_modes_of_real_states_on_large_batches(dtype, N):
-    """Whole-layer and narrow launches of the sequential samplers sum in the same order also where whole layers take the
-    128 x 128 tiles: the same states to the last bit."""
+def test_real_states_of_large_batches_bit_for_bit(dtype, N):
+    """Whole-layer and narrow launches of the sequential samplers, and passes over any number of samples, sum in the same
+    order also where whole layers take the 128 x 128 tiles: the same states to the last bit."""
     D = 24
     w = S.Workload(f"seqreal{dtype}", D, 2, [1100, 1100], dtype, N, "random", "fan_in", S.SEED_BASE + 1450, gain=1.5, real=True)
     net = S.make_network(w, with_bias=True)
@@ -119,5 +119,11 @@ def test_sequential_modes_of_real_states_on_large_batches(dtype, N):
             B.sequential_sample_real(h, noise, N, mode, out[mode])
         torch.cuda.synchronize()
         assert torch.equal(*out), int((out[0] != out[1]).sum())
+        for chains in (1, 3):                # (the line is the call's, not a chain's or a pass's)
+            B.made_set_option(h, B.MADE_OPT_CHAINS, chains)
+            for _ in range(3):
+                B.jacobi_sample_real(h, noise, N, None, 0.0, 0, out[1])
+                torch.cuda.synchronize()
+                assert torch.equal(*out), (chains, int((out[0] != out[1]).sum()))
     finally:
         B.made_free(h)
