@@ -47,3 +47,34 @@ def test_fused_draw_of_any_class_count(C, D, N, dtype):
         assert (out["jacobi", 1][0][clear] == out["sequential", 1][0][clear]).all()
     finally:
         B.made_free(h)
+
+
+@pytest.mark.parametrize("C,D,N,dtype,onehot,hidden", [(2, 75, 65, "bf16", False, [200, 1000]), (5, 40, 1, "f32", True, [90, 333]),
+                                                       (64, 40, 100, "bf16", True, [700, 900]), (33, 19, 70, "bf16", False, [500]),
+                                                       (7, 100, 16, "f32", False, [150, 520]), (226, 7, 31, "bf16", False, [640]),
+                                                       (100, 9, 32, "f32", False, [300]), (128, 12, 64, "bf16", False, [1024])])
+def test_logits_have_the_same_bits_in_every_sampler(C, D, N, dtype, onehot, hidden):
+    """Noise that is exactly minus the logits of the all-zero state: every class then scores exactly 0 and class 0 is drawn
+    everywhere -- if and only if a sampler's logits have the bits of made_forward_logits, whatever run of positions and
+    batch a workgroup takes them for."""
+    w = S.Workload(f"bits{C}", D, C, hidden, dtype, N, "random", "fan_in", S.SEED_BASE + 950 + C, gain=2.0, onehot=onehot)
+    net = S.make_network(w, with_bias=True)
+    h = B.model_from_network(net)
+    try:
+        z = torch.empty((N, D, C), device="cuda")
+        B.made_forward_logits(h, torch.zeros((N, D), dtype=torch.uint8, device="cuda"), N, z)
+        noise = -z
+        x = torch.empty((N, D), dtype=torch.uint8, device="cuda")
+        it = torch.zeros((N,), dtype=torch.int32, device="cuda")
+        for what, call in (("jacobi", lambda: B.jacobi_sample(h, noise, N, None, 0, x, it)),
+                           ("gs 1", lambda: B.gs_jacobi_sample(h, noise, N, None, 1, x)),
+                           ("gs 3", lambda: B.gs_jacobi_sample(h, noise, N, None, 3, x)),
+                           ("seq 0", lambda: B.sequential_sample(h, noise, N, 0, x)), ("seq 1", lambda: B.sequential_sample(h, noise, N, 1, x))):
+            x.fill_(255)
+            call()
+            torch.cuda.synchronize()
+            assert (x == 0).all(), (what, int((x != 0).sum()))
+        B.jacobi_sample(h, noise, N, None, 0, x, it)
+        assert (it == 1).all()
+    finally:
+        B.made_free(h)
