@@ -664,8 +664,8 @@ static void plan_column(made_model* m) {
     m->col_lds_cnt[l] = off;
     off += ((D + 2) * (int)sizeof(int) + 15) & ~15;
   }
-  const int statics = 256;                               // the kernel's own small LDS arrays
-  if (off + statics > 160 * 1024) return;                // LDS of a gfx950 compute unit
+  const int limit = 160 * 1024 - 256;                    // LDS of a gfx950 compute unit, less the kernel's own small arrays
+  if (off > limit) return;
   std::vector<int> bounds(1, 0);
   for (int a = 0; a < D; a = bounds.back()) {
     int b = a + 1;
@@ -674,9 +674,10 @@ static void plan_column(made_model* m) {
     bounds.push_back(b);
   }
   hipError_t e = hipSuccess;
+  // (the attribute is the kernel's, not this model's: the same for every model, or a smaller one would take it from a larger)
   for (int seq = 0; seq < 2; ++seq)
     column_kernel(m, seq != 0, [&](auto* kernel) {
-      if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, off);
+      if (e == hipSuccess) e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, limit);
     });
   if (e == hipSuccess) e = hipMalloc((void**)&m->col_ctr, 4 * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMemset(m->col_ctr, 0, 4 * sizeof(unsigned long long));

@@ -86,3 +86,25 @@ def test_too_many_units_of_one_degree_take_the_other_paths():
         assert (x.cpu().numpy()[clear] == xs[clear]).all()
     finally:
         B.made_free(h)
+
+
+def test_a_smaller_model_made_later_leaves_the_larger_one_its_lds():
+    """Two models of one depth and type alive, the larger (about 130 KB of LDS) called after the smaller was made."""
+    models = []
+    try:
+        for D, H in ((784, 2000), (20, 30)):
+            w = S.Workload(f"lds{D}", D, 1, [H, H], "bf16", 6, "random", "fan_in", S.SEED_BASE + 780 + D, gain=2.5)
+            net = S.make_network(w, with_bias=True)
+            models.append((w, S.make_noise(w), O.build_model(net.D, net.C, net.degrees, net.W, net.b, "bf16"), B.model_from_network(net)))
+        for w, noise, ref, h in models:
+            x = torch.empty((w.N, w.D), dtype=torch.uint8, device="cuda")
+            for call in (lambda: B.gs_jacobi_sample(h, torch.from_numpy(noise).cuda(), w.N, None, 8, x),
+                         lambda: B.sequential_sample(h, torch.from_numpy(noise).cuda(), w.N, 1, x)):
+                call()
+                torch.cuda.synchronize()
+                assert B.made_last_stats(h)["kernels"] == 1
+                ok, margin = O.fixed_point_check(ref, x.cpu().numpy(), noise)
+                assert (ok | (margin < 1e-3)).all()
+    finally:
+        for m in models:
+            B.made_free(m[-1])
