@@ -238,7 +238,9 @@ int gs_jacobi_sample_real(made_model* m, const float* noise, int32_t N, const fl
 
 /*
  * made_last_stats -- counters of the most recent *_sample call on this model (host side):
- *   out[0] passes launched (network passes over the still-active part of the batch)
+ *   out[0] passes launched (network passes over the still-active part of the batch; where parts of the batch iterate
+ *          on their own -- MADE_OPT_CHAINS, MADE_OPT_XCD_RESIDENT, MADE_OPT_RESIDENT -- those of the part with the most;
+ *          the block-wise kernel, whose samples do, counts for every block those of the slowest sample)
  *   out[1] sum over passes of active samples (sample-passes; the unit of algorithmic work)
  *   out[2] kernels launched
  *   out[3] host waits on the device

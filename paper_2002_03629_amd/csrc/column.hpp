@@ -36,6 +36,7 @@ struct ColumnArgs {
   int lds_w[COL_MAX_L + 1];         // staged weights of layer l (float), input-major
   int lds_cnt[COL_MAX_L];
   int lds_red, lds_clear;           // partial sums of phase 1; bytes to clear at the start (inputs and staged weights)
+  int lds_passes;                   // GS-Jacobi: [n_blocks] bytes, most passes of one of this workgroup's samples
   const int* bounds;                // sequential: block boundaries [n_blocks + 1]; NULL: blocks of `block` positions
   int n_blocks, block;
   int D, N;
@@ -43,8 +44,11 @@ struct ColumnArgs {
   const uint8_t* x_init;            // GS-Jacobi: [N, D] or NULL
   uint8_t* x;                       // [N, D]
   int* iters;                       // GS-Jacobi: [N] passes
-  unsigned long long* ctr;          // GS-Jacobi: device, zero between calls: [0] finished workgroups, [1] most passes of
-  unsigned long long* host;         // a workgroup, [2] sample-passes; pinned host memory: [0] passes, [1] sample-passes
+  // GS-Jacobi, device, zero between calls: finished workgroups and sample-passes; [n_blocks] most passes of a sample
+  unsigned long long* ctr;
+  int* block_passes;
+  unsigned long long* host;         // pinned host memory: [0] passes, [1] sample-passes, [2] call_id when both are there
+  unsigned long long call_id;
 };
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -168,7 +172,7 @@ template <typename T, int L, bool SEQ>
 __global__ __launch_bounds__(COL_WAVES * 64) void column_sampler_kernel(ColumnArgs p) {
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ unsigned long long passes_s[COL_S];
-  __shared__ int block_passes_s[COL_S];
+  __shared__ int block_passes_s[COL_S], all_passes_s, last_s;
   constexpr int NT_ = COL_WAVES * 64;
   constexpr int EPL = Elem<T>::EPL, KC = 2 * EPL, P = 16 / (int)sizeof(T);
   constexpr int RED = COL_UNITS * L + COL_POS;     // rows of a block over all layers
@@ -183,7 +187,6 @@ __global__ __launch_bounds__(COL_WAVES * 64) void column_sampler_kernel(ColumnAr
   float* red = (float*)(lds + p.lds_red);
   const int n = blockIdx.x * COL_S + wave;         // phase 2: this wave's sample
   const bool solver = wave < COL_S && n < p.N;
-  unsigned long long wg_passes = 0;
   int my_passes = 0;
   // element (sample, k) of a layer's input in LDS (see col_product)
   auto put = [&](int l, int k, float v) {
@@ -328,7 +331,7 @@ __global__ __launch_bounds__(COL_WAVES * 64) void column_sampler_kernel(ColumnAr
     if (!SEQ && threadIdx.x == 0) {
       int most = 0;
       for (int i = 0; i < COL_S; ++i) most = max(most, block_passes_s[i]);
-      wg_passes += (unsigned long long)most;
+      lds[p.lds_passes + blk] = (unsigned char)most;     // (<= COL_POS)
     }
   }
 
@@ -338,21 +341,34 @@ __global__ __launch_bounds__(COL_WAVES * 64) void column_sampler_kernel(ColumnAr
       if (solver) p.iters[n] = my_passes;
     }
     __syncthreads();
+    // A block takes as many passes as its slowest sample of the whole batch.  (Returning atomics, each performed before the
+    // barrier: the workgroup that sees the full count sees every contribution.)
+    for (int b = threadIdx.x; b < p.n_blocks; b += NT_) {
+      const int o = __hip_atomic_fetch_max(&p.block_passes[b], (int)lds[p.lds_passes + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("" ::"v"(o));
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
       unsigned long long sum = 0;
       for (int i = 0; i < COL_S; ++i) sum += passes_s[i];
-      // (returning atomics, each performed before the next is issued: the workgroup that sees the full count sees
-      // every contribution)
-      unsigned long long o = __hip_atomic_fetch_add(&p.ctr[2], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("" ::"v"(o));
-      o = __hip_atomic_fetch_max(&p.ctr[1], wg_passes, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned long long o = __hip_atomic_fetch_add(&p.ctr[1], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("" ::"v"(o));
       o = __hip_atomic_fetch_add(&p.ctr[0], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (o == (unsigned long long)gridDim.x - 1) {
-        for (int i = 0; i < 2; ++i)
-          __hip_atomic_store(&p.host[i], __hip_atomic_load(&p.ctr[1 + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        for (int i = 0; i < 3; ++i) __hip_atomic_store(&p.ctr[i], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last_s = o == (unsigned long long)gridDim.x - 1;
+      all_passes_s = 0;
+    }
+    __syncthreads();
+    if (last_s) {                                    // (uniform) report, and leave the counters at zero
+      int mine = 0;
+      for (int b = threadIdx.x; b < p.n_blocks; b += NT_) mine += __hip_atomic_exchange(&p.block_passes[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (mine) atomicAdd(&all_passes_s, mine);
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const unsigned long long sum = __hip_atomic_exchange(&p.ctr[1], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&p.ctr[0], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&p.host[0], (unsigned long long)all_passes_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&p.host[1], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&p.host[2], p.call_id, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
   }

@@ -275,12 +275,14 @@ struct made_model {
   int use_xcd = 1;                            // made_set_option(MADE_OPT_XCD_RESIDENT): 0 never, 1 where it pays, 2 whenever possible
   int xcd_grid = 0;                           // workgroups of xcd_sampler_kernel (0 = not usable on this device / model)
   // block-wise forward substitution (column_sampler_kernel): LDS layout, 0 bytes = this model does not fit
-  int col_lds_bytes = 0, col_lds_clear = 0, col_lds_red = 0;
+  int col_lds_bytes = 0, col_lds_clear = 0, col_lds_red = 0, col_lds_passes = 0;
   int col_lds_act[COL_MAX_L + 1] = {}, col_lds_w[COL_MAX_L + 1] = {}, col_lds_cnt[COL_MAX_L] = {};
   int* col_bounds = nullptr;                  // device: block boundaries of sequential sampling
   int col_blocks = 0;
   unsigned long long* col_ctr = nullptr;
+  int* col_block_passes = nullptr;
   volatile unsigned long long* col_host = nullptr;
+  unsigned long long col_calls = 0;
   // sample-resident kernel (resident_sampler_kernel): LDS layout, 0 bytes = this model does not fit
   int use_resident = 2;                       // made_set_option(MADE_OPT_RESIDENT): 0 never, 1 whenever it fits, 2 where it pays
   int res_lds_bytes = 0, res_lds_enc = 0, res_lds_clear = 0;
@@ -481,6 +483,7 @@ extern "C" int made_free(made_model* m) {
   }
   if (m->col_bounds) (void)hipFree(m->col_bounds);
   if (m->col_ctr) (void)hipFree(m->col_ctr);
+  if (m->col_block_passes) (void)hipFree(m->col_block_passes);
   if (m->col_host) (void)hipHostFree((void*)m->col_host);
   if (m->res_ctr) (void)hipFree(m->res_ctr);
   if (m->res_host) (void)hipHostFree((void*)m->res_host);
@@ -664,6 +667,8 @@ static void plan_column(made_model* m) {
     m->col_lds_cnt[l] = off;
     off += ((D + 2) * (int)sizeof(int) + 15) & ~15;
   }
+  m->col_lds_passes = off;
+  off += (D + 15) & ~15;                                 // (at most D blocks)
   const int limit = 160 * 1024 - 256;                    // LDS of a gfx950 compute unit, less the kernel's own small arrays
   if (off > limit) return;
   std::vector<int> bounds(1, 0);
@@ -681,7 +686,10 @@ static void plan_column(made_model* m) {
     });
   if (e == hipSuccess) e = hipMalloc((void**)&m->col_ctr, 4 * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMemset(m->col_ctr, 0, 4 * sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMalloc((void**)&m->col_block_passes, D * sizeof(int));
+  if (e == hipSuccess) e = hipMemset(m->col_block_passes, 0, D * sizeof(int));
   if (e == hipSuccess) e = hipHostMalloc((void**)&m->col_host, 4 * sizeof(unsigned long long), hipHostMallocDefault);
+  if (e == hipSuccess) memset((void*)m->col_host, 0, 4 * sizeof(unsigned long long));
   if (e == hipSuccess && bounds.back() == D) {
     e = hipMalloc((void**)&m->col_bounds, bounds.size() * sizeof(int));
     if (e == hipSuccess) e = hipMemcpy(m->col_bounds, bounds.data(), bounds.size() * sizeof(int), hipMemcpyHostToDevice);
@@ -2418,8 +2426,11 @@ static int run_column(made_model* m, const float* noise, int N, const uint8_t* x
   p.x_init = x_init;
   p.x = x;
   p.iters = iters_out ? iters_out : m->ws.iters;
+  p.lds_passes = m->col_lds_passes;
   p.ctr = m->col_ctr;
+  p.block_passes = m->col_block_passes;
   p.host = (unsigned long long*)m->col_host;
+  p.call_id = ++m->col_calls;
   prof_mark(m, m->L + 1, false, s);
   column_kernel(m, seq, [&](auto* kernel) {
     hipLaunchKernelGGL(kernel, dim3((N + COL_S - 1) / COL_S), dim3(COL_WAVES * 64), (size_t)m->col_lds_bytes, s, p);
@@ -2431,9 +2442,17 @@ static int run_column(made_model* m, const float* noise, int N, const uint8_t* x
   m->ws.pending_stream = s;
   *done = true;
   if (seq && !m->profiling) return MADE_OK;      // (nothing to report: the caller's stream orders the result)
-  HIP_TRY(hipStreamSynchronize(s));
-  m->ws.pending = false;
-  m->stats[3] = 1;
+  // GS-Jacobi reports into pinned memory once the last workgroup is done
+  const auto t0 = std::chrono::steady_clock::now();
+  for (uint64_t polls = 1; !seq && m->col_host[2] != p.call_id; ++polls)
+    if ((polls & 0xfff) == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > 30.0)
+      return give_up_waiting(m, s);
+  std::atomic_thread_fence(std::memory_order_acquire);
+  if (m->profiling) {
+    HIP_TRY(hipStreamSynchronize(s));
+    m->ws.pending = false;
+    m->stats[3] = 1;
+  }
   prof_collect(m);
   if (!seq) {
     m->stats[0] = (int64_t)m->col_host[0];
