@@ -2391,15 +2391,27 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
 
 // GS-Jacobi (block > 0) or lean sequential sampling (block = 0) in one launch of column_sampler_kernel.  Sets *done when
 // the call was served this way.  GS-Jacobi blocks have to fit the kernel's lanes: at most COL_POS positions, at most
-// COL_UNITS units of a layer.  Measured (784 positions, 2 x 2000 units, bf16, us per call): blocks of 16, batch 128:
-// 446 against 1209 in xcd_sampler_kernel; batch 1 / 1024 / 8192: 449 / 449 / 3418 against 1154 / 2224 / 7496 in that
-// kernel or per-layer launches; sequential, batch 128 / 8192: 577 / 4582 against 10166 / 42015 in per-layer launches.
+// COL_UNITS units of a layer.
+// Where it pays, measured in us a call: a compute unit holds one workgroup, so 1024 samples go at a time and the time grows with
+// every 1024 (2 x 2000 units, 784 positions, bf16, blocks of 16, batch 1024 / 2048 / 8192 / 32768: 448 / 874 / 3431 / 13654).
+//   GS-Jacobi: up to 1024 samples always (1024 samples, blocks of 4 / 16: 784 / 2 x 2000 1171 / 448 against 8437 / 2176 in
+//     xcd_sampler_kernel; 196 / 2 x 500 257 / 119 against 819 / 277 in resident_sampler_kernel; 64 / 256, blocks of 4 / 8: 82 / 61
+//     against 227 / 156; a single sample, blocks of 1 / 16: 196 / 2 x 500 720 / 107 against 1560 / 239).  resident_sampler_kernel,
+//     where the model fits it, takes 8192 at a time: batch 2048 / 3072 / 8192, blocks of 4: 64 / 256 137 / 191 / 457 against 228 /
+//     227 / 240, 196 / 2 x 500 486 / 716 / 1871 against 819 / 816 / 821, 300 / 3 x 200 858 / 1273 / 3348 against 1375 / 1372 /
+//     1387: the line is at 2048.  Against per-layer launches, batch 8192 / 32768, blocks of 4 / 16: 784 / 2 x 2000 9226 / 3431 and
+//     36819 / 13654 against 30093 / 8224 and 40484 / 11861 (bf16: up to 24576), 784 / 1000 fp32 5841 / 1961 and 23311 / 7773
+//     against 37535 / 10084 and 65020 / 17013 (always).
+//   Sequential: 784 / 2 x 2000, batch 128 / 8192 / 32768: 577 / 4601 / 18355 against 10166 / 50813 / 100327; 64 / 256, 1024 / 32768:
+//     51 / 1088 against 604 / 1113, so networks of at most 256 units stop there.
 static int run_column(made_model* m, const float* noise, int N, const uint8_t* x_init, uint8_t* x, int block,
                       int32_t* iters_out, hipStream_t s, bool* done) {
   *done = false;
   if (m->arch != 0 || m->use_resident != 2 || m->col_lds_bytes <= 0) return MADE_OK;
   const bool seq = block == 0;
   if (seq ? m->col_blocks == 0 : block > COL_POS) return MADE_OK;
+  const bool narrow = m->widest_tiles <= 8;
+  if (seq ? narrow && N > 32768 : N > (m->res_lds_bytes > 0 ? 2048 : m->dtype == MADE_BF16 ? 24576 : 1 << 30)) return MADE_OK;
   for (int a = 0; !seq && a < m->D; a += block)
     if (column_units(m, a, std::min(a + block, m->D)) > COL_UNITS) return MADE_OK;
   ColumnArgs p;

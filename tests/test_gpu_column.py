@@ -120,3 +120,26 @@ def test_a_smaller_model_made_later_leaves_the_larger_one_its_lds():
     finally:
         for m in models:
             B.made_free(m[-1])
+
+
+@pytest.mark.parametrize("D,hidden,N,dtype", [(64, [100], 2048, "bf16"), (64, [100], 2049, "bf16"), (16, [40], 32768, "f32"), (16, [40], 32769, "f32")])
+def test_batches_around_the_lines_to_the_other_paths(D, hidden, N, dtype):
+    """GS-Jacobi up to and beyond 2048 samples on a model the sample-resident kernel holds, the sequential sampler of a narrow
+    network up to and beyond 32768."""
+    w = S.Workload(f"line{D}", D, 1, hidden, dtype, N, "random", "fan_in", S.SEED_BASE + 790 + D, gain=2.5)
+    net = S.make_network(w, with_bias=True)
+    noise = S.make_noise(w)
+    ref = O.build_model(net.D, net.C, net.degrees, net.W, net.b, "bf16" if dtype == "bf16" else None)
+    h = B.model_from_network(net)
+    try:
+        u = torch.from_numpy(noise).cuda()
+        x = torch.empty((N, D), dtype=torch.uint8, device="cuda")
+        for call in (lambda: B.gs_jacobi_sample(h, u, N, None, 4, x), lambda: B.sequential_sample(h, u, N, 1, x)):
+            x.fill_(9)
+            call()
+            torch.cuda.synchronize()
+            ok, margin = O.fixed_point_check(ref, x.cpu().numpy(), noise)
+            assert (ok | (margin < 1e-3)).all()
+        assert (B.made_last_stats(h)["kernels"] == 1) == (N <= 32768)
+    finally:
+        B.made_free(h)
