@@ -1197,10 +1197,12 @@ static void launch_quad_t(LayerArgs a, int n_tiles, hipStream_t s) {
 //     117 / 151 against 99 / 100 / 101 / 103; 200 / 2 x 1100 (real states), batch 2048 (80) / 3000 (120) / 4096: J 519 / 638 / 774
 //     against 584 / 645 / 686.  fp32 (32 against 128), from 224 on: 784 / 2 x 2000, batch 3000 (192) / 3500 / 4096: F 376 / 436 /
 //     498 against 414 / 416 / 418; 200 / 2 x 1100, batch 4096 (160) / 6000: J 2677 / 3696 against 3021 / 3398.
-//     A sampling layer of such rows waits until 320: 300 / 500, batch 4000 / 8000 / 16384 (256) / 32768 (512): J 217 / 298 / 470 / 791 against 419 / 495 / 507 / 630.
-//     Networks no wider than one 128-unit column are bound by the samples' own traffic and take the wide tile
-//     from a batch on: 64 / 120, batch 4500 / 8000 / 16000: 126 / 156 / 220 against 124 / 145 / 158; fp32 8000 / 16000:
-//     192 / 278 against 212 / 227.
+//     A sampling layer of such rows waits until 256: 300 / 500, batch 4000 / 8000 / 16384 (256) / 32768 (512): J 217 / 298 /
+//     470 / 791 against 419 / 495 / 507 / 630.
+//     Launches no wider than one 128-unit column are bound by the samples' own traffic and take the wide tile (rows of the
+//     other kind again excepted, unless the whole network is that narrow) from a batch on: 64 / 120, batch 4500 / 8000 /
+//     16000: J 126 / 156 / 220 against 124 / 145 / 158; fp32 8000 / 16000: 192 / 278 against 212 / 227; GS-Jacobi on 784 / 2 x
+//     2000, blocks of 30, batch 4096 / 8192 / 16384: 3380 / 4906 / 8936 against 3840 / 4200 / 5059.
 //   128 against 256, where the paired workgroups of 256 x 256 fill nine tenths of their last round over the compute units:
 //     784 / 2 x 2000, batch 16384 (256 workgroups) / 24000 (376) / 32768 (512): J 948 / 1437 / 1865 against 934 / 1556 / 1818;
 //     1000 / 2 x 1200, 16384 (192) / 32768 (384): J 935 / 1689 against 1032 / 1860.
@@ -1219,9 +1221,10 @@ static int tile_edge(const made_model* m, int epi, int layer, int n_tiles, int n
   };
   const long long p8 = paired(8), rounds = (p8 + 255) / 256;
   if (line_rows >= m->big_batch && (m->big_output || (epi == EPI_RELU && 10 * p8 >= 9 * 256 * rounds))) return 256;
-  const int line = epi == EPI_BERNOULLI && m->D % 16 != 0 ? 320 : bf16 ? 144 : 224;
+  const int line = epi == EPI_BERNOULLI && m->D % 16 != 0 ? 256 : bf16 ? 144 : 224;
   if (line_rows >= m->mid_batch &&
-      (m->mid_set || paired(4) >= line || (m->widest_tiles <= 4 && line_rows >= (bf16 ? 6144 : 12288))))
+      (m->mid_set || paired(4) >= line ||
+       ((m->widest_tiles <= 4 || (line_tiles <= 4 && line < 256)) && line_rows >= (bf16 ? 6144 : 12288))))
     return 128;
   if ((epi == EPI_RELU || epi == EPI_BERNOULLI) && bf16 && !m->mid_set && n_rows > DERIVE_MAX_ROWS &&
       (epi == EPI_RELU || m->D % 16 == 0 || m->layers[layer].k_chunks > NW / 2) && (long long)((n_tiles + 1) / 2) * ((n_rows + QUAD - 1) / QUAD) >= 176)
