@@ -37,14 +37,16 @@ def test_fused_draw_of_any_class_count(C, D, N, dtype):
                 else:
                     B.sequential_sample(h, u, N, 1, x)
                 torch.cuda.synchronize()
-                out[call, fused] = (x.cpu().numpy(), it.cpu().numpy())
+                out[call, fused] = (x.cpu().numpy(), it.cpu().numpy(), B.made_last_stats(h)["kernels"])
         for call in ("jacobi", "gs", "sequential"):
-            x, it = out[call, 1]
+            x = out[call, 1][0]
             ok, margin = O.fixed_point_check(ref, x, noise)
             assert (ok | (margin < 1e-3)).all(), call
             clear = margin.min(axis=1) >= 1e-3       # (at a fixed point both forms reached: the same one)
             assert (x[clear] == out[call, 0][0][clear]).all(), call
         assert (out["jacobi", 1][0][clear] == out["sequential", 1][0][clear]).all()
+        # (a launch less per position where the draw is fused)
+        assert out["sequential", 1][2] == out["sequential", 0][2] - D
     finally:
         B.made_free(h)
 

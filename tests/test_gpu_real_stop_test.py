@@ -37,6 +37,8 @@ def test_with_and_without_tail(D, hidden, dtype, N):
             (xa, ia, sa, ta), (xb, ib, sb, tb) = out
             assert (xa == xb).all() and (ia == ib).all() and sa == sb, (N, eps, cap)
             assert ta["sample_passes"] == tb["sample_passes"] == ia.sum()
+            # (every pass but the last allowed one goes without a tail, on up to 256 samples)
+            assert (ta["tail_less_passes"] > 0) == (N <= 256 and cap != 1) and tb["tail_less_passes"] == 0
             assert ia.min() >= 1 and (not cap or ia.max() <= cap)
     finally:
         B.made_free(h)
