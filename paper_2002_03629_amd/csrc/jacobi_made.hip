@@ -264,7 +264,7 @@ struct made_model {
   int fused_categorical = 1;                  // made_set_option(MADE_OPT_FUSED_CATEGORICAL)
   int use_persistent = 0;                     // made_set_option(MADE_OPT_PERSISTENT): 1 = the device-wide cooperative kernel
                                               // (measured slower, see header)
-  int frozen_positions = 1;                   // made_set_option(MADE_OPT_FROZEN_POSITIONS): 256-class output kernel skips the
+  int frozen_positions = 1;                   // made_set_option(MADE_OPT_FROZEN_POSITIONS): a fused categorical draw skips the
                                               // positions below the first one that changed in the pass before
   int zero_start_fill = 1;                    // made_set_option(MADE_OPT_ZERO_START): 1 = the set-up kernel writes the first hidden layer of a call started from zeros
   int call_graph = 0;                         // made_set_option(MADE_OPT_CALL_GRAPH): replay a call's launches as one HIP graph

@@ -219,8 +219,8 @@ struct LayerArgs {
   int tile_begin;        // first unit tile this launch covers
   int n_launch_tiles;    // unit tiles this launch covers
   int row_tiles;         // sample tiles this launch covers (upper bound; tiles beyond n_rows idle)
-  int big_by_rows;       // 256 x 256 kernel only: XCDs own sample tiles (1) or unit tiles (0)
-  int io_aligned;        // 256 x 256 kernel only: D % 16 == 0 and noise / x are 16-byte aligned
+  int big_by_rows;       // 128 x 128 and 256 x 256 tiles: XCDs own sample tiles (1) or unit tiles (0)
+  int io_aligned;        // 64 x 64 and larger tiles: D % 16 == 0 and noise / x are 16-byte aligned
   // active samples: rows[0 .. *n_rows_ptr) are sample ids (NULL = identity, n_rows fixed)
   const int* rows;
   const int* n_rows_ptr;

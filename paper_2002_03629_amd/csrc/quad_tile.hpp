@@ -63,13 +63,12 @@ __global__ __launch_bounds__(NW * 64) void masked_layer_quad_kernel(LayerArgs a)
     const int p_lo = a.t_lo, p_hi = min(a.t_hi, a.D);
     if constexpr (EPI == EPI_BERNOULLI) {
       const size_t x_row = (size_t)e_sample * a.D;
-      const size_t n_row = (size_t)(a.noise_mod > 0 ? min(e_sample % a.noise_mod, a.noise_n - 1) : e_sample) * a.D;
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
         const int col = col0 + 8 * g;
         if (a.io_aligned) {      // (D is a multiple of 16: a run lies wholly inside the row or behind its end)
           const int c = col < a.D ? col : 0;
-          const float4 v = *(const float4*)(a.noise + n_row + c);
+          const float4 v = *(const float4*)(a.noise + x_row + c);
           u[g][0] = v.x; u[g][1] = v.y; u[g][2] = v.z; u[g][3] = v.w;
           xo[g] = *(const uint32_t*)(a.x + x_row + c);
         } else {
@@ -77,7 +76,7 @@ __global__ __launch_bounds__(NW * 64) void masked_layer_quad_kernel(LayerArgs a)
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             const int at = min(col + c, a.D - 1);
-            u[g][c] = a.noise[n_row + at];
+            u[g][c] = a.noise[x_row + at];
             xo[g] |= (uint32_t)a.x[x_row + at] << (8 * c);
           }
         }
