@@ -26,6 +26,7 @@
 namespace jm {
 
 constexpr int CAT_ANY_WAVES = 8;
+static_assert(NW == 8, "the parts of a sum are dealt to eight waves by tile count");
 constexpr int CAT_ANY_ROWS = 64;                       // samples per workgroup
 constexpr int CAT_ANY_TILES = 9;                       // C = 226..255 not a multiple of 32: one position touches nine tiles
 constexpr int CAT_ANY_FULL = 256;                      // output rows of a workgroup's positions, at most

@@ -127,3 +127,19 @@ def test_real_states_of_large_batches_bit_for_bit(dtype, N):
                 assert torch.equal(*out), (chains, int((out[0] != out[1]).sum()))
     finally:
         B.made_free(h)
+
+
+@pytest.mark.parametrize("D,hidden,dtype,sizes", [(160, [700], "bf16", (960, 961, 6016, 6017)), (160, [700], "f32", (9472, 9473)),
+                                                  (64, [120], "bf16", (6143, 6144)), (64, [120], "f32", (12287, 12288)),
+                                                  (40, [2000], "bf16", (16383, 16384))])
+def test_batches_around_the_lines_between_the_tiles(D, hidden, dtype, sizes):
+    """The last batch on one tile and the first on the next: 32 and 64 (176 workgroups), 64 and 128 (144 paired ones, fp32
+    224), networks of one column (6144 rows, fp32 12288), 128 and 256 (256 paired ones at 16384)."""
+    for N in sizes:
+        w = S.Workload(f"line{D}", D, 1, hidden, dtype, N, "random", "fan_in", S.SEED_BASE + 1600 + D, gain=2.5)
+        net = S.make_network(w, with_bias=True)
+        ref, noise = oracle_models(net)[1], S.make_noise(w)
+        with GpuModel(net) as g:
+            B.made_set_option(g.h, B.MADE_OPT_CHAINS, 1)
+            certify(ref, g.jacobi(noise)[0], noise, (D, dtype, N))
+            certify(ref, g.gs_jacobi(noise, 30)[0], noise, (D, dtype, N, "gs"))
