@@ -275,8 +275,10 @@ struct made_model {
   int use_xcd = 1;                            // made_set_option(MADE_OPT_XCD_RESIDENT): 0 never, 1 where it pays, 2 whenever possible
   int xcd_grid = 0;                           // workgroups of xcd_sampler_kernel (0 = not usable on this device / model)
   // block-wise forward substitution (column_sampler_kernel): LDS layout, 0 bytes = this model does not fit
-  int col_lds_bytes = 0, col_lds_clear = 0, col_lds_red = 0, col_lds_passes = 0;
-  int col_lds_act[COL_MAX_L + 1] = {}, col_lds_w[COL_MAX_L + 1] = {}, col_lds_cnt[COL_MAX_L] = {};
+  struct ColumnLds {                     // [0] GS-Jacobi, [1] sequential; bytes = 0: the model does not fit
+    int bytes = 0, w_bytes = 0, clear = 0, red = 0, passes = 0;
+    int act[COL_MAX_L + 1] = {}, w[COL_MAX_L + 1] = {}, cnt[COL_MAX_L] = {};
+  } col_lds[2];
   int* col_bounds = nullptr;                  // device: block boundaries of sequential sampling
   int col_blocks = 0;
   unsigned long long* col_ctr = nullptr;
@@ -651,30 +653,46 @@ static void plan_column(made_model* m) {
   const int L = m->L, D = m->D;
   if (m->C != 1 || m->real || L > COL_MAX_L) return;
   const int es = (int)elem_size(m);
-  int off = 0;
-  for (int l = 0; l <= L; ++l) {
-    m->col_lds_act[l] = off;
-    off += m->layers[l].in_pad * COL_S * es;
-  }
-  for (int l = 0; l <= L; ++l) {
-    m->col_lds_w[l] = off;
-    off += (l == 0 ? COL_POS * COL_UNITS : l < L ? COL_UNITS * COL_UNITS : COL_UNITS * COL_POS) * (int)sizeof(float);
-  }
-  m->col_lds_clear = off;
-  m->col_lds_red = off;
-  off += COL_WAVES * COL_S * (COL_UNITS * L + COL_POS) * (int)sizeof(float);
-  for (int l = 0; l < L; ++l) {
-    m->col_lds_cnt[l] = off;
-    off += ((D + 2) * (int)sizeof(int) + 15) & ~15;
-  }
-  m->col_lds_passes = off;
-  off += (D + 15) & ~15;                                 // (at most D blocks)
   const int limit = 160 * 1024 - 256;                    // LDS of a gfx950 compute unit, less the kernel's own small arrays
-  if (off > limit) return;
+  for (int seq = 0; seq < 2; ++seq) {
+    made_model::ColumnLds& c = m->col_lds[seq];
+    int off = 0;
+    for (int l = 0; l <= L; ++l) {
+      c.act[l] = off;
+      off += m->layers[l].in_pad * COL_S * es;
+    }
+    for (int l = 0; l <= L; ++l) {
+      const int inputs = l == 0 ? COL_POS : COL_UNITS, pitch = l < L ? COL_UNITS : COL_POS;
+      c.w[l] = off;
+      off += seq ? ColStage<float, true>::bytes(inputs, pitch) : es == 2 ? ColStage<bf16_t, false>::bytes(inputs, pitch)
+                                                                         : ColStage<float, false>::bytes(inputs, pitch);
+    }
+    // a second buffer of staged weights, so that a block's are written while the block before is solved; a model that
+    // leaves no room for it has them written between two blocks
+    const int staged = off - c.w[0];
+    int rest = COL_PRODUCERS * COL_S * (COL_UNITS * L + COL_POS) * (int)sizeof(float) + ((D + 15) & ~15) +
+               L * (((D + 2) * (int)sizeof(int) + 15) & ~15);
+    if (off + staged + rest <= limit) {
+      c.w_bytes = staged;
+      off += staged;
+    }
+    if (off + rest > limit) continue;
+    c.clear = off;
+    c.red = off;
+    off += COL_PRODUCERS * COL_S * (COL_UNITS * L + COL_POS) * (int)sizeof(float);
+    for (int l = 0; l < L; ++l) {
+      c.cnt[l] = off;
+      off += ((D + 2) * (int)sizeof(int) + 15) & ~15;
+    }
+    c.passes = off;
+    off += (D + 15) & ~15;                               // (at most D blocks)
+    c.bytes = off;
+  }
+  if (!m->col_lds[0].bytes && !m->col_lds[1].bytes) return;
   std::vector<int> bounds(1, 0);
   for (int a = 0; a < D; a = bounds.back()) {
     int b = a + 1;
-    while (b < D && b - a < COL_POS && column_units(m, a, b + 1) <= COL_UNITS) ++b;
+    while (b < D && b - a < COL_POS && column_units(m, a, b + 1) <= COL_SEQ_UNITS) ++b;
     if (column_units(m, a, b) > COL_UNITS) break;        // (more units of one degree than a wave has lanes)
     bounds.push_back(b);
   }
@@ -695,7 +713,7 @@ static void plan_column(made_model* m) {
     if (e == hipSuccess) e = hipMemcpy(m->col_bounds, bounds.data(), bounds.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess) m->col_blocks = (int)bounds.size() - 1;
   }
-  if (e == hipSuccess) m->col_lds_bytes = off;
+  if (e != hipSuccess) m->col_lds[0].bytes = m->col_lds[1].bytes = 0;
   (void)hipGetLastError();
 }
 
@@ -2396,25 +2414,25 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
 // the call was served this way.  GS-Jacobi blocks have to fit the kernel's lanes: at most COL_POS positions, at most
 // COL_UNITS units of a layer.
 // Where it pays, measured in us a call: a compute unit holds one workgroup, so 1024 samples go at a time and the time grows with
-// every 1024 (2 x 2000 units, 784 positions, bf16, blocks of 16, batch 1024 / 2048 / 8192 / 32768: 448 / 874 / 3431 / 13654).
-//   GS-Jacobi: up to 1024 samples always (1024 samples, blocks of 4 / 16: 784 / 2 x 2000 1171 / 448 against 8437 / 2176 in
-//     xcd_sampler_kernel; 196 / 2 x 500 257 / 119 against 819 / 277 in resident_sampler_kernel; 64 / 256, blocks of 4 / 8: 82 / 61
-//     against 227 / 156; a single sample, blocks of 1 / 16: 196 / 2 x 500 720 / 107 against 1560 / 239).  resident_sampler_kernel,
-//     where the model fits it, takes 8192 at a time: batch 2048 / 3072 / 8192, blocks of 4: 64 / 256 137 / 191 / 457 against 228 /
-//     227 / 240, 196 / 2 x 500 486 / 716 / 1871 against 819 / 816 / 821, 300 / 3 x 200 858 / 1273 / 3348 against 1375 / 1372 /
-//     1387: the line is at 2048.  Against per-layer launches, batch 8192 / 32768, blocks of 4 / 16: 784 / 2 x 2000 9226 / 3431 and
-//     36819 / 13654 against 30093 / 8224 and 40484 / 11861 (bf16: up to 24576), 784 / 1000 fp32 5841 / 1961 and 23311 / 7773
-//     against 37535 / 10084 and 65020 / 17013 (always).
-//   Sequential: 784 / 2 x 2000, batch 128 / 8192 / 32768: 577 / 4601 / 18355 against 10166 / 50813 / 100327; 64 / 256, 1024 / 32768:
-//     51 / 1088 against 604 / 1113, so networks of at most 256 units stop there.
+// every 1024 (2 x 2000 units, 784 positions, bf16, blocks of 16, batch 1024 / 2048 / 8192 / 32768: 297 / 560 / 2148 / 8492).
+//   GS-Jacobi: against the per-layer launches always (784 / 2 x 2000 bf16, blocks of 4 / 16, batch 1024 / 8192 / 32768: 926 / 297,
+//     7222 / 2148 and 28819 / 8492 against 12724 / 3535, 24296 / 8012 and 43336 / 12566; 784 / 1000 fp32 at 32768: 24147 / 7025
+//     against 66387 / 17686).  resident_sampler_kernel, where the model fits it, takes 8192 at a time: batch 2048 / 3072 / 4096,
+//     blocks of 4: 64 / 256 fp32 130 / 182 / 231 against 311 / 309 / 307, 196 / 2 x 500 429 / 628 / 826 against 830 / 830 / 829, 300 /
+//     3 x 200 769 / 1138 / 1508 against 1405 / 1401 / 1400; blocks of 16, the latter two: 147 / 206 / 263 against 282 / 293 / 301 and
+//     235 / 333 / 430 against 402 / 404 / 398: the line is at 3072.  Blocks of one position, 2048 / 3072: 405 / 593 against 501 / 500,
+//     1587 / 2363 against 1637 / 1629: at 2048 for blocks below 4.
+//   Sequential: 784 / 2 x 2000, batch 128 / 8192 / 32768: 273 / 2139 / 8501 against 10166 / 45709 / 107614; 64 / 256 bf16, 1024 / 32768:
+//     37 / 646 against 671 / 1177, and at that rate even at 65536 to 131072: networks of at most 256 units stop at 32768.
 static int run_column(made_model* m, const float* noise, int N, const uint8_t* x_init, uint8_t* x, int block,
                       int32_t* iters_out, hipStream_t s, bool* done) {
   *done = false;
-  if (m->arch != 0 || m->use_resident != 2 || m->col_lds_bytes <= 0) return MADE_OK;
   const bool seq = block == 0;
+  const made_model::ColumnLds& lds = m->col_lds[seq];
+  if (m->arch != 0 || m->use_resident != 2 || lds.bytes <= 0) return MADE_OK;
   if (seq ? m->col_blocks == 0 : block > COL_POS) return MADE_OK;
   const bool narrow = m->widest_tiles <= 8;
-  if (seq ? narrow && N > 32768 : N > (m->res_lds_bytes > 0 ? 2048 : m->dtype == MADE_BF16 ? 24576 : 1 << 30)) return MADE_OK;
+  if (seq ? narrow && N > 32768 : m->res_lds_bytes > 0 && N > (block < 4 ? 2048 : 3072)) return MADE_OK;
   for (int a = 0; !seq && a < m->D; a += block)
     if (column_units(m, a, std::min(a + block, m->D)) > COL_UNITS) return MADE_OK;
   ColumnArgs p;
@@ -2423,15 +2441,16 @@ static int run_column(made_model* m, const float* noise, int N, const uint8_t* x
     p.W[l] = m->layers[l].W;
     p.bias[l] = m->layers[l].bias;
     p.k_chunks[l] = m->layers[l].k_chunks;
-    p.lds_act[l] = m->col_lds_act[l];
-    p.lds_w[l] = m->col_lds_w[l];
+    p.lds_act[l] = lds.act[l];
+    p.lds_w[l] = lds.w[l];
     if (l < m->L) {
       p.cnt_lt[l] = m->layers[l].cnt_lt;
-      p.lds_cnt[l] = m->col_lds_cnt[l];
+      p.lds_cnt[l] = lds.cnt[l];
     }
   }
-  p.lds_red = m->col_lds_red;
-  p.lds_clear = m->col_lds_clear;
+  p.lds_red = lds.red;
+  p.lds_w_bytes = lds.w_bytes;
+  p.lds_clear = lds.clear;
   p.bounds = seq ? m->col_bounds : nullptr;
   p.n_blocks = seq ? m->col_blocks : (m->D + block - 1) / block;
   p.block = block;
@@ -2441,14 +2460,14 @@ static int run_column(made_model* m, const float* noise, int N, const uint8_t* x
   p.x_init = x_init;
   p.x = x;
   p.iters = iters_out ? iters_out : m->ws.iters;
-  p.lds_passes = m->col_lds_passes;
+  p.lds_passes = lds.passes;
   p.ctr = m->col_ctr;
   p.block_passes = m->col_block_passes;
   p.host = (unsigned long long*)m->col_host;
   p.call_id = ++m->col_calls;
   prof_mark(m, m->L + 1, false, s);
   column_kernel(m, seq, [&](auto* kernel) {
-    hipLaunchKernelGGL(kernel, dim3((N + COL_S - 1) / COL_S), dim3(COL_WAVES * 64), (size_t)m->col_lds_bytes, s, p);
+    hipLaunchKernelGGL(kernel, dim3((N + COL_S - 1) / COL_S), dim3(COL_WAVES * 64), (size_t)lds.bytes, s, p);
   });
   prof_mark(m, m->L + 1, true, s);
   HIP_TRY(hipGetLastError());

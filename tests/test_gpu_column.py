@@ -100,6 +100,60 @@ def test_too_many_units_of_one_degree_take_the_other_paths():
         B.made_free(h)
 
 
+@pytest.mark.parametrize("crowd,at,before,dtype", [(64, 5, 31, "bf16"), (64, 5, 32, "bf16"), (61, 3, 7, "bf16"), (63, 9, 1, "f32"), (60, 5, 2, "bf16")])
+def test_a_position_with_as_many_units_as_a_wave_has_lanes(crowd, at, before, dtype):
+    """`crowd` units of degree `at` in both layers behind `before` units of lower degree (the block's weights then begin at an
+    odd or an even input): the widest blocks the kernel takes, alone and among others."""
+    D, N = 14, 5
+    w = S.Workload(f"crowd{crowd}", D, 1, [crowd + before + 20] * 2, dtype, N, "random", "fan_in", S.SEED_BASE + 760 + before, gain=2.5)
+    net = S.make_network(w, with_bias=True)
+    for d in net.degrees:
+        d[:] = D - 1 - np.arange(d.size) % 3
+        d[:crowd] = at
+        d[crowd:crowd + before] = 1 + np.arange(before) % (at - 1)
+    noise = S.make_noise(w)
+    ref = O.build_model(net.D, net.C, net.degrees, net.W, net.b, "bf16" if dtype == "bf16" else None)
+    xs, margin = O.sequential_sample(ref, noise)
+    clear = margin.min(axis=1) >= 1e-3
+    h = B.model_from_network(net)
+    try:
+        u = torch.from_numpy(noise).cuda()
+        x = torch.empty((N, D), dtype=torch.uint8, device="cuda")
+        for call in (lambda: B.sequential_sample(h, u, N, 1, x), lambda: B.gs_jacobi_sample(h, u, N, None, 1, x)):
+            x.fill_(9)
+            call()
+            torch.cuda.synchronize()
+            assert B.made_last_stats(h)["kernels"] == 1
+            ok, at_ = O.fixed_point_check(ref, x.cpu().numpy(), noise)
+            assert (ok | (at_ < 1e-3)).all()
+            assert (x.cpu().numpy()[clear] == xs[clear]).all()
+    finally:
+        B.made_free(h)
+
+
+@pytest.mark.parametrize("D,hidden,dtype", [(100, [2500, 2200], "f32"), (90, [2300, 2100, 1900], "bf16"), (60, [1200, 900, 700], "f32")])
+def test_models_that_leave_room_for_one_buffer_of_staged_weights(D, hidden, dtype):
+    """Inputs of 60 to 100 KB per workgroup: a block's own weights are written between two blocks."""
+    N = 6
+    w = S.Workload(f"one{D}", D, 1, hidden, dtype, N, "random", "fan_in", S.SEED_BASE + 740 + D, gain=2.5)
+    net = S.make_network(w, with_bias=True)
+    noise = S.make_noise(w)
+    ref = O.build_model(net.D, net.C, net.degrees, net.W, net.b, "bf16" if dtype == "bf16" else None)
+    h = B.model_from_network(net)
+    try:
+        u = torch.from_numpy(noise).cuda()
+        x = torch.empty((N, D), dtype=torch.uint8, device="cuda")
+        for call in (lambda: B.sequential_sample(h, u, N, 1, x), lambda: B.gs_jacobi_sample(h, u, N, None, 1, x)):
+            x.fill_(9)
+            call()
+            torch.cuda.synchronize()
+            assert B.made_last_stats(h)["kernels"] == 1
+            ok, margin = O.fixed_point_check(ref, x.cpu().numpy(), noise)
+            assert (ok | (margin < 1e-3)).all()
+    finally:
+        B.made_free(h)
+
+
 def test_a_smaller_model_made_later_leaves_the_larger_one_its_lds():
     """Two models of one depth and type alive, the larger (about 130 KB of LDS) called after the smaller was made."""
     models = []
