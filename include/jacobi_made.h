@@ -246,7 +246,8 @@ int gs_jacobi_sample_real(made_model* m, const float* noise, int32_t N, const fl
  *   out[3] host waits on the device
  *   out[4] convolutional model: image rows recomputed by the k x k layers, summed over passes and images (a pass
  *          only recomputes the rows below the first symbol that changed in the pass before); 0 otherwise
- *   out[5] passes whose stop test had no tail (MADE_OPT_LAZY_STOP_TEST: the next pass derived its list itself)
+ *   out[5] passes whose stop test had no tail (MADE_OPT_LAZY_STOP_TEST: the next pass derived its list itself; real states in
+ *          one launch, see MADE_OPT_XCD_RESIDENT: all but the last allowed pass)
  *   out[6] jacobi_sample of a 256-class model: visible output-layer weights the call's passes multiplied per sample
  *          (a pass skips the positions below the first one its predecessor changed: MADE_OPT_FROZEN_POSITIONS);
  *          0 otherwise
@@ -295,13 +296,16 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   recording fixes: a set of arguments called again and again has two recordings, made by its third and fourth call.)
  *   Same results and pass counts.  The model keeps the 128 most recently used recordings; a
  *   change of any option or of the workspace size discards them.  The caller must not capture such a call itself.
- *   MADE_OPT_XCD_RESIDENT (default 1; 0, 1 or 2): jacobi_sample / gs_jacobi_sample of Bernoulli models in ONE launch in
+ *   MADE_OPT_XCD_RESIDENT (default 1; 0, 1 or 2): jacobi_sample / gs_jacobi_sample of Bernoulli models, and jacobi_sample_real
+ *   on up to 256 samples (one chain, MADE_OPT_LAZY_STOP_TEST = 1, more than one allowed pass), in ONE launch in
  *   which every XCD (a group of compute units with an L2 of its own) iterates its own eighth of the samples through
  *   all passes, synchronising only among its own workgroups and through its own L2 -- samples are independent
  *   systems, so nothing has to cross the chip.  0 = never; 1 = where it was measured faster than one launch per layer
- *   and pass: gs_jacobi_sample up to 1024 samples (1.5-2x), jacobi_sample up to 512 samples on models whose layers are
- *   at most 1024 units wide (1.2-1.3x; on wider layers a phase of this kernel costs more than a launch); 2 = whenever
- *   the batch fits (2048 samples).  Same symbols and pass counts as the per-layer launches.  The kernel checks that its workgroups sit on the XCDs it assumes and are
+ *   and pass: gs_jacobi_sample up to 1024 samples (1.5-2x), jacobi_sample and jacobi_sample_real up to 256 samples on models of
+ *   up to 6 MB of visible weights and 2048 units a layer (1.4-2x), jacobi_sample up to 512 samples on models whose layers are
+ *   at most 1024 units wide (1.2-1.3x); 2 = whenever
+ *   the batch fits (2048 samples, jacobi_sample_real: 256).  A call that finds another such call under way on the device takes
+ *   the per-layer launches.  Same symbols and pass counts as the per-layer launches.  The kernel checks that its workgroups sit on the XCDs it assumes and are
  *   all resident; if not it backs out, and this and every later call on the model take the per-layer launches.
  *   MADE_OPT_FUSED_CATEGORICAL (default 1): draw the Gumbel-max symbols inside the output layer's kernel (C = 256:
  *   always, logits stay in registers; other C: batches below the two tile-batch options, logits stay in LDS); 0 = write

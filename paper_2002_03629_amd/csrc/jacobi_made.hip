@@ -28,6 +28,7 @@
 #include "onehot.hpp"
 #include "categorical_any.hpp"
 #include "column.hpp"
+#include "xcd_pass.hpp"
 #include "quad_tile.hpp"
 
 using namespace jm;
@@ -171,6 +172,10 @@ struct Workspace {
   volatile int* xcd_report = nullptr;     // pinned, device-visible: what xcd_sampler_kernel reports (8 words per XCD + flags)
   int* xcd_report_dev = nullptr;     // the same memory as the device addresses it
   unsigned xcd_calls = 0;            // calls served by xcd_sampler_kernel on this workspace
+  unsigned long long* xp_slots = nullptr;   // xcd_pass_kernel: barrier flags [XCDS][XP_GROUP],
+  unsigned* xp_words = nullptr;             // registration and barrier counts [XCDS][32], and behind them its back-out flags
+  unsigned xp_calls = 0;
+  unsigned xcd_report_calls = 0;            // calls that reported through xcd_report
 };
 
 // Masked convolutional model (arch 1): first layer 3 -> F (type A), n_conv - 1 layers F -> F (type B), 1 x 1 head.
@@ -273,6 +278,7 @@ struct made_model {
   int lazy_retire = 1;                        // made_set_option(MADE_OPT_LAZY_STOP_TEST): 1 = Jacobi on lists of up to 256 samples
                                               // derives a pass's list in its first kernel instead of in the previous one's tail
   int use_xcd = 1;                            // made_set_option(MADE_OPT_XCD_RESIDENT): 0 never, 1 where it pays, 2 whenever possible
+  bool xp_fits = false;                       // xcd_pass_kernel can serve this model on this device
   int xcd_grid = 0;                           // workgroups of xcd_sampler_kernel (0 = not usable on this device / model)
   // block-wise forward substitution (column_sampler_kernel): LDS layout, 0 bytes = this model does not fit
   struct ColumnLds {                     // [0] GS-Jacobi, [1] sequential; bytes = 0: the model does not fit
@@ -336,6 +342,8 @@ static void free_workspace(Workspace& w) {
   if (w.flags) (void)hipFree(w.flags);
   if (w.h_pin) (void)hipHostFree((void*)w.h_pin);
   if (w.xcd_report) (void)hipHostFree((void*)w.xcd_report);
+  if (w.xp_slots) (void)hipFree(w.xp_slots);
+  if (w.xp_words) (void)hipFree(w.xp_words);
   w = Workspace();
 }
 
@@ -416,6 +424,11 @@ static int ensure_workspace(made_model* m, int N, bool need_z) {
   HIP_TRY(hipHostGetDevicePointer((void**)&w.xcd_report_dev, (void*)w.xcd_report, 0));
   for (int i = 0; i < 8 * XCDS + 8; ++i) w.xcd_report[i] = 0;
   w.xcd_calls = 0;
+  HIP_TRY(hipMalloc((void**)&w.xp_slots, (size_t)XCDS * XP_GROUP * sizeof(unsigned long long)));
+  HIP_TRY(hipMemset(w.xp_slots, 0, (size_t)XCDS * XP_GROUP * sizeof(unsigned long long)));
+  HIP_TRY(hipMalloc((void**)&w.xp_words, (size_t)(XCDS + 1) * 32 * sizeof(unsigned)));
+  HIP_TRY(hipMemset(w.xp_words, 0, (size_t)(XCDS + 1) * 32 * sizeof(unsigned)));
+  w.xp_calls = 0;
   HIP_TRY(hipMalloc((void**)&w.dev_stats, (size_t)2 * XCDS * sizeof(long long)));
   HIP_TRY(hipMalloc((void**)&w.iters, (size_t)n_pad * sizeof(int)));
   HIP_TRY(hipMalloc((void**)&w.flags, sizeof(int)));
@@ -627,6 +640,12 @@ static int validate_config(const made_config* cfg, const int32_t* const* degrees
   }
   if (!W[cfg->n_hidden]) return fail(MADE_ERR_ARG, "made_init: W[%d] (output layer) is NULL", cfg->n_hidden);
   return MADE_OK;
+}
+
+template <typename F>
+static void xcd_pass_pick(const made_model* m, F&& f) {
+  if (m->dtype == MADE_BF16) m->real ? f(xcd_pass_kernel<bf16_t, true>) : f(xcd_pass_kernel<bf16_t, false>);
+  else m->real ? f(xcd_pass_kernel<float, true>) : f(xcd_pass_kernel<float, false>);
 }
 
 template <typename F>
@@ -912,6 +931,13 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
     if (pe == hipSuccess && per_cu_x >= 1 && cus >= XCDS && cus % XCDS == 0 && C == 1 && !m->real &&
         L + 1 <= PERSIST_MAX_LAYERS)
       m->xcd_grid = std::min(cus * std::min(per_cu_x, 2), XCDS * XCD_LINE);
+    // xcd_pass_kernel: one workgroup on each of 256 compute units, two unit tiles of a layer at most
+    int per_cu_p = 0;
+    if (pe == hipSuccess)
+      xcd_pass_pick(m, [&](auto* kernel) { pe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_p, kernel, NW * 64, 0); });
+    m->xp_fits = pe == hipSuccess && per_cu_p >= 1 && cus == XCDS * XP_GROUP && (C == 1 || m->real) && !m->onehot &&
+                 L + 1 <= PERSIST_MAX_LAYERS;
+    for (int l = 0; l <= L; ++l) m->xp_fits = m->xp_fits && m->layers[l].n_tiles <= XP_MAX_TILES;
     (void)hipGetLastError();
   }
   // The sample-resident kernel keeps one 32-sample row group of the input and of every hidden layer, the biases
@@ -2603,6 +2629,62 @@ static int run_persistent(made_model* m, const float* noise, int N, const uint8_
   return MADE_OK;
 }
 
+// The kernels whose workgroups wait for one another need the whole chip: two of them, of two models called from two threads, could
+// each get a part of it and wait until both back out.  A call that finds another one under way takes the other paths, whose
+// results are the same bit for bit.  (A call's kernel has reported when the call lets go; what is left of it waits for nobody.)
+struct WholeChip {
+  static std::atomic<int>& taken(int device) {
+    static std::atomic<int> flags[NOALLOC_MAX_DEVICES];
+    return flags[device >= 0 && device < NOALLOC_MAX_DEVICES ? device : 0];
+  }
+  std::atomic<int>& flag;
+  const bool got;
+  explicit WholeChip(int device) : flag(taken(device)), got(flag.exchange(1, std::memory_order_acquire) == 0) {}
+  ~WholeChip() { if (got) flag.store(0, std::memory_order_release); }
+  WholeChip(const WholeChip&) = delete;
+};
+
+// Every XCD's first workgroup reports into pinned memory once its share of the batch is done; the call returns when all have
+// (results stay ordered on the stream like those of any launch).
+static int xcd_wait(made_model* m, int call_id, hipStream_t s, bool* backed_out) {
+  Workspace& w = m->ws;
+  const auto t0 = std::chrono::steady_clock::now();
+  uint64_t polls = 0;
+  for (;;) {
+    if (w.xcd_report[64] != 0) { *backed_out = true; break; }
+    int n_done = 0;
+    for (int g = 0; g < XCDS; ++g) n_done += (w.xcd_report[g * 8 + 5] == call_id);
+    if (n_done == XCDS) break;
+    if ((++polls & 0xfff) == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > 30.0)
+      return give_up_waiting(m, s);
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  if (m->profiling || *backed_out) {
+    HIP_TRY(hipStreamSynchronize(s));
+    m->stats[3] += 1;
+    w.pending = false;
+  } else {
+    w.pending = true;                // (workgroups may still be writing symbols and leaving the kernel)
+    w.pending_stream = s;
+  }
+  prof_collect(m);
+  *backed_out = *backed_out || w.xcd_report[64] != 0;
+  return MADE_OK;
+}
+
+static int xcd_results(made_model* m) {
+  int call_flags = 0;
+  for (int g = 0; g < XCDS; ++g) {
+    const volatile int* r = m->ws.xcd_report + g * 8;
+    const int64_t passes = ((int64_t)r[1] << 32) | (uint32_t)r[0], sp = ((int64_t)r[3] << 32) | (uint32_t)r[2];
+    m->stats[0] = std::max<int64_t>(m->stats[0], passes);
+    m->stats[1] += sp;
+    call_flags |= r[4];
+  }
+  if (call_flags & 1) return fail(MADE_ERR_NOT_CONVERGED, "samples were still changing after the last allowed pass");
+  return MADE_OK;
+}
+
 // The whole call in one launch, each XCD iterating its own share of the samples (see xcd_sampler_kernel).  *done = true
 // when the call was served this way; when the kernel backs out (workgroups not on the expected XCD, or not
 // co-resident) the path is switched off for this model and the caller takes the per-layer launches.
@@ -2623,6 +2705,8 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
     const bool gs = block < m->D;
     if (gs ? N > 1024 : (N > 512 || widest > 32)) return MADE_OK;
   }
+  WholeChip chip(m->device);
+  if (!chip.got) return MADE_OK;
   Workspace& w = m->ws;
   PersistArgs p;
   memset(&p, 0, sizeof p);
@@ -2658,8 +2742,8 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
   p.bar = w.bar;
   p.stats = w.dev_stats;
   p.spin_limit = 1u << 20;
-  p.reg_base = w.xcd_calls * (unsigned)(m->xcd_grid / XCDS);
-  p.call_id = (int)(++w.xcd_calls);
+  p.reg_base = w.xcd_calls++ * (unsigned)(m->xcd_grid / XCDS);
+  p.call_id = (int)(++w.xcd_report_calls);
   p.host_report = w.xcd_report_dev;
   // The device flags are only ever set when the kernel backs out (after which this path is switched off), but the
   // per-layer scheduler and the persistent kernel share the word: the stream-ordered clear costs one small memset.
@@ -2672,29 +2756,9 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
   prof_mark(m, m->L + 1, true, s);
   HIP_TRY(hipGetLastError());
   m->stats[2] += 1;
-  // Every XCD's first workgroup reports into pinned memory once its share of the batch is done; the call returns
-  // when all have (results stay ordered on the stream like those of any launch).
-  const auto t0 = std::chrono::steady_clock::now();
-  uint64_t polls = 0;
   bool backed_out = false;
-  for (;;) {
-    if (w.xcd_report[64] != 0) { backed_out = true; break; }
-    int n_done = 0;
-    for (int g = 0; g < XCDS; ++g) n_done += (w.xcd_report[g * 8 + 5] == p.call_id);
-    if (n_done == XCDS) break;
-    if ((++polls & 0xfff) == 0 && std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > 30.0)
-      return give_up_waiting(m, s);
-  }
-  if (m->profiling || backed_out) {
-    HIP_TRY(hipStreamSynchronize(s));
-    m->stats[3] += 1;
-    w.pending = false;
-  } else {
-    w.pending = true;                // (workgroups may still be leaving the kernel; they touch nothing any more)
-    w.pending_stream = s;
-  }
-  prof_collect(m);
-  if (backed_out || w.xcd_report[64] != 0) {     // results are incomplete: take the other path from now on
+  TRY(xcd_wait(m, p.call_id, s, &backed_out));
+  if (backed_out) {                              // results are incomplete: take the other path from now on
     const int flags = w.xcd_report[64];
     unsigned counters[2 * XCDS * XCD_LINE];
     memset(counters, 0, sizeof counters);
@@ -2711,17 +2775,87 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
     w.xcd_report[64] = 0;
     return MADE_OK;
   }
-  int call_flags = 0;
-  for (int g = 0; g < XCDS; ++g) {
-    const volatile int* r = w.xcd_report + g * 8;
-    const int64_t passes = ((int64_t)r[1] << 32) | (uint32_t)r[0], sp = ((int64_t)r[3] << 32) | (uint32_t)r[2];
-    m->stats[0] = std::max<int64_t>(m->stats[0], passes);
-    m->stats[1] += sp;
-    call_flags |= r[4];
+  *done = true;
+  return xcd_results(m);
+}
+
+// jacobi_sample / jacobi_sample_real in one launch of xcd_pass_kernel: up to 32 samples per XCD.  *done as in run_xcd.
+// Where it pays (use_xcd = 1), measured in us a call against the per-layer launches, batch 1 / 16 / 128 / 256: 64 / 256 fp32 30 / 37 /
+// 42 / 43 against 43 / 52 / 64 / 65; 784 / 2 x 512 real 85 / 98 / 99 / 108 against 143 / 192 / 208 / 234; 784 / 2 x 1000 fp32 64 / 99 /
+// 99 / 103 against 83 / 135 / 143 / 150; 784 / 2 x 1500 (4.6 MB of visible weights) 51 / 54 / 62 / 65 against 70 / 71 / 90 / 97;
+// 300 / 2 x 2000 (5.2 MB) 51 / 56 / 70 / 82 against 58 / 59 / 80 / 105.  Every XCD reads all weights, so the gain shrinks once they
+// pass its L2 of 4 MB: 784 / 2 x 2000 (7.4 MB) 51 / 71 / 83 / 96 against 59 / 75 / 96 / 122.  The line is at 6 MB: wider models keep
+// the per-layer launches, whose kernels the profile of a call can tell apart.
+static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_init, void* x, float eps, int cap,
+                        int32_t* iters_out, hipStream_t s, bool* done) {
+  *done = false;
+  if (!m->use_xcd || !m->xp_fits || N > XCDS * XP_ROWS || m->n_chains > 1) return MADE_OK;
+  // (real states: one of the calls that MADE_OPT_LAZY_STOP_TEST covers)
+  if (m->real && (!m->lazy_retire || cap < 2)) return MADE_OK;
+  if (m->use_xcd == 1) {
+    size_t visible = 0;
+    for (const Layer& ly : m->layers)
+      for (int k : ly.h_tile_kend) visible += (size_t)k * TILE * elem_size(m);
+    if (visible > (size_t)XP_VISIBLE) return MADE_OK;
+  }
+  WholeChip chip(m->device);
+  if (!chip.got) return MADE_OK;
+  Workspace& w = m->ws;
+  XcdPassArgs p;
+  memset(&p, 0, sizeof p);
+  for (int l = 0; l <= m->L; ++l) {
+    const Layer& ly = m->layers[l];
+    PersistLayer& pl = p.layer[l];
+    pl.W = ly.W;
+    pl.bias = ly.bias;
+    pl.tile_kend = ly.tile_kend;
+    pl.out = l < m->L ? w.act[l] : nullptr;
+    pl.k_chunks = ly.k_chunks;
+    pl.n_tiles = ly.n_tiles;
+    pl.out_chunks = l < m->L ? m->layers[l + 1].k_chunks : 0;
+    const size_t bytes = (size_t)w.n_pad * ly.in_pad * elem_size(m);
+    if (bytes >= ((size_t)1 << 31)) return MADE_OK;          // (the workspace of a call with far more samples)
+    p.row_bytes[l] = (unsigned)bytes;
+  }
+  p.L = m->L;
+  p.enc = w.enc;
+  p.enc_chunks = m->layers[0].k_chunks;
+  p.noise = noise;
+  p.x_init = x_init;
+  p.x = x;
+  p.eps = eps;
+  p.N = N;
+  p.D = m->D;
+  p.cap = cap;
+  p.flag_unconverged = cap < m->D;
+  p.zero_start = m->zero_start_fill && !x_init;
+  p.iters = iters_out ? iters_out : w.iters;
+  p.slots = w.xp_slots;
+  p.words = w.xp_words;
+  p.flags = (int*)(w.xp_words + XCDS * 32);
+  p.spin_limit = 1u << 20;
+  p.reg_base = w.xp_calls++ * (unsigned)XP_GROUP;
+  p.call_id = (int)(++w.xcd_report_calls);
+  p.host_report = w.xcd_report_dev;
+  prof_mark(m, m->L + 1, false, s);
+  xcd_pass_pick(m, [&](auto* kernel) { hipLaunchKernelGGL(kernel, dim3(XCDS * XP_GROUP), dim3(NW * 64), 0, s, p); });
+  prof_mark(m, m->L + 1, true, s);
+  HIP_TRY(hipGetLastError());
+  m->stats[2] += 1;
+  bool backed_out = false;
+  TRY(xcd_wait(m, p.call_id, s, &backed_out));
+  if (backed_out) {
+    (void)fail(MADE_OK, "xcd_pass_kernel backed out (flags %d: 4 = more workgroups on an XCD than expected, 2 = a barrier's "
+                        "wait ran out); other paths serve this model from now on", (int)w.xcd_report[64]);
+    m->xp_fits = false;
+    m->stats[2] = 0;
+    w.xcd_report[64] = 0;
+    return MADE_OK;
   }
   *done = true;
-  if (call_flags & 1) return fail(MADE_ERR_NOT_CONVERGED, "samples were still changing after the last allowed pass");
-  return MADE_OK;
+  const int rc = xcd_results(m);
+  if (m->real) m->stats[5] = std::min<int64_t>(m->stats[0], cap - 1);   // (the last allowed pass counts as one with a tail)
+  return rc;
 }
 
 // The whole call in one launch of the sample-resident kernel (see resident_sampler_kernel): one workgroup per 32
@@ -2801,6 +2935,8 @@ extern "C" int jacobi_sample(made_model* m, const float* noise, int32_t N, const
   const int cap = (max_iters <= 0 || max_iters > m->D) ? m->D : max_iters;
   bool done = false;
   TRY(run_persistent(m, noise, N, x_init, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
+  if (done) return MADE_OK;
+  TRY(run_xcd_pass(m, noise, N, x_init, x_out, 0.f, cap, iters_out, s, &done));
   if (done) return MADE_OK;
   if (N <= 256) TRY(run_xcd(m, noise, N, x_init, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
   if (done) return MADE_OK;
@@ -2909,6 +3045,9 @@ extern "C" int jacobi_sample_real(made_model* m, const float* noise, int32_t N, 
   TRY(settle(m, s));
   TRY(ensure_workspace(m, N, true));
   const int cap = (max_iters <= 0 || max_iters > m->D) ? m->D : max_iters;
+  bool done = false;
+  TRY(run_xcd_pass(m, noise, N, x_init, x_out, eps, cap, iters_out, s, &done));
+  if (done) return MADE_OK;
   std::vector<Block> blocks(1, make_block(m, 0, m->D, cap, false));
   return run_chains(m, blocks, noise, (const uint8_t*)x_init, (uint8_t*)x_out, N, cap < m->D, iters_out, s);
 }

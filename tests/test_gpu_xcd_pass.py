@@ -1,0 +1,109 @@
+"""A Jacobi call in one launch, every XCD on its own eighth of the batch, against the per-layer launches: the same sums in the
+same order, so the same symbols or states bit for bit, the same pass counts and the same verdict -- where the rows of an XCD, the
+unit tiles of its workgroups (none, one, two) or the K chunks of a wave (none, those requested ahead, more) run out, with a
+start of one's own, pass limits and a tolerance."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2002_03629_amd import binding as B
+from paper_2002_03629_amd import synth as S
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # D, hidden, dtype
+    (64, [256], "f32"), (2, [3], "bf16"), (33, [31, 65], "bf16"), (131, [96, 160, 40], "f32"), (200, [1024, 1025], "bf16"),
+    (100, [2048], "bf16"), (60, [1500, 300], "f32"), (784, [512, 512], "bf16")]
+
+
+def _call(h, real, noise, N, init, eps, cap, D):
+    x = torch.full((N, D), 7, dtype=torch.float32 if real else torch.uint8, device="cuda")
+    it = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    code = 0
+    try:
+        if real:
+            B.jacobi_sample_real(h, noise, N, init, eps, cap, x, it)
+        else:
+            B.jacobi_sample(h, noise, N, init, cap, x, it)
+    except B.MadeError as e:
+        code = e.code
+        assert code == B.MADE_ERR_NOT_CONVERGED
+    torch.cuda.synchronize()
+    return x.cpu().numpy(), it.cpu().numpy(), code, B.made_last_stats(h)
+
+
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("D,hidden,dtype", SHAPES)
+def test_against_launches(D, hidden, dtype, real):
+    w = S.Workload(f"xp{D}", D, 2 if real else 1, hidden, dtype, 256, "random", "fan_in", S.SEED_BASE + 2100 + D, gain=2.0, real=real)
+    net = S.make_network(w, with_bias=True)
+    gen = np.random.default_rng(D)
+    h = B.model_from_network(net)
+    try:
+        for N in (1, 8, 9, 100, 255, 256):
+            noise = (gen.logistic(size=(N, D)) if real else gen.random((N, D))).astype(np.float32)
+            start = gen.normal(size=(N, D)).astype(np.float32) if real else gen.integers(0, 2, size=(N, D)).astype(np.uint8)
+            noise, start = torch.from_numpy(noise).cuda(), torch.from_numpy(start).cuda()
+            for init, eps, cap, zero in ((None, 0.0, 0, 1), (start, 0.0, 0, 1), (None, 0.05, 3, 1), (None, 0.0, 2, 0)):
+                if not real and eps:
+                    continue
+                B.made_set_option(h, B.MADE_OPT_ZERO_START, zero)
+                out = []
+                for xcd in (2, 0):
+                    B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, xcd)
+                    out.append(_call(h, real, noise, N, init, eps, cap, D))
+                (xa, ia, ca, sa), (xb, ib, cb, sb) = out
+                assert sa["kernels"] == 1 and sb["kernels"] > 1, B.made_last_error()
+                assert (xa == xb).all() and (ia == ib).all() and ca == cb, (N, init is not None, eps, cap)
+                assert sa["sample_passes"] == sb["sample_passes"] == ia.sum() and sa["passes"] == sb["passes"]
+    finally:
+        B.made_free(h)
+
+
+def test_more_samples_and_one_hot_models_take_the_other_paths():
+    w = S.Workload("xpn", 40, 2, [50], "bf16", 257, "random", "fan_in", S.SEED_BASE + 2190, gain=1.5, real=True)
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    try:
+        noise = torch.from_numpy(np.random.default_rng(3).logistic(size=(257, 40)).astype(np.float32)).cuda()
+        for N, one in ((256, True), (257, False), (256, True)):
+            st = _call(h, True, noise, N, None, 0.0, 0, 40)[3]
+            assert (st["kernels"] == 1) == one, st
+    finally:
+        B.made_free(h)
+
+
+def test_calls_from_two_threads_do_not_wait_for_each_other():
+    """Two models sampled at once, from two threads on two streams: whichever path a call finds free, its result is the one it
+    reaches alone."""
+    import threading
+    models = []
+    for real in (True, False):
+        w = S.Workload(f"xpt{real}", 120, 2 if real else 1, [200, 150], "bf16", 60, "random", "fan_in", S.SEED_BASE + 2195, gain=2.0, real=real)
+        models.append((real, B.model_from_network(S.make_network(w, with_bias=True))))
+    gen = np.random.default_rng(8)
+    noises = [torch.from_numpy((gen.logistic(size=(60, 120)) if real else gen.random((60, 120))).astype(np.float32)).cuda() for real, _ in models]
+    try:
+        alone = [_call(h, real, u, 60, None, 0.0, 0, 120)[:2] for (real, h), u in zip(models, noises)]
+        wrong = []
+
+        def work(i):
+            real, h = models[i]
+            x = torch.empty(60, 120, dtype=torch.float32 if real else torch.uint8, device="cuda")
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(20):
+                    (B.jacobi_sample_real(h, noises[i], 60, None, 0.0, 0, x) if real else B.jacobi_sample(h, noises[i], 60, None, 0, x))
+                    torch.cuda.current_stream().synchronize()
+                    if not (x.cpu().numpy() == alone[i][0]).all():
+                        wrong.append(i)
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not wrong
+        for (real, h), u in zip(models, noises):      # (nothing was switched off on the way)
+            assert _call(h, real, u, 60, None, 0.0, 0, 120)[3]["kernels"] == 1
+    finally:
+        for _, h in models:
+            B.made_free(h)
