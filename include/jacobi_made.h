@@ -286,7 +286,9 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   launches, batches whose layers run on the 32 x 32 or 64 x 64 tiles): the first hidden layer of
  *   the first pass multiplies an all-zero input, so the kernel that sets the call up writes its activations, ReLU(bias),
  *   itself, and the first pass starts at the second hidden layer: one launch less per call, same results bit for bit.
- *   0 = launch the layer.
+ *   From 512 samples on the whole first pass of such a call multiplies equal rows: its layers are evaluated for one row
+ *   and every sample is drawn from that (the same symbols, up to the order of a sum's terms on the batches of the LDS-staged
+ *   tiles; same fixed point).  0 = launch the layers for every sample.
  *   MADE_OPT_CALL_GRAPH (default 0; 0 or 1): calls that MADE_OPT_LAZY_STOP_TEST covers are short and bound by what the
  *   host pays per kernel launch.  With 1, the second call with the same arguments (noise, x_init, x_out and iters_out
  *   pointers, N, max_iters, flag, a stream other than the null stream; the buffers' contents may differ) records the

@@ -130,6 +130,7 @@ struct Chain {
   int bound = 0;                     // upper limit of the active count in the current block: the chain's size, then
                                      // what the latest confirmed pass left (the list only shrinks inside a block)
   bool block_started = false, finished = false, iters_cleared = false;
+  bool first_row = false;            // this call's first pass evaluates the layers for one row (see enqueue_first_row)
   bool lazy = false;                 // this call's passes use the tail-less stop test (see DeriveArgs)
   bool frozen = false;               // this call's passes skip the output positions that cannot change (CatArgs::t_first_ptr)
   bool first_hidden_ready = false;   // the set-up kernel wrote the first hidden layer of the call's first pass (zero start)
@@ -158,6 +159,7 @@ struct Workspace {
   float* zero_bias = nullptr;        // [largest out_pad] zeros: the launches that fill `partial` add no bias
   int* changed = nullptr;
   unsigned* lazy_masks = nullptr;    // [3 * DERIVE_WORDS] changed-row bits of the tail-less stop test (see DeriveArgs)
+  float* first_z = nullptr;          // Bernoulli models: the logits of one row (see first_draw_kernel)
   int* iters = nullptr;
   int* call_iters = nullptr;         // where the current call counts passes per sample: the caller's iters_out, else `iters`
   bool pending = false;              // the last call returned with (empty, speculative) kernels still queued on
@@ -343,6 +345,7 @@ static void free_workspace(Workspace& w) {
   if (w.h_pin) (void)hipHostFree((void*)w.h_pin);
   if (w.xcd_report) (void)hipHostFree((void*)w.xcd_report);
   if (w.xp_slots) (void)hipFree(w.xp_slots);
+  if (w.first_z) (void)hipFree(w.first_z);
   if (w.xp_words) (void)hipFree(w.xp_words);
   w = Workspace();
 }
@@ -424,6 +427,7 @@ static int ensure_workspace(made_model* m, int N, bool need_z) {
   HIP_TRY(hipHostGetDevicePointer((void**)&w.xcd_report_dev, (void*)w.xcd_report, 0));
   for (int i = 0; i < 8 * XCDS + 8; ++i) w.xcd_report[i] = 0;
   w.xcd_calls = 0;
+  if (m->C == 1 && !m->real) HIP_TRY(hipMalloc((void**)&w.first_z, (size_t)m->layers[m->L].out_pad * sizeof(float)));
   HIP_TRY(hipMalloc((void**)&w.xp_slots, (size_t)XCDS * XP_GROUP * sizeof(unsigned long long)));
   HIP_TRY(hipMemset(w.xp_slots, 0, (size_t)XCDS * XP_GROUP * sizeof(unsigned long long)));
   HIP_TRY(hipMalloc((void**)&w.xp_words, (size_t)(XCDS + 1) * 32 * sizeof(unsigned)));
@@ -1702,13 +1706,13 @@ static void launch_conv_head(made_model* m, const ConvHeadArgs& c, hipStream_t s
 }
 
 static int launch_init_state(made_model* m, const uint8_t* x_init, uint8_t* x, int N, hipStream_t s,
-                             const CallReset* reset_in = nullptr, void* enc_buf = nullptr) {
+                             const CallReset* reset_in = nullptr, void* enc_buf = nullptr, int reset_rows = 0) {
   void* const enc = enc_buf ? enc_buf : m->ws.enc;
   CallReset reset;
   memset(&reset, 0, sizeof reset);
   if (reset_in) reset = *reset_in;
   const size_t total = (size_t)N * m->D;
-  const int blocks = (int)std::min<size_t>((total + 255) / 256, 4096);
+  const int blocks = (int)std::min<size_t>((std::max(total, (size_t)reset_rows) + 255) / 256, 4096);   // (reset_rows: list entries, if more)
   if (m->arch == 1) {   // the first convolution reads the symbols themselves
     if (x) {
       ConvNet& cv = m->conv;
@@ -2017,6 +2021,37 @@ static int fill_partial_sums(made_model* m, const RowSet& rs, const Block& blk, 
 }
 
 // Enqueue the next pass of chain c's current block on the chain's stream.
+// First pass of a call whose samples all start from zeros: the layers for one row (the first one's activations are there, see
+// CallReset), the logits, the draw of all samples.  Which pass it is, what it draws and what it reports are the same as with every
+// row evaluated; MADE_OPT_ZERO_START = 0 evaluates them.
+// Where it pays: from FIRST_ROW_BATCH samples on; below, the smaller launches save what one more costs.  us a call without and with
+// it at 512 / 1000 / 2048 / 8192 / 32768: 784 / 2 x 2000 bf16 168 / 212 / 334 / 597 / 1751 and 158 / 192 / 279 / 516 / 1402; 100 / 2 x 300
+// 63 / 83 / 105 / 219 / 280 and 64 / 82 / 98 / 173 / 231; 300 / 1000 73 / 130 / 180 / 350 / 685 and 75 / 126 / 167 / 301 / 574.
+constexpr int FIRST_ROW_BATCH = 512;
+static int enqueue_first_row(made_model* m, const float* noise, uint8_t* x, int N, hipStream_t s) {
+  Workspace& w = m->ws;
+  const RowSet one{nullptr, nullptr, 1};
+  TRY(run_hidden(m, one, nullptr, -1, s, nullptr, false, nullptr, nullptr, nullptr, 1));
+  LayerArgs a = base_args(m, m->L, w.act[m->L - 1], one);
+  a.out = w.first_z;
+  a.ldo = m->layers[m->L].out_pad;
+  launch_layer<EPI_LOGITS>(m, m->L, a, m->layers[m->L].n_tiles, 1, s);
+  // chunks of a wave: as many as leave four waves for every SIMD of the chip
+  const int chunks = m->layers[0].k_chunks, groups = (N + 31) / 32;
+  const int per_wave = std::max(1, std::min(chunks, groups * chunks / 4096));
+  const int waves = groups * ((chunks + per_wave - 1) / per_wave);
+  const int aligned = m->D % 4 == 0 && (uintptr_t)noise % 16 == 0 && (uintptr_t)x % 4 == 0;
+  if (m->dtype == MADE_BF16)
+    hipLaunchKernelGGL((first_draw_kernel<bf16_t>), dim3((waves + 3) / 4), dim3(256), 0, s, w.first_z, noise, x, (bf16_t*)w.enc, chunks, N,
+                       m->D, w.changed, per_wave, aligned);
+  else
+    hipLaunchKernelGGL((first_draw_kernel<float>), dim3((waves + 3) / 4), dim3(256), 0, s, w.first_z, noise, x, (float*)w.enc, chunks, N,
+                       m->D, w.changed, per_wave, aligned);
+  HIP_TRY(hipGetLastError());
+  m->stats[2]++;
+  return MADE_OK;
+}
+
 static int enqueue_pass(made_model* m, Chain& c, const Block& blk, const float* noise, uint8_t* x,
                         bool flag_unconverged, bool force_tail = false) {
   Workspace& w = m->ws;
@@ -2120,15 +2155,20 @@ static int enqueue_pass(made_model* m, Chain& c, const Block& blk, const float* 
                              c.bound_at_block_start >= m->partial_batch && blk.cap > 2;
     PartialSums ps{blk.k_first.data(), w.partial.data()};
     if (use_partial && k == 2) TRY(fill_partial_sums(m, rs, blk, s));
-    TRY(run_hidden(m, rs, blk.limited ? blk.hidden_limit.data() : nullptr, blk.in_limit, s,
-                   cached ? blk.hidden_frozen.data() : nullptr, by_pos, nullptr, use_partial ? &ps : nullptr,
-                   derive_in ? &dv : nullptr, (k == 1 && c.block == 0 && c.first_hidden_ready) ? 1 : 0));
+    const bool first_row = k == 1 && c.first_row;
+    if (first_row) {
+      TRY(enqueue_first_row(m, noise, x, c.count, s));
+    } else {
+      TRY(run_hidden(m, rs, blk.limited ? blk.hidden_limit.data() : nullptr, blk.in_limit, s,
+                     cached ? blk.hidden_frozen.data() : nullptr, by_pos, nullptr, use_partial ? &ps : nullptr,
+                     derive_in ? &dv : nullptr, (k == 1 && c.block == 0 && c.first_hidden_ready) ? 1 : 0));
+    }
     // a long list is retired by a kernel of its own, spread over the chip, instead of by the output kernel's
     // last workgroup
     const RetireArgs retire = io.retire;
-    const bool split_retire = retire.enabled && n_bound >= m->retire_split;
+    const bool split_retire = retire.enabled && (first_row || n_bound >= m->retire_split);
     if (split_retire) io.retire.enabled = 0;
-    TRY(run_output_sample(m, rs, io, blk.whole_network, blk.out_k_limit, s, by_pos, use_partial ? &ps : nullptr));
+    if (!first_row) TRY(run_output_sample(m, rs, io, blk.whole_network, blk.out_k_limit, s, by_pos, use_partial ? &ps : nullptr));
     if (split_retire) {
       hipLaunchKernelGGL(retire_kernel, dim3((n_bound + RETIRE_WG_ROWS - 1) / RETIRE_WG_ROWS), dim3(256), 0, s, retire);
       HIP_TRY(hipGetLastError());
@@ -2179,6 +2219,7 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
     c.block_started = c.finished = c.iters_cleared = false;
     c.lazy = false;
     c.first_hidden_ready = false;
+    c.first_row = false;
     c.log_first.clear();
     c.stream = n_chains == 1 ? s : c.own_stream;   // a single chain needs no fork and join
   }
@@ -2219,6 +2260,16 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
       r.h0_chunks = m->layers[1].k_chunks;
       r.h0_units = m->layers[0].n_tiles * TILE;
       c.first_hidden_ready = true;
+    }
+    // Large batches: the whole first pass of such a call evaluates the network on equal rows.  The layers take one of them, the
+    // draw takes all samples (enqueue_first_row).
+    if (m->zero_start_fill && !x_init && m->C == 1 && !m->real && !m->onehot && blocks.size() == 1 && !blocks[0].limited &&
+        blocks[0].stop_test && c.count >= FIRST_ROW_BATCH) {
+      r.h0_bias = m->layers[0].bias;
+      r.h0_out = w.act[0];
+      r.h0_chunks = m->layers[1].k_chunks;
+      r.h0_units = m->layers[0].n_tiles * TILE;
+      c.first_hidden_ready = c.first_row = true;
     }
     // A call of the tail-less kind is short (cfg2: 18 launches of ~5 us each) and bound by what the host pays per
     // launch: on request it is recorded once and replayed as one graph launch (see CallGraph).  The first call with
@@ -2297,7 +2348,9 @@ static int run_chains(made_model* m, const std::vector<Block>& blocks, const flo
       HIP_TRY(hipGraphLaunch(cg->exec, s));
       c.lazy = false;
     } else {
-      TRY(launch_init_state(m, x_init, x, N, s, &r));
+      // (first_row: the draw writes every symbol and its encoding, the set-up kernel one row of the first layer)
+      if (c.first_row) TRY(launch_init_state(m, nullptr, nullptr, 1, s, &r, nullptr, r.padded));
+      else TRY(launch_init_state(m, x_init, x, N, s, &r));
       c.block_started = true;
       c.iters_cleared = true;
     }

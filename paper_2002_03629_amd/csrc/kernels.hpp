@@ -2707,6 +2707,83 @@ __global__ void init_state_kernel(const uint8_t* x_init, uint8_t* x, T* enc, int
   }
 }
 
+// First pass of a call started from zeros, large batches: every sample's input is the same, so are their logits, and the layers
+// have been evaluated for one row (z).  What is left of the pass is the draw of N x D symbols, their encoding and the changed
+// counters: a stream of the noise (4 bytes in, 1 + 2 or 1 + 4 out per symbol).  A wave takes CPW chunks of a group of 32 samples;
+// lane (q, i) holds piece i of a chunk (the 16 bytes that frag_offset keeps together: 8 lanes, a line, of 8 samples) for the
+// samples q, q + 8, ...  Probabilities are those of the layer kernels' epilogues.  (Batch 32768 of 784 positions, 2 x 2000 units:
+// the pass took 428 us with every row evaluated; the call 1760 -> 1413 us.)
+template <typename T>
+__global__ __launch_bounds__(256) void first_draw_kernel(const float* z, const float* noise, uint8_t* x, T* enc, int enc_chunks, int N,
+                                                         int D, int* changed, int chunks_per_wave, int aligned) {
+  constexpr int P = 16 / (int)sizeof(T), KC = 8 * P;
+  const int lane = threadIdx.x & 63, wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int q = lane >> 3, i = lane & 7;
+  const int spans = (enc_chunks + chunks_per_wave - 1) / chunks_per_wave;
+  const int group = wave / spans, c0 = (wave % spans) * chunks_per_wave, c1 = min(c0 + chunks_per_wave, enc_chunks);
+  if (group * 32 >= N) return;
+  int count[4] = {0, 0, 0, 0};
+  for (int c = c0; c < c1; ++c) {
+    const int d = c * KC + i * P;
+    float prob[P];
+#pragma unroll
+    for (int e = 0; e < P; ++e) prob[e] = d + e < D ? bernoulli_probability(z[d + e]) : 0.f;
+    float u[4][P];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int n = group * 32 + 8 * k + q;
+      const float* src = noise + (size_t)n * D + d;
+      if (aligned && n < N && d + P <= D) {
+#pragma unroll
+        for (int e = 0; e < P; e += 4) {
+          const float4 v = *(const float4*)(src + e);
+          u[k][e] = v.x; u[k][e + 1] = v.y; u[k][e + 2] = v.z; u[k][e + 3] = v.w;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < P; ++e) u[k][e] = n < N && d + e < D ? src[e] : 1.f;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int n = group * 32 + 8 * k + q;
+      if (n >= N) continue;
+      unsigned bits = 0;
+#pragma unroll
+      for (int e = 0; e < P; ++e) bits |= (u[k][e] < prob[e] ? 1u : 0u) << e;
+      count[k] += __builtin_popcount(bits);
+      const uint32_t one = sizeof(T) == 2 ? 0x3f80u : 0x3f800000u;
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        w[e] = sizeof(T) == 2 ? ((bits >> (2 * e)) & 1u) * one | (((bits >> (2 * e + 1)) & 1u) * one) << 16 : ((bits >> e) & 1u) * one;
+      *(uint4*)((unsigned char*)enc + ((size_t)group * enc_chunks + c) * 4096 + (((i & 3) * 2 + (i >> 2)) * 32 + 8 * k + q) * 16) =
+          make_uint4(w[0], w[1], w[2], w[3]);
+      uint8_t* dst = x + (size_t)n * D + d;
+      if (aligned && d + P <= D) {
+#pragma unroll
+        for (int e = 0; e < P; e += 4) {
+          const uint32_t b = bits >> e;
+          *(uint32_t*)(dst + e) = (b & 1u) | (b & 2u) << 7 | (b & 4u) << 14 | (b & 8u) << 21;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < P; ++e)
+          if (d + e < D) dst[e] = (uint8_t)(bits >> e & 1u);
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int n = group * 32 + 8 * k + q;
+    int v = count[k];
+    v += __shfl_xor(v, 1);
+    v += __shfl_xor(v, 2);
+    v += __shfl_xor(v, 4);
+    if (i == 0 && n < N && v > 0) __hip_atomic_fetch_add(&changed[(size_t)n * CHG], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
 // Jacobi-GS (Algorithm 2), start of an iteration: every block's virtual sample starts from the previous
 // iterate: xv[i * np + n] = x[n] for all blocks i, and the network input of the virtual samples is rebuilt.
 template <typename T>
