@@ -20,7 +20,7 @@ constexpr int RNN_WAVES = 8;
 constexpr int RNN_MAX_H = 128;
 constexpr int RNN_TILES_PER_WAVE = 2;
 
-__device__ __forceinline__ float rnn_sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
+__device__ __forceinline__ float rnn_sigmoid_fast(float z);   // (with the recurrences, below)
 
 struct RnnJacobiArgs {
   const float* W;        // [H, H], W[i][j] multiplies h_{t-1}[j] in unit i
@@ -33,6 +33,7 @@ struct RnnJacobiArgs {
   int B, T, H;
   int cap;               // pass limit, 1 .. T
   float eps;
+  int x_bytes;           // distance of the second copy of X in LDS; 0: there is one
 };
 
 // fp32 value = hi + lo + O(2^-17 |value|), both parts bf16 (round to nearest even; gfx950 converts in hardware)
@@ -50,8 +51,14 @@ __device__ __forceinline__ void split_bf16(float v, bf16_t& hi, bf16_t& lo) {
 // Wave w owns column tile (32 units) w % CT for good: its two W panels (hi, lo) stay in registers, as do G,
 // sigmoid(z) and the current iterate of the (at most two) 32 x 32 tiles it owns.  The MFMA takes W^T as its row
 // operand, so a lane holds 4 runs of 4 consecutive units of ONE time step: inputs come in 16-byte loads and the
-// new X goes back to LDS in 8-byte pieces.  X lives in LDS as two bf16 arrays [time][unit] and is updated in
-// place: all waves read (MFMA phase), barrier, all waves write, barrier.
+// new X goes back to LDS in 8-byte pieces.  X lives in LDS as two bf16 arrays [time][unit], twice where it fits: a pass
+// reads one copy and writes the other, so that there is one barrier a pass and one wave's update runs beside the
+// other's products (they share a SIMD); with one copy all waves read, barrier, all waves write, barrier.
+// The stop test asks whether any element moved by more than eps (one ballot); the first pass from zeros has no product.
+// Bound by the two together: 48 MFMAs (0.64 us a wave, two to a SIMD) and ~450 other instructions a wave and pass.
+// H = 128, 100 steps, 10 passes: one sequence 44.9 -> 39.3 us, 256
+// 56 -> 49.9 us, of which about 12 us are the set-up.  Tried: every input requested at once ahead of the set-up (47.5 us),
+// a wave's two tiles multiplied in turn (47.4).
 template <int CT>
 __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_jacobi_kernel(RnnJacobiArgs a) {
   constexpr int Hp = 32 * CT;
@@ -59,11 +66,11 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_jacobi_kernel(RnnJacobiArg
   constexpr int LDX = Hp + 8;            // row pitch of X in bf16 elements (16 bytes of padding)
   constexpr int TW = RNN_TILES_PER_WAVE;
   extern __shared__ __align__(16) unsigned char rnn_lds[];
-  __shared__ unsigned diff_s[2];
+  __shared__ int moved_s[3];             // (pass k sets one, clears the next pass's, and may still read its own then)
   const int T = a.T, H = a.H;
   const int Tp = (T + 31) / 32 * 32, RT = Tp / 32;
-  bf16_t* Xhi = (bf16_t*)rnn_lds;
-  bf16_t* Xlo = Xhi + (size_t)Tp * LDX;
+  const int lo_off = Tp * LDX;                       // (elements) X's low parts behind its high ones
+  int x_read = 0, x_write = a.x_bytes / 2;           // (elements) the copy a pass reads, the one it writes
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int cl = lane & 31, hh = lane >> 5;
   const int seq = blockIdx.x;
@@ -121,61 +128,66 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_jacobi_kernel(RnnJacobiArg
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         G[i][4 * jj + e] = gv[e];
-        S[i][4 * jj + e] = (row_ok && u0 + e < H) ? rnn_sigmoid(zv[e]) : 0.0f;
+        S[i][4 * jj + e] = (row_ok && u0 + e < H) ? rnn_sigmoid_fast(zv[e]) : 0.0f;
         D[i][4 * jj + e] = dv[e];
       }
     }
   }
-  // X[t-1][unit .. unit+3] = S[t] * D[t], both bf16 parts, 8 bytes each
-  auto store_x = [&](int i, int jj) {
+  // X[t-1][unit .. unit+3] = S[t] * D[t], both bf16 parts (see split_bf16), 8 bytes each
+  auto store_x = [&](int copy, int i, int jj) {
     const int t = 32 * (q + i * nq) + cl;
     if (t >= 1 && t < T) {
-      bf16_t h4[4], l4[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) split_bf16(S[i][4 * jj + e] * D[i][4 * jj + e], h4[e], l4[e]);
-      const int off = (t - 1) * LDX + 32 * c + 8 * jj + 4 * hh;
-      *(uint2*)(Xhi + off) = make_uint2(h4[0] | (h4[1] << 16), h4[2] | (h4[3] << 16));
-      *(uint2*)(Xlo + off) = make_uint2(l4[0] | (l4[1] << 16), l4[2] | (l4[3] << 16));
+      typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+      typedef float f32x4_t __attribute__((ext_vector_type(4)));
+      const f32x4_t v = {S[i][4 * jj] * D[i][4 * jj], S[i][4 * jj + 1] * D[i][4 * jj + 1], S[i][4 * jj + 2] * D[i][4 * jj + 2],
+                         S[i][4 * jj + 3] * D[i][4 * jj + 3]};
+      const bf16x4_t hi = __builtin_convertvector(v, bf16x4_t);
+      const bf16x4_t lo = __builtin_convertvector(v - __builtin_convertvector(hi, f32x4_t), bf16x4_t);
+      bf16_t* x = (bf16_t*)rnn_lds + copy + (t - 1) * LDX + 32 * c + 8 * jj + 4 * hh;
+      *(bf16x4_t*)x = hi;
+      *(bf16x4_t*)(x + lo_off) = lo;
     }
   };
 
-  for (int i = threadIdx.x; i < Tp * LDX / 2; i += RNN_WAVES * 64) ((unsigned*)rnn_lds)[i] = 0u, ((unsigned*)Xlo)[i] = 0u;
-  if (threadIdx.x < 2) diff_s[threadIdx.x] = 0u;
+  for (int i = threadIdx.x; i < (4 * lo_off + a.x_bytes) / 16; i += RNN_WAVES * 64) ((uint4*)rnn_lds)[i] = make_uint4(0, 0, 0, 0);
+  if (threadIdx.x < 3) moved_s[threadIdx.x] = 0;
   __syncthreads();
   if (a.d_init) {
 #pragma unroll
     for (int i = 0; i < TW; ++i)
       if (tile_ok[i]) {
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) store_x(i, jj);
+        for (int jj = 0; jj < 4; ++jj) store_x(x_read, i, jj);
       }
   }
   __syncthreads();
 
-  int k = 0, conv = 0;
+  int k = 0, conv = 0, slot = 0;
   while (k < a.cap) {
     ++k;
-    // ---- MFMA phase: acc^T = W^T X^T for the wave's tiles
+    const int next_slot = slot == 2 ? 0 : slot + 1;
+    // ---- acc^T = W^T X^T for the wave's tiles
     f32x16 acc[TW];
+    const bool product = k > 1 || a.d_init;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][e] = 0.0f;
-      if (tile_ok[i]) {
-        const int xoff = (32 * (q + i * nq) + cl) * LDX + hh * (Hp / 2);
+      if (tile_ok[i] && product) {
+        const bf16_t* x = (const bf16_t*)rnn_lds + x_read + (32 * (q + i * nq) + cl) * LDX + hh * (Hp / 2);
 #pragma unroll
         for (int m = 0; m < KB; ++m) {
-          const bf16x8 xh = __builtin_bit_cast(bf16x8, *(const uint4*)(Xhi + xoff + 8 * m));
-          const bf16x8 xl = __builtin_bit_cast(bf16x8, *(const uint4*)(Xlo + xoff + 8 * m));
+          const bf16x8 xh = __builtin_bit_cast(bf16x8, *(const uint4*)(x + 8 * m));
+          const bf16x8 xl = __builtin_bit_cast(bf16x8, *(const uint4*)(x + lo_off + 8 * m));
           acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, whi[m]), xl, acc[i], 0, 0, 0);
           acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wlo[m]), xh, acc[i], 0, 0, 0);
           acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, whi[m]), xh, acc[i], 0, 0, 0);
         }
       }
     }
-    __syncthreads();   // every wave has read the old X
-    // ---- update phase: D = G + acc, forward difference, X[t-1] = S[t] * D[t]
-    float diff = 0.0f;
+    if (!a.x_bytes) __syncthreads();   // (uniform) every wave has read the old X
+    // ---- D = G + acc, forward difference, X[t-1] = S[t] * D[t]
+    bool moved = false;
 #pragma unroll
     for (int i = 0; i < TW; ++i) {
       if (tile_ok[i]) {
@@ -184,23 +196,24 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_jacobi_kernel(RnnJacobiArg
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const float dn = G[i][4 * jj + e] + acc[i][4 * jj + e];
-            const float df = fabsf(dn - D[i][4 * jj + e]);
-            diff = fmaxf(diff, df == df ? df : __builtin_inff());       // (a NaN never counts as converged)
+            moved |= !(fabsf(dn - D[i][4 * jj + e]) <= a.eps);          // (a NaN never counts as converged)
             D[i][4 * jj + e] = dn;
           }
-          store_x(i, jj);
+          store_x(x_write, i, jj);
         }
       }
     }
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) diff = fmaxf(diff, __shfl_xor(diff, s));
-    if (lane == 0) atomicMax(&diff_s[k & 1], __float_as_uint(diff));   // (non-negative floats order like their bits)
-    if (threadIdx.x == 0) diff_s[(k + 1) & 1] = 0u;                    // the slot of the pass after this one
-    __syncthreads();
-    if (__uint_as_float(diff_s[k & 1]) <= a.eps) {
+    if (__any(moved) && lane == 0) moved_s[slot] = 1;
+    if (threadIdx.x == 0) moved_s[next_slot] = 0;
+    lds_barrier();
+    if (!moved_s[slot]) {
       conv = 1;
       break;
     }
+    slot = next_slot;
+    const int other = x_read;
+    x_read = x_write;
+    x_write = other;
   }
 
 #pragma unroll
@@ -476,11 +489,11 @@ __global__ __launch_bounds__(RnnStep<CT>::THREADS) void rnn_forward_kernel(const
 // in chunks of 64 rows that go through LDS, the next chunk's loads in flight (registers) while this one is multiplied
 // with fp32 MFMA; wave w takes column tile w % CT and every (8 / CT)-th part of the chunk's rows.  dU and db ride
 // along on the vector units from the same p (slot 0 of the eight columns of blockIdx.z = 0 is db, the rest inputs).
-// Bound by fp32 MFMA (256 flop per clock and unit) once every compute unit has a slice.  With one slice the results
+// Two workgroups to a compute unit fill each other's waits for a chunk.  With one slice the results
 // are stored; with several every slice's sums go to a piece of static device memory and a kernel of its own adds them
 // in slice order, so that two calls give the same bits.
-// H = 128, 100 steps: 256 sequences 33 us in all (28.7 us for the product, 29 TFLOP/s, 4 us for the addition, 1.4 us for
-// taking a piece; 30 us when the slices were added by fp32 atomics in order of completion), one sequence 8.8 us; with a
+// H = 128, 100 steps: 256 sequences 27.2 us for the product (29.7 with one workgroup to a compute unit and the library's
+// exponential), 4.6 us for the addition, 4 us for taking a piece (in all, before: 33 us; 30 us when the slices were added by fp32 atomics in order of completion), one sequence 8.8 us; with a
 // workgroup per 32 x 32 tile of dW over all rows (16 workgroups, loads waited for one by one) 2900 us and 11.8 us.
 constexpr int GRAD_ROWS = 64;         // rows per chunk
 constexpr int GRAD_SLOTS = 8;         // columns of [1, x] per blockIdx.z
@@ -491,7 +504,7 @@ constexpr int GRAD_SLOTS = 8;         // columns of [1, x] per blockIdx.z
 // free adds its slices in one workgroup per strip instead: the same sums in the same order, without the spread over
 // the chip.
 constexpr int GRAD_PIECES = 4;
-constexpr long long GRAD_PIECE_FLOATS = 5 << 18;       // 5 MiB: 64 slices of H = 128, I up to 28
+constexpr long long GRAD_PIECE_FLOATS = 10 << 18;      // 10 MiB: 128 slices of H = 128, I up to 28
 __device__ float g_grad_piece[GRAD_PIECES][GRAD_PIECE_FLOATS];
 constexpr int GRAD_KEY_SHIFT = 16;
 // 0 = free, else the key of the call that holds the piece << GRAD_KEY_SHIFT + workgroups of its adding kernel that are
@@ -558,8 +571,9 @@ __global__ __launch_bounds__(64 * GRAD_GROUPS) void rnn_grads_add_kernel(unsigne
   }
 }
 
+// (second launch bound: waves per SIMD, i.e. two workgroups to a compute unit)
 template <int CT>
-__global__ __launch_bounds__(RNN_WAVES * 64) void rnn_param_grads_kernel(const float* z, const float* h, const float* x, const float* d,
+__global__ __launch_bounds__(RNN_WAVES * 64, 4) void rnn_param_grads_kernel(const float* z, const float* h, const float* x, const float* d,
                                                                          const float* h0, long long rows, int T, int H, int I,
                                                                          int slice_rows, int slices, unsigned long long key,
                                                                          float* dW, float* dU, float* db) {
@@ -659,13 +673,13 @@ __global__ __launch_bounds__(RNN_WAVES * 64) void rnn_param_grads_kernel(const f
           *(float4*)(Hs + (e / Hp) * LDH + e % Hp) = hv[k];
         }
       }
-      *(float4*)(Ps + tid * 4) = make_float4(rnn_sigmoid(zv.x) * dv.x, rnn_sigmoid(zv.y) * dv.y, rnn_sigmoid(zv.z) * dv.z,
-                                             rnn_sigmoid(zv.w) * dv.w);
+      *(float4*)(Ps + tid * 4) = make_float4(rnn_sigmoid_fast(zv.x) * dv.x, rnn_sigmoid_fast(zv.y) * dv.y,
+                                             rnn_sigmoid_fast(zv.z) * dv.z, rnn_sigmoid_fast(zv.w) * dv.w);
       Xs[tid] = xv;
       __syncthreads();
       if (c + 1 < n_chunks) request(c + 1);
       if (gemm && q < NQ) {
-#pragma unroll
+#pragma unroll 4
         for (int m = 0; m < GRAD_ROWS / NQ; m += 2) {
           const int k = q * (GRAD_ROWS / NQ) + m + hh;
           acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Ps[k * 32 + cl], Hs[k * LDH + 32 * tj + cl], acc, 0, 0, 0);

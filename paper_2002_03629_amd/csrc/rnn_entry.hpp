@@ -91,7 +91,10 @@ extern "C" int rnn_backward_jacobi(const float* W, const float* z, const float* 
   a.cap = (n_iters <= 0 || n_iters > T) ? T : n_iters;
   a.eps = eps;
   const int CT = (H + 31) / 32, Tp = round_up(T, 32);
-  const size_t lds = (size_t)2 * Tp * (32 * CT + 8) * sizeof(uint16_t);
+  // (a second copy of X where LDS holds it: every shape but more than 480 steps of up to 32 units)
+  const size_t one = (size_t)2 * Tp * (32 * CT + 8) * sizeof(uint16_t);
+  a.x_bytes = 2 * one <= 160 * 1024 - 256 ? (int)one : 0;
+  const size_t lds = one + a.x_bytes;
   hipStream_t s = (hipStream_t)stream;
   switch (CT) {
     case 1: return rnn_launch_jacobi<1>(a, lds, s);
@@ -108,10 +111,10 @@ extern "C" int rnn_param_grads(const float* z, const float* h, const float* x, c
   if (!z || !h || !x || !d || !dW || !dU || !db) return fail(MADE_ERR_ARG, "rnn_param_grads: NULL argument");
   const int CT = (H + 31) / 32;
   const long long rows = (long long)B * T, chunks = (rows + GRAD_ROWS - 1) / GRAD_ROWS;
-  // One slice (results stored at once) for up to GRAD_ONE_SLICE chunks, else as many as give every compute unit a
-  // workgroup and fit a piece.
+  // One slice (results stored at once) for up to GRAD_ONE_SLICE chunks, else as many as give every compute unit two
+  // workgroups and fit a piece.
   const long long stride = grad_stride(H, I);
-  long long slices = chunks <= GRAD_ONE_SLICE ? 1 : std::min<long long>(chunks, 256 / CT);
+  long long slices = chunks <= GRAD_ONE_SLICE ? 1 : std::min<long long>(chunks, 512 / CT);
   slices = std::max<long long>(1, std::min(slices, GRAD_PIECE_FLOATS / stride));
   const long long slice_rows = std::max<long long>(1, (chunks + slices - 1) / slices * GRAD_ROWS);
   slices = std::max<long long>(1, (rows + slice_rows - 1) / slice_rows);
