@@ -208,13 +208,17 @@ struct ColProducer {
   static constexpr int pitch(int l) { return l < L ? COL_UNITS : COL_POS; }
   static constexpr int inputs(int l) { return l == 0 ? COL_POS : COL_UNITS; }
   static constexpr int pieces(int l) { return ((l == 0 ? COL_POS : COL_UNITS) + P - 2) / P + 1; }
-  static constexpr int stage_loads(int l) { return (pieces(l) + COL_PRODUCERS - 1) / COL_PRODUCERS; }
-  static constexpr int STAGE = stage_loads(1);                                    // (the most of a layer)
-  static_assert(stage_loads(0) <= STAGE && stage_loads(L) <= STAGE, "room for the staged pieces");
+  // staging: the first waves serve layer 0, which has half the pieces, the others a layer each (L = 1: 2 and 6 of them, L = 2: 2, 3
+  // and 3, L = 3: 2 each)
+  static constexpr int stage_first(int l) { return l == 0 ? 0 : 2 + (COL_PRODUCERS - 2) * (l - 1) / L; }
+  static constexpr int stage_waves(int l) { return stage_first(l + 1) - stage_first(l); }
+  static constexpr int stage_loads(int l) { return (pieces(l) + stage_waves(l) - 1) / stage_waves(l); }
+  static constexpr int most(int a, int b) { return a > b ? a : b; }
+  static constexpr int STAGE = most(stage_loads(0), most(stage_loads(1), stage_loads(L)));
 
   f32x4 acc[L + 1][4];
   uint4 late_w[L + 1][4];
-  uint4 staged[L + 1][STAGE];
+  uint4 staged[STAGE];
 
   static __device__ __forceinline__ int steps_before(int k0) {     // steps that hold the columns below k0
     const int rem = k0 % KC;
@@ -327,17 +331,21 @@ struct ColProducer {
     });
   }
 
+  // (which late step of a layer is a wave's: the layers' steps, up to four in bf16, lie beside one another)
+  static __device__ __forceinline__ int late_step(int l, int pw) { return (pw - 3 * l) & (COL_PRODUCERS - 1); }
   // The rest of the inputs before block b, those that block `cur` makes final: requested ahead of the barrier ...
   __device__ __forceinline__ void late_request(const ColumnArgs& p, const ColBlock<L>& b, const ColBlock<L>& cur, int pw) {
     static_for<L + 1>([&](auto LL) {
       constexpr int l = LL;
-      const int first = steps_whole(cur.k0(l)), last = steps_before(b.k0(l)) - 1;
+      const int j = steps_whole(cur.k0(l)) + late_step(l, pw);
       static_for<tiles(l)>([&](auto TT) { late_w[l][TT] = make_uint4(0, 0, 0, 0); });   // (or the old values would count as live)
-      if (b.rows(l) > 0 && last >= first) {
+      if (b.rows(l) > 0 && j < steps_before(b.k0(l))) {
         static_for<tiles(l)>([&](auto TT) {
           constexpr int t = TT;
-          const uint32_t wp = row_pieces(p.k_chunks[l], b.row0(l) + min(16 * t + (int)(threadIdx.x & 15), b.rows(l) - 1));
-          late_w[l][t] = *(const uint4*)((const unsigned char*)p.W[l] + (size_t)min(first + pw, last) * 2048 + wp);
+          if (16 * t < b.rows(l)) {
+            const uint32_t wp = row_pieces(p.k_chunks[l], b.row0(l) + min(16 * t + (int)(threadIdx.x & 15), b.rows(l) - 1));
+            late_w[l][t] = *(const uint4*)((const unsigned char*)p.W[l] + (size_t)j * 2048 + wp);
+          }
         });
       }
     });
@@ -347,7 +355,7 @@ struct ColProducer {
                                                float* red, int pw) {
     static_for<L + 1>([&](auto LL) {
       constexpr int l = LL;
-      const int j = steps_whole(cur.k0(l)) + pw, end = steps_before(b.k0(l));
+      const int j = steps_whole(cur.k0(l)) + late_step(l, pw), end = steps_before(b.k0(l));
       if (b.rows(l) > 0 && j < end) {
         const uint4 x = act_piece(lds + p.lds_act[l], j);
         static_for<tiles(l)>([&](auto TT) { acc[l][TT] = col_mfma(late_w[l][TT], x, acc[l][TT], T{}); });
@@ -364,37 +372,34 @@ struct ColProducer {
   }
 
   // The weights between block b's own units and positions: requested, and written to LDS as ColStage has them.  A wave takes
-  // whole pieces, a lane a row (rows past the last repeat it).
-  __device__ __forceinline__ void stage_request(const ColumnArgs& p, const ColBlock<L>& b, int pw) {
-    const int lane = threadIdx.x & 63;
+  // whole pieces of one layer, a lane a row (rows past the last repeat it).
+  template <typename F>
+  __device__ __forceinline__ void stage_each(const ColBlock<L>& b, int pw, F&& piece_of) {
     static_for<L + 1>([&](auto LL) {
       constexpr int l = LL;
-      const int p0 = b.k0(l) / P, p1 = (b.k0(l) + b.n_k(l) + P - 1) / P;
-      const int g = b.row0(l) + min(lane, max(b.rows(l) - 1, 0));
+      if (pw < stage_first(l) || pw >= stage_first(l + 1) || b.rows(l) == 0) return;
+      const int p0 = b.k0(l) / P + pw - stage_first(l), p1 = (b.k0(l) + b.n_k(l) + P - 1) / P;
+      static_for<stage_loads(l)>([&](auto I) {
+        if (p0 + I * stage_waves(l) < p1) piece_of(LL, I, p0 + I * stage_waves(l));
+      });
+    });
+  }
+  __device__ __forceinline__ void stage_request(const ColumnArgs& p, const ColBlock<L>& b, int pw) {
+    static_for<STAGE>([&](auto I) { staged[I] = make_uint4(0, 0, 0, 0); });
+    stage_each(b, pw, [&](auto LL, auto I, int piece) {
+      constexpr int l = LL;
+      const int g = b.row0(l) + min((int)(threadIdx.x & 63), b.rows(l) - 1);
       const uint32_t row = (uint32_t)(g >> 5) * (uint32_t)p.k_chunks[l] * 4096u + (uint32_t)(g & 31) * 16u;
-#pragma unroll
-      for (int i = 0; i < stage_loads(l); ++i) {
-        staged[l][i] = make_uint4(0, 0, 0, 0);
-        const int piece = p0 + pw + i * COL_PRODUCERS;
-        if (piece < p1 && b.rows(l) > 0) {
-          const int k = piece * P, c = k / KC, kk = k % KC, h = kk / EPL, s = (kk % EPL) / P;
-          staged[l][i] = *(const uint4*)((const unsigned char*)p.W[l] + ((size_t)c * 4096 + (s * 2 + h) * 512) + row);
-        }
-      }
+      const int k = piece * P, c = k / KC, kk = k % KC, h = kk / EPL, s = (kk % EPL) / P;
+      staged[I] = *(const uint4*)((const unsigned char*)p.W[l] + ((size_t)c * 4096 + (s * 2 + h) * 512) + row);
     });
   }
   __device__ __forceinline__ void stage_store(const ColumnArgs& p, unsigned char* lds, const ColBlock<L>& b, int buffer, int pw) {
     const int lane = threadIdx.x & 63;
-    static_for<L + 1>([&](auto LL) {
+    stage_each(b, pw, [&](auto LL, auto I, int piece) {
       constexpr int l = LL;
-      unsigned char* ws = lds + p.lds_w[l] + buffer * p.lds_w_bytes;
-      const int p0 = b.k0(l) / P, p1 = (b.k0(l) + b.n_k(l) + P - 1) / P;
-#pragma unroll
-      for (int i = 0; i < stage_loads(l); ++i) {
-        const int piece = p0 + pw + i * COL_PRODUCERS;
-        if (piece < p1 && b.rows(l) > 0 && (pitch(l) == 64 || lane < pitch(l)))
-          ColStage<T, SEQ>::store(ws, inputs(l), pitch(l), b.k0(l), piece * P, lane, staged[l][i]);
-      }
+      if (pitch(l) == 64 || lane < pitch(l))
+        ColStage<T, SEQ>::store(lds + p.lds_w[l] + buffer * p.lds_w_bytes, inputs(l), pitch(l), b.k0(l), piece * P, lane, staged[I]);
     });
   }
 };
