@@ -1454,6 +1454,13 @@ static int cat_any_positions(int C, int n_pos, int pair_tiles) {
 }
 
 // Output layer + draw for positions [t_lo, t_hi).  whole = evaluate every output tile regardless.
+// 256 classes: a workgroup has eight waves where a launch has more than one workgroup to a compute unit and not more than two, and
+// at least 16 K chunks to a row.  us a call with four and eight waves: 512 positions, 1000 units, batch 1 / 64 (512 workgroups, 16
+// chunks) 185 / 391 and 170 / 359; 400 / 1500, batch 64 381 and 355; 512 / 500 fp32, batch 64 598 and 489; 200 / 600 fp32, batch 128 (400)
+// 551 and 433; 300 / 1000, batch 64 287 and 281.  Elsewhere the larger workgroup costs more than it hides: 200 / 500, batch 64 / 128 (8
+// chunks) 148 / 187 and 156 / 197; 200 / 2 x 1500, batch 64 (200 workgroups) 180 and 193; 128 / 2 x 1000, batch 128 (256) 188 and 196; 512 /
+// 1000, batch 128 (1024 workgroups) keeps four waves.
+static bool cat_eight_waves(int workgroups, int k_chunks) { return workgroups > 256 && workgroups <= 512 && k_chunks >= 16; }
 static int run_output_sample(made_model* m, const RowSet& rs, const SampleIO& io, bool whole, int k_limit,
                              hipStream_t s, bool by_pos = false, const PartialSums* ps = nullptr) {
   const Layer& ly = m->layers[m->L];
@@ -1544,10 +1551,16 @@ static int run_output_sample(made_model* m, const RowSet& rs, const SampleIO& io
         hipLaunchKernelGGL((categorical_any_kernel<bf16_t>), grid, dim3(CAT_ANY_WAVES * 64), 0, s, ca);
       else
         hipLaunchKernelGGL((categorical_any_kernel<float>), grid, dim3(CAT_ANY_WAVES * 64), 0, s, ca);
-    } else if (m->dtype == MADE_BF16)
-      hipLaunchKernelGGL((categorical_output_kernel<bf16_t>), dim3(c.n_pos * c.pair_tiles), dim3(CAT_WAVES * 64), 0, s, c);
-    else
-      hipLaunchKernelGGL((categorical_output_kernel<float>), dim3(c.n_pos * c.pair_tiles), dim3(CAT_WAVES * 64), 0, s, c);
+    } else {
+      const auto draw = [&](auto t) {
+        using T = decltype(t);
+        const dim3 grid(c.n_pos * c.pair_tiles);
+        if (cat_eight_waves((int)grid.x, c.k_chunks)) hipLaunchKernelGGL((categorical_output_kernel<T, 1>), grid, dim3(512), 0, s, c);
+        else hipLaunchKernelGGL((categorical_output_kernel<T, 2>), grid, dim3(256), 0, s, c);
+      };
+      if (m->dtype == MADE_BF16) draw(bf16_t());
+      else draw(float());
+    }
     prof_mark(m, m->L, true, s);
     m->stats[2]++;
   } else {

@@ -1736,7 +1736,6 @@ __global__ __launch_bounds__(NW * 64, 4) void xcd_sampler_kernel(PersistArgs p) 
 // the longest visible prefix are scheduled first.
 // ------------------------------------------------------------------------------------------------
 constexpr int CAT_C = 256;
-constexpr int CAT_WAVES = 4;
 constexpr int CAT_PD = 2;
 
 struct CatArgs {
@@ -1767,17 +1766,16 @@ struct CatArgs {
   RetireArgs retire;
 };
 
-template <typename T, int CNT, bool TWO>
-__device__ __forceinline__ void cat_group(const uint4* W0, const uint4* W1, const uint4* A0, const uint4* A1, int c0,
-                                          f32x16 (&acc)[2][2]) {
-  uint4 w0[CNT][4], w1[CNT][4], a0[CNT][4], a1[CNT][4];
+template <typename T, int CNT, bool TWO, int Q>
+__device__ __forceinline__ void cat_group(const uint4* (&W)[Q], const uint4* A0, const uint4* A1, int c0, f32x16 (&acc)[Q][2]) {
+  uint4 w[Q][CNT][4], a0[CNT][4], a1[CNT][4];
 #pragma unroll
   for (int p = 0; p < CNT; ++p) {
     const size_t o = (size_t)(c0 + p) * 256;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      w0[p][s] = load_stream16(W0 + o + s * 64);
-      w1[p][s] = load_stream16(W1 + o + s * 64);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) w[q][p][s] = load_stream16(W[q] + o + s * 64);
       a0[p][s] = A0[o + s * 64];
       if (TWO) a1[p][s] = A1[o + s * 64];
     }
@@ -1785,29 +1783,31 @@ __device__ __forceinline__ void cat_group(const uint4* W0, const uint4* W1, cons
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int p = 0; p < CNT; ++p) {
-    mfma_chunk<T>(w0[p], a0[p], acc[0][0]);
-    mfma_chunk<T>(w1[p], a0[p], acc[1][0]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) mfma_chunk<T>(w[q][p], a0[p], acc[q][0]);
     if (TWO) {
-      mfma_chunk<T>(w0[p], a1[p], acc[0][1]);
-      mfma_chunk<T>(w1[p], a1[p], acc[1][1]);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) mfma_chunk<T>(w[q][p], a1[p], acc[q][1]);
     }
   }
 }
 
-template <typename T, bool TWO>
-__device__ __forceinline__ void cat_stream(const uint4* W0, const uint4* W1, const uint4* A0, const uint4* A1,
-                                           int n_chunks, f32x16 (&acc)[2][2]) {
+template <typename T, bool TWO, int Q>
+__device__ __forceinline__ void cat_stream(const uint4* (&W)[Q], const uint4* A0, const uint4* A1, int n_chunks, f32x16 (&acc)[Q][2]) {
   int c = 0;
-  for (; c + CAT_PD <= n_chunks; c += CAT_PD) cat_group<T, CAT_PD, TWO>(W0, W1, A0, A1, c, acc);
-  if (c < n_chunks) cat_group<T, 1, TWO>(W0, W1, A0, A1, c, acc);
+  for (; c + CAT_PD <= n_chunks; c += CAT_PD) cat_group<T, CAT_PD, TWO, Q>(W, A0, A1, c, acc);
+  if (c < n_chunks) cat_group<T, 1, TWO, Q>(W, A0, A1, c, acc);
 }
 
-template <typename T>
-__global__ __launch_bounds__(CAT_WAVES * 64) void categorical_output_kernel(CatArgs a) {
+// Q: 32-class tiles of a wave; 8 / Q waves.  Two read the activations half as often; with one a workgroup has twice the loads in
+// flight, which pays where compute units have about two of them and no third one waits (see cat_eight_waves).  Same sums.
+template <typename T, int Q>
+__global__ __launch_bounds__(CAT_C / TILE / Q * 64) void categorical_output_kernel(CatArgs a) {
+  constexpr int WAVES = CAT_C / TILE / Q;
   static_assert(CAT_PD == 2, "the remainder handling assumes a prefetch depth of 2");
   constexpr int KC = 2 * Elem<T>::EPL;
-  __shared__ float sm_val[CAT_WAVES][64];
-  __shared__ int sm_idx[CAT_WAVES][64];
+  __shared__ float sm_val[WAVES][64];
+  __shared__ int sm_idx[WAVES][64];
   const int n_rows = a.n_rows_ptr ? *a.n_rows_ptr : a.n_rows;
   const int t_first = a.t_first_ptr ? *a.t_first_ptr : 0;
   const int pos_i = blockIdx.x / a.pair_tiles, pair = blockIdx.x % a.pair_tiles;
@@ -1823,24 +1823,25 @@ __global__ __launch_bounds__(CAT_WAVES * 64) void categorical_output_kernel(CatA
     if (k_end > a.k_cap) k_end = a.k_cap;
     const int n_chunks = (k_end + KC - 1) / KC;
     const size_t group = (size_t)a.k_chunks * 256;
-    const uint4* W0 = (const uint4*)a.W + (size_t)(t * (CAT_C / TILE) + wave * 2) * group + h * 32 + r;
-    const uint4* W1 = W0 + group;
+    const uint4* W[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) W[q] = (const uint4*)a.W + (size_t)(t * (CAT_C / TILE) + wave * Q + q) * group + h * 32 + r;
     const uint4* A0 = (const uint4*)a.A + (size_t)(n0 >> 5) * group + h * 32 + (n0 & 31);
     const uint4* A1 = (const uint4*)a.A + (size_t)(n1 >> 5) * group + h * 32 + (n1 & 31);
 
-    f32x16 acc[2][2];
+    f32x16 acc[Q][2];
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+    for (int q = 0; q < Q; ++q)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[q][j][i] = 0.f;
     if (two)
-      cat_stream<T, true>(W0, W1, A0, A1, n_chunks, acc);
+      cat_stream<T, true, Q>(W, A0, A1, n_chunks, acc);
     else
-      cat_stream<T, false>(W0, W1, A0, A1, n_chunks, acc);
+      cat_stream<T, false, Q>(W, A0, A1, n_chunks, acc);
 
-    // acc[q][j][i]: class (wave*2 + q)*32 + 8*(i/4) + 4*h + i%4 of sample tile j's row r
+    // acc[q][j][i]: class (wave*Q + q)*32 + 8*(i/4) + 4*h + i%4 of sample tile j's row r
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if (j == 0 || two) {
@@ -1850,10 +1851,10 @@ __global__ __launch_bounds__(CAT_WAVES * 64) void categorical_output_kernel(CatA
         float best = -INFINITY;
         int best_c = 0x7fffffff;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int q = 0; q < Q; ++q) {
 #pragma unroll
           for (int i4 = 0; i4 < 4; ++i4) {
-            const int cb = (wave * 2 + q) * 32 + 8 * i4 + 4 * h;
+            const int cb = (wave * Q + q) * 32 + 8 * i4 + 4 * h;
             const float4 gv = *(const float4*)(gp + cb);
             const float4 bv = *(const float4*)(bp + cb);
             const float v0 = (acc[q][j][i4 * 4 + 0] + bv.x) + gv.x;
@@ -1886,7 +1887,7 @@ __global__ __launch_bounds__(CAT_WAVES * 64) void categorical_output_kernel(CatA
         float best = sm_val[0][sl];
         int best_c = sm_idx[0][sl];
 #pragma unroll
-        for (int w = 1; w < CAT_WAVES; ++w)
+        for (int w = 1; w < WAVES; ++w)
           if (sm_val[w][sl] > best) { best = sm_val[w][sl]; best_c = sm_idx[w][sl]; }   // waves hold increasing classes
         sample = a.rows ? a.rows[row0 + sl] : row0 + sl;
         const size_t idx = (size_t)sample * a.D + t;
