@@ -518,7 +518,7 @@ def run_one(args, torch, B, S, light=False):
                       f"conv_layer_kernel (k x k masked convolution as implicit GEMM, all {n_layers - 2} such layers)"
                       if dom < n_layers - 1 else "conv_head_kernel (1 x 1 head + Gumbel-max)")
     elif dom == n_layers:
-        layer_name = ("persistent_sampler_kernel" if args.path == "persistent" else "xcd_sampler_kernel") + \
+        layer_name = ("persistent_sampler_kernel" if args.path == "persistent" else "xcd_pass_kernel / xcd_sampler_kernel") + \
                      " (all passes of a call in one launch: hidden layers, output layer + sampling, stop test)"
     else:
         if dom == n_layers - 1 and w.C == 256:
