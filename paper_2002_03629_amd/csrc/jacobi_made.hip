@@ -359,6 +359,11 @@ static int settle(made_model* m, hipStream_t s) {
   return MADE_OK;
 }
 
+// Waits for clears of fresh memory.  hipMemset runs on the null stream and may return before it is done, and a
+// caller's non-blocking stream is not ordered after it: on a busy GPU (calls of other models on other streams) a
+// clear could land after the call's own kernels had written their lists.  Only calls that allocate wait.
+static hipError_t settle_clears() { return hipStreamSynchronize(nullptr); }
+
 static int ensure_workspace(made_model* m, int N, bool need_z) {
   Workspace& w = m->ws;
   if (w.pending && (N > w.N_cap || (need_z && m->C > 1 && !w.zbuf))) {   // about to free memory queued kernels may use
@@ -391,6 +396,7 @@ static int ensure_workspace(made_model* m, int N, bool need_z) {
     HIP_TRY(hipMalloc((void**)&w.iters, (size_t)n_pad * sizeof(int)));
     HIP_TRY(hipMalloc((void**)&w.flags, sizeof(int)));
     HIP_TRY(hipHostMalloc((void**)&w.h_pin, 8 * sizeof(int), hipHostMallocDefault));
+    HIP_TRY(settle_clears());
     w.N_cap = cap;
     return MADE_OK;
   }
@@ -438,6 +444,7 @@ static int ensure_workspace(made_model* m, int N, bool need_z) {
   HIP_TRY(hipMalloc((void**)&w.flags, sizeof(int)));
   HIP_TRY(hipMemset(w.flags, 0, sizeof(int)));
   HIP_TRY(hipHostMalloc((void**)&w.h_pin, (8 + 4 * XCDS) * sizeof(int), hipHostMallocDefault));
+  HIP_TRY(settle_clears());
   w.N_cap = cap;
   return MADE_OK;
 }
@@ -468,6 +475,7 @@ static int ensure_chain(made_model* m, size_t i, int rows_cap, int pin_len) {
   // (second half: per pass, the first position the NEXT pass evaluates -- see CatArgs::t_first_ptr)
   HIP_TRY(hipHostMalloc((void**)&c.h_pin, (size_t)2 * pin_len * sizeof(int), hipHostMallocMapped));
   HIP_TRY(hipHostGetDevicePointer((void**)&c.d_pin, (void*)c.h_pin, 0));
+  HIP_TRY(settle_clears());
   c.rows_cap = rows_cap;
   c.pin_len = pin_len;
   return MADE_OK;
@@ -729,6 +737,7 @@ static void plan_column(made_model* m) {
   if (e == hipSuccess) e = hipMemset(m->col_ctr, 0, 4 * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMalloc((void**)&m->col_block_passes, D * sizeof(int));
   if (e == hipSuccess) e = hipMemset(m->col_block_passes, 0, D * sizeof(int));
+  if (e == hipSuccess) e = settle_clears();
   if (e == hipSuccess) e = hipHostMalloc((void**)&m->col_host, 4 * sizeof(unsigned long long), hipHostMallocDefault);
   if (e == hipSuccess) memset((void*)m->col_host, 0, 4 * sizeof(unsigned long long));
   if (e == hipSuccess && bounds.back() == D) {
@@ -980,6 +989,7 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
                : hipFuncSetAttribute((const void*)resident_sampler_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize, off);
       if (le == hipSuccess) le = hipMalloc((void**)&m->res_ctr, 4 * sizeof(unsigned long long));
       if (le == hipSuccess) le = hipMemset(m->res_ctr, 0, 4 * sizeof(unsigned long long));
+      if (le == hipSuccess) le = settle_clears();
       if (le == hipSuccess) le = hipHostMalloc((void**)&m->res_host, 4 * sizeof(unsigned long long), hipHostMallocDefault);
       if (le == hipSuccess) m->res_lds_bytes = off;
     }
@@ -2003,6 +2013,7 @@ static int fill_partial_sums(made_model* m, const RowSet& rs, const Block& blk, 
     if (!w.zero_bias) {
       HIP_TRY(hipMalloc((void**)&w.zero_bias, (size_t)widest * sizeof(float)));
       HIP_TRY(hipMemset(w.zero_bias, 0, (size_t)widest * sizeof(float)));
+      HIP_TRY(settle_clears());
     }
     w.partial_cap = w.n_pad;
   }
