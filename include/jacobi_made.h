@@ -246,8 +246,8 @@ int gs_jacobi_sample_real(made_model* m, const float* noise, int32_t N, const fl
  *   out[3] host waits on the device
  *   out[4] convolutional model: image rows recomputed by the k x k layers, summed over passes and images (a pass
  *          only recomputes the rows below the first symbol that changed in the pass before); 0 otherwise
- *   out[5] passes whose stop test had no tail (MADE_OPT_LAZY_STOP_TEST: the next pass derived its list itself; real states in
- *          one launch, see MADE_OPT_XCD_RESIDENT: all but the last allowed pass)
+ *   out[5] per-layer launches: passes whose stop test had no tail (MADE_OPT_LAZY_STOP_TEST: the next pass derived its list
+ *          itself); 0 for a call in one launch, which makes no list
  *   out[6] jacobi_sample of a 256-class model: visible output-layer weights the call's passes multiplied per sample
  *          (a pass skips the positions below the first one its predecessor changed: MADE_OPT_FROZEN_POSITIONS);
  *          0 otherwise
@@ -299,7 +299,7 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   Same results and pass counts.  The model keeps the 128 most recently used recordings; a
  *   change of any option or of the workspace size discards them.  The caller must not capture such a call itself.
  *   MADE_OPT_XCD_RESIDENT (default 1; 0, 1 or 2): jacobi_sample / gs_jacobi_sample of Bernoulli models, and jacobi_sample_real
- *   on up to 256 samples (one chain, MADE_OPT_LAZY_STOP_TEST = 1, more than one allowed pass), in ONE launch in
+ *   on up to 256 samples (one chain), in ONE launch in
  *   which every XCD (a group of compute units with an L2 of its own) iterates its own eighth of the samples through
  *   all passes, synchronising only among its own workgroups and through its own L2 -- samples are independent
  *   systems, so nothing has to cross the chip.  0 = never; 1 = where it was measured faster than one launch per layer

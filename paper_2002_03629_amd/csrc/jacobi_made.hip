@@ -2867,8 +2867,6 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_
                         int32_t* iters_out, hipStream_t s, bool* done) {
   *done = false;
   if (!m->use_xcd || !m->xp_fits || N > XCDS * XP_ROWS || m->n_chains > 1) return MADE_OK;
-  // (real states: one of the calls that MADE_OPT_LAZY_STOP_TEST covers)
-  if (m->real && (!m->lazy_retire || cap < 2)) return MADE_OK;
   if (m->use_xcd == 1) {
     size_t visible = 0;
     for (const Layer& ly : m->layers)
@@ -2930,9 +2928,7 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_
     return MADE_OK;
   }
   *done = true;
-  const int rc = xcd_results(m);
-  if (m->real) m->stats[5] = std::min<int64_t>(m->stats[0], cap - 1);   // (the last allowed pass counts as one with a tail)
-  return rc;
+  return xcd_results(m);
 }
 
 // The whole call in one launch of the sample-resident kernel (see resident_sampler_kernel): one workgroup per 32

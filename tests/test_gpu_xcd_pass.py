@@ -60,6 +60,31 @@ def test_against_launches(D, hidden, dtype, real):
         B.made_free(h)
 
 
+@pytest.mark.parametrize("real", [False, True])
+def test_one_launch_whatever_the_stop_test_of_the_launches(real):
+    """MADE_OPT_LAZY_STOP_TEST belongs to the per-layer launches: with either value, and with a single allowed pass, the call is
+    one launch, and no pass of it counts as one whose list the next pass derived."""
+    D, N = 50, 33
+    w = S.Workload(f"xps{real}", D, 2 if real else 1, [70], "bf16", N, "random", "fan_in", S.SEED_BASE + 2180, gain=2.0, real=real)
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    try:
+        gen = np.random.default_rng(5)
+        noise = torch.from_numpy((gen.logistic(size=(N, D)) if real else gen.random((N, D))).astype(np.float32)).cuda()
+        for lazy in (1, 0):
+            B.made_set_option(h, B.MADE_OPT_LAZY_STOP_TEST, lazy)
+            for cap in (0, 1, 2):
+                out = []
+                for xcd in (1, 0):
+                    B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, xcd)
+                    out.append(_call(h, real, noise, N, None, 0.0, cap, D))
+                (xa, ia, ca, sa), (xb, ib, cb, sb) = out
+                assert sa["kernels"] == 1 and sa["tail_less_passes"] == 0, (lazy, cap, sa)
+                assert (xa == xb).all() and (ia == ib).all() and ca == cb and sa["passes"] == sb["passes"], (lazy, cap)
+                assert (sb["tail_less_passes"] > 0) == (lazy == 1 and cap != 1), (lazy, cap, sb)
+    finally:
+        B.made_free(h)
+
+
 def test_more_samples_and_one_hot_models_take_the_other_paths():
     w = S.Workload("xpn", 40, 2, [50], "bf16", 257, "random", "fan_in", S.SEED_BASE + 2190, gain=1.5, real=True)
     h = B.model_from_network(S.make_network(w, with_bias=True))
