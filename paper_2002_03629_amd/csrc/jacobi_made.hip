@@ -149,6 +149,8 @@ static void free_chain(Chain& c) {
   c = Chain();
 }
 
+constexpr int GRID_BAR = 2 * XCDS * XCD_LINE + XCDS * 32;   // (words, see Workspace::bar)
+
 struct Workspace {
   int N_cap = 0;
   void* enc = nullptr;               // [N_pad, D_pad] network input of the current iterate
@@ -168,7 +170,8 @@ struct Workspace {
   int n_pad = 0;
   std::vector<Chain> chains;         // independent sub-batches, each on its own stream
   hipEvent_t fork_ev = nullptr;
-  unsigned* bar = nullptr;           // persistent kernel: grid barrier counter
+  unsigned* bar = nullptr;           // xcd_sampler_kernel: barrier flags, registration, barrier counts; then (GRID_BAR) the
+                                     // persistent kernel's grid barrier counter, in a line of its own
   long long* dev_stats = nullptr;    // persistent kernel: [passes, sample-passes]
   volatile int* h_pin = nullptr;     // pinned host words: [0] flags copy, [2..5] persistent kernel's statistics
   volatile int* xcd_report = nullptr;     // pinned, device-visible: what xcd_sampler_kernel reports (8 words per XCD + flags)
@@ -426,9 +429,9 @@ static int ensure_workspace(made_model* m, int N, bool need_z) {
   HIP_TRY(hipMemset(w.lazy_masks, 0, (size_t)64 * sizeof(unsigned)));
   w.n_pad = n_pad;
   // (xcd_sampler_kernel: per XCD a flag array for its barrier and a counter for the registration of its workgroups,
-  // and the word in which it keeps counting its barriers from call to call)
-  HIP_TRY(hipMalloc((void**)&w.bar, (size_t)(2 * XCDS * XCD_LINE + XCDS * 32) * sizeof(unsigned)));
-  HIP_TRY(hipMemset(w.bar, 0, (size_t)(2 * XCDS * XCD_LINE + XCDS * 32) * sizeof(unsigned)));
+  // and the word in which it keeps counting its barriers from call to call; persistent_sampler_kernel: its counter)
+  HIP_TRY(hipMalloc((void**)&w.bar, (size_t)(GRID_BAR + 32) * sizeof(unsigned)));
+  HIP_TRY(hipMemset(w.bar, 0, (size_t)(GRID_BAR + 32) * sizeof(unsigned)));
   HIP_TRY(hipHostMalloc((void**)&w.xcd_report, (size_t)(8 * XCDS + 8) * sizeof(int), hipHostMallocMapped));
   HIP_TRY(hipHostGetDevicePointer((void**)&w.xcd_report_dev, (void*)w.xcd_report, 0));
   for (int i = 0; i < 8 * XCDS + 8; ++i) w.xcd_report[i] = 0;
@@ -2668,10 +2671,10 @@ static int run_persistent(made_model* m, const float* noise, int N, const uint8_
   p.n_pad = w.n_pad;
   p.iters = w.iters;
   p.flags = w.flags;
-  p.bar = w.bar;
+  p.bar = w.bar + GRID_BAR;   // (not word 0: that is a barrier flag of xcd_sampler_kernel, kept from call to call)
   p.stats = w.dev_stats;
   p.spin_limit = 1u << 22;
-  HIP_TRY(hipMemsetAsync(w.bar, 0, sizeof(unsigned), s));
+  HIP_TRY(hipMemsetAsync(p.bar, 0, sizeof(unsigned), s));
   HIP_TRY(hipMemsetAsync(w.flags, 0, sizeof(int), s));
   void* args[] = {&p};
   prof_mark(m, m->L + 1, false, s);

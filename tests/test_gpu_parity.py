@@ -375,6 +375,26 @@ def test_xcd_resident_kernel_serves_the_call():
             assert (xb == xb2).all() and (itb == itb2).all()
 
 
+def test_whole_call_kernels_in_turn_on_one_model():
+    """The kernel with one barrier for the whole grid and the one with a barrier per XCD share a model's scratch memory: calls
+    of the two in turn, long and short, give what the per-layer launches give."""
+    import gpu_util
+    if gpu_util.XCD != 2:
+        pytest.skip("runs once, on the XCD-resident execution path")
+    w = S.workload("mid_bf16")
+    net = S.make_network(w, with_bias=True)
+    noise = S.make_noise(w)
+    with GpuModel(net) as g:
+        want = {}
+        for persistent, xcd in [(0, 0)] + [(1, 0), (0, 2)] * 6:
+            B.made_set_option(g.h, B.MADE_OPT_PERSISTENT, persistent)
+            B.made_set_option(g.h, B.MADE_OPT_XCD_RESIDENT, xcd)
+            for block in (0, 7, 64):                      # (0: Jacobi)
+                x, it = g.gs_jacobi(noise, block) if block else g.jacobi(noise)
+                ref = want.setdefault(block, (x, it))
+                assert (x == ref[0]).all() and (it == ref[1]).all(), (persistent, xcd, block)
+
+
 def test_tail_less_stop_test_serves_the_call_and_changes_nothing():
     """MADE_OPT_LAZY_STOP_TEST = 1: every pass but a call's last allowed one has no tail (the next pass derives its
     list), and symbols, per-sample pass counts and the call's statistics are those of the tail, bit for bit -- from
