@@ -270,7 +270,9 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  * made_set_option -- execution choices that never change results.
  *   MADE_OPT_PERSISTENT (default 0): 1 = serve jacobi_sample / gs_jacobi_sample of Bernoulli models with
  *   batch <= 2048 from ONE cooperative launch that keeps a workgroup per CU resident and separates layers by
- *   a grid-wide barrier; 0 = one kernel launch per layer and pass.  Same results either way; on MI355X the
+ *   a grid-wide barrier; 0 = one kernel launch per layer and pass.  A call that finds another whole-call kernel
+ *   whose workgroups wait for one another under way on the device (this one, or MADE_OPT_XCD_RESIDENT's) takes the launches too.
+ *   Same results either way; on MI355X the
  *   per-layer launches are currently the faster of the two at batch 128, hence the default.
  *   MADE_OPT_FROZEN_POSITIONS (default 1; 0 or 1): categorical models whose draw is fused into the output kernel: a pass
  *   of jacobi_sample / gs_jacobi_sample evaluates only the output positions behind the lowest position that the

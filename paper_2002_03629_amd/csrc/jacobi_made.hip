@@ -2632,6 +2632,21 @@ extern "C" int sequential_sample(made_model* m, const float* noise, int32_t N, i
   return MADE_OK;
 }
 
+// The kernels whose workgroups wait for one another (persistent, xcd_sampler and xcd_pass) need the whole chip: two of them, of two
+// models called from two threads, could each get a part of it and wait until both back out, or the persistent one fails.  A call
+// that finds another one under way takes the other paths, whose results are the same bit for bit.  (A call's kernel has reported when the call lets go; what is left of it waits for nobody.)
+struct WholeChip {
+  static std::atomic<int>& taken(int device) {
+    static std::atomic<int> flags[NOALLOC_MAX_DEVICES];
+    return flags[device >= 0 && device < NOALLOC_MAX_DEVICES ? device : 0];
+  }
+  std::atomic<int>& flag;
+  const bool got;
+  explicit WholeChip(int device) : flag(taken(device)), got(flag.exchange(1, std::memory_order_acquire) == 0) {}
+  ~WholeChip() { if (got) flag.store(0, std::memory_order_release); }
+  WholeChip(const WholeChip&) = delete;
+};
+
 // The whole call in one cooperative launch (see persistent_sampler_kernel).  Returns 1 in *done when the call
 // was served this way, 0 when the caller must take the stream-ordered path.
 static int run_persistent(made_model* m, const float* noise, int N, const uint8_t* x_init, uint8_t* x, int block,
@@ -2639,6 +2654,8 @@ static int run_persistent(made_model* m, const float* noise, int N, const uint8_
   *done = false;
   if (m->arch != 0 || m->real || !m->use_persistent || m->persist_grid <= 0 || N > PERSIST_MAX_N) return MADE_OK;
   if ((uintptr_t)x % 4 != 0) return MADE_OK;   // the kernel re-reads symbols through their aligned 32-bit words
+  WholeChip chip(m->device);
+  if (!chip.got) return MADE_OK;
   Workspace& w = m->ws;
   PersistArgs p;
   memset(&p, 0, sizeof p);
@@ -2708,21 +2725,6 @@ static int run_persistent(made_model* m, const float* noise, int N, const uint8_
   if (flags & 1) return fail(MADE_ERR_NOT_CONVERGED, "samples were still changing after the last allowed pass");
   return MADE_OK;
 }
-
-// The kernels whose workgroups wait for one another need the whole chip: two of them, of two models called from two threads, could
-// each get a part of it and wait until both back out.  A call that finds another one under way takes the other paths, whose
-// results are the same bit for bit.  (A call's kernel has reported when the call lets go; what is left of it waits for nobody.)
-struct WholeChip {
-  static std::atomic<int>& taken(int device) {
-    static std::atomic<int> flags[NOALLOC_MAX_DEVICES];
-    return flags[device >= 0 && device < NOALLOC_MAX_DEVICES ? device : 0];
-  }
-  std::atomic<int>& flag;
-  const bool got;
-  explicit WholeChip(int device) : flag(taken(device)), got(flag.exchange(1, std::memory_order_acquire) == 0) {}
-  ~WholeChip() { if (got) flag.store(0, std::memory_order_release); }
-  WholeChip(const WholeChip&) = delete;
-};
 
 // Every XCD's first workgroup reports into pinned memory once its share of the batch is done; the call returns when all have
 // (results stay ordered on the stream like those of any launch).

@@ -97,9 +97,10 @@ def test_more_samples_and_one_hot_models_take_the_other_paths():
         B.made_free(h)
 
 
-def test_calls_from_two_threads_do_not_wait_for_each_other():
+@pytest.mark.parametrize("persistent", [0, 1])
+def test_calls_from_two_threads_do_not_wait_for_each_other(persistent):
     """Two models sampled at once, from two threads on two streams: whichever path a call finds free, its result is the one it
-    reaches alone."""
+    reaches alone, and no call fails.  persistent: the second one's calls ask for the kernel with one barrier for the whole grid."""
     import threading
     models = []
     for real in (True, False):
@@ -107,26 +108,31 @@ def test_calls_from_two_threads_do_not_wait_for_each_other():
         models.append((real, B.model_from_network(S.make_network(w, with_bias=True))))
     gen = np.random.default_rng(8)
     noises = [torch.from_numpy((gen.logistic(size=(60, 120)) if real else gen.random((60, 120))).astype(np.float32)).cuda() for real, _ in models]
+    B.made_set_option(models[1][1], B.MADE_OPT_PERSISTENT, persistent)
     try:
         alone = [_call(h, real, u, 60, None, 0.0, 0, 120)[:2] for (real, h), u in zip(models, noises)]
-        wrong = []
+        wrong, done = [], [0, 0]
 
         def work(i):
             real, h = models[i]
             x = torch.empty(60, 120, dtype=torch.float32 if real else torch.uint8, device="cuda")
-            with torch.cuda.stream(torch.cuda.Stream()):
-                for _ in range(20):
-                    (B.jacobi_sample_real(h, noises[i], 60, None, 0.0, 0, x) if real else B.jacobi_sample(h, noises[i], 60, None, 0, x))
-                    torch.cuda.current_stream().synchronize()
-                    if not (x.cpu().numpy() == alone[i][0]).all():
-                        wrong.append(i)
+            try:
+                with torch.cuda.stream(torch.cuda.Stream()):
+                    for _ in range(20):
+                        (B.jacobi_sample_real(h, noises[i], 60, None, 0.0, 0, x) if real else B.jacobi_sample(h, noises[i], 60, None, 0, x))
+                        torch.cuda.current_stream().synchronize()
+                        if not (x.cpu().numpy() == alone[i][0]).all():
+                            wrong.append(i)
+                        done[i] += 1
+            except Exception as e:                    # (it would end this thread unseen)
+                wrong.append((i, repr(e)))
 
         threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
         for t in threads:
             t.start()
         for t in threads:
             t.join()
-        assert not wrong
+        assert not wrong and done == [20, 20], (wrong, done)
         for (real, h), u in zip(models, noises):      # (nothing was switched off on the way)
             assert _call(h, real, u, 60, None, 0.0, 0, 120)[3]["kernels"] == 1
     finally:
