@@ -310,7 +310,11 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   at most 1024 units wide (1.2-1.3x); 2 = whenever
  *   the batch fits (2048 samples, jacobi_sample_real: 256).  A call that finds another such call under way on the device takes
  *   the per-layer launches.  Same symbols and pass counts as the per-layer launches.  The kernel checks that its workgroups sit on the XCDs it assumes and are
- *   all resident; if not it backs out, and this and every later call on the model take the per-layer launches.
+ *   all resident; if not it backs out and the call takes the per-layer launches: so does every later call on the model if a
+ *   workgroup sat on another XCD, and the next 16 calls (32, 64, ... up to 4096 if they keep backing out; setting this option
+ *   ends that) if a wait ran out, as it does while long kernels of another stream or process hold compute units.
+ *   MADE_OPT_WAIT_LIMIT (default 2^20, >= 0): how many times a workgroup of such a kernel polls for the others at one
+ *   barrier before it backs out (2^20 polls: some tenths of a second).  A smaller one bounds the delay on a GPU that is shared.
  *   MADE_OPT_FUSED_CATEGORICAL (default 1): draw the Gumbel-max symbols inside the output layer's kernel (C = 256:
  *   always, logits stay in registers; other C: batches below the two tile-batch options, logits stay in LDS); 0 = write
  *   the logits to scratch memory and draw in a second kernel.
@@ -360,7 +364,8 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
 enum { MADE_OPT_PERSISTENT = 1, MADE_OPT_FUSED_CATEGORICAL = 2, MADE_OPT_CHAINS = 3, MADE_OPT_BIG_TILE_BATCH = 4,
        MADE_OPT_CONV_ROWS = 5, MADE_OPT_PREFIX_CACHE = 6, MADE_OPT_RESIDENT = 7, MADE_OPT_RETIRE_SPLIT = 8,
        MADE_OPT_MID_TILE_BATCH = 9, MADE_OPT_PARTIAL_SUM_BATCH = 10, MADE_OPT_XCD_RESIDENT = 11,
-       MADE_OPT_LAZY_STOP_TEST = 12, MADE_OPT_FROZEN_POSITIONS = 13, MADE_OPT_CALL_GRAPH = 14, MADE_OPT_ZERO_START = 15 };
+       MADE_OPT_LAZY_STOP_TEST = 12, MADE_OPT_FROZEN_POSITIONS = 13, MADE_OPT_CALL_GRAPH = 14, MADE_OPT_ZERO_START = 15,
+       MADE_OPT_WAIT_LIMIT = 16 };
 int made_set_option(made_model* m, int32_t option, int32_t value);
 
 /*

@@ -226,6 +226,11 @@ struct CallGraph {
 };
 constexpr int CALL_GRAPHS_MAX = 128;
 
+// The XCD kernels need all their workgroups resident; kernels of other streams or processes that hold compute units for longer than
+// a barrier waits make a call back out.  That passes: this many calls go by the other paths, twice as many after every further
+// call that backs out (up to SIT_OUT_MOST), and a call that is served starts the count again.
+constexpr int SIT_OUT_FIRST = 16, SIT_OUT_MOST = 4096;
+
 struct made_model {
   int arch = 0;                               // 0 masked MLP, 1 masked convolutional network
   bool poisoned = false;                      // a call gave up waiting for the device with its kernels still queued:
@@ -284,6 +289,8 @@ struct made_model {
                                               // derives a pass's list in its first kernel instead of in the previous one's tail
   int use_xcd = 1;                            // made_set_option(MADE_OPT_XCD_RESIDENT): 0 never, 1 where it pays, 2 whenever possible
   bool xp_fits = false;                       // xcd_pass_kernel can serve this model on this device
+  int wait_limit = 1 << 20;                   // made_set_option(MADE_OPT_WAIT_LIMIT): polls at a barrier of the two XCD kernels
+  int sit_out = 0, sit_out_next = SIT_OUT_FIRST;   // calls that leave these kernels out after a wait that ran out, and after the next
   int xcd_grid = 0;                           // workgroups of xcd_sampler_kernel (0 = not usable on this device / model)
   // block-wise forward substitution (column_sampler_kernel): LDS layout, 0 bytes = this model does not fit
   struct ColumnLds {                     // [0] GS-Jacobi, [1] sequential; bytes = 0: the model does not fit
@@ -573,6 +580,13 @@ extern "C" int made_set_option(made_model* m, int32_t option, int32_t value) {
   if (option == MADE_OPT_XCD_RESIDENT) {
     if (value < 0 || value > 2) return fail(MADE_ERR_ARG, "made_set_option: MADE_OPT_XCD_RESIDENT=%d outside [0, 2]", value);
     m->use_xcd = value;
+    m->sit_out = 0;
+    m->sit_out_next = SIT_OUT_FIRST;
+    return MADE_OK;
+  }
+  if (option == MADE_OPT_WAIT_LIMIT) {
+    if (value < 0) return fail(MADE_ERR_ARG, "made_set_option: MADE_OPT_WAIT_LIMIT=%d must be >= 0", value);
+    m->wait_limit = value;
     return MADE_OK;
   }
   if (option == MADE_OPT_FUSED_CATEGORICAL) {
@@ -2767,9 +2781,26 @@ static int xcd_results(made_model* m) {
   return MADE_OK;
 }
 
+// A call has backed out and its kernel has ended: true if the kernel is switched off for good (workgroups not where it expects
+// them, flag 4), false if a wait ran out, after which its calls sit out a while and the kernel starts from clean counters.
+static bool xcd_backed_out(made_model* m, const char* kernel) {
+  const int flags = m->ws.xcd_report[64];
+  m->ws.xcd_report[64] = 0;
+  m->stats[2] = 0;
+  if (flags & 4) {
+    (void)fail(MADE_OK, "%s backed out: more workgroups on an XCD than expected; other paths serve this model from now on", kernel);
+    return true;
+  }
+  m->sit_out = m->sit_out_next + 1;   // (every call starts by counting it down; no attempt while it is positive)
+  m->sit_out_next = std::min(2 * m->sit_out_next, SIT_OUT_MOST);
+  (void)fail(MADE_OK, "%s backed out: a barrier's wait ran out (workgroups not resident together); other paths serve this call "
+                      "and the next %d", kernel, m->sit_out - 1);
+  return false;
+}
+
 // The whole call in one launch, each XCD iterating its own share of the samples (see xcd_sampler_kernel).  *done = true
 // when the call was served this way; when the kernel backs out (workgroups not on the expected XCD, or not
-// co-resident) the path is switched off for this model and the caller takes the per-layer launches.
+// co-resident) the caller takes the other paths (see xcd_backed_out).
 static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_init, uint8_t* x, int block,
                    int cap, bool flag_unconverged, int32_t* iters_out, hipStream_t s, bool* done) {
   *done = false;
@@ -2787,6 +2818,7 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
     const bool gs = block < m->D;
     if (gs ? N > 1024 : (N > 512 || widest > 32)) return MADE_OK;
   }
+  if (m->sit_out > 0) return MADE_OK;
   WholeChip chip(m->device);
   if (!chip.got) return MADE_OK;
   Workspace& w = m->ws;
@@ -2823,12 +2855,12 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
   p.flags = w.flags;
   p.bar = w.bar;
   p.stats = w.dev_stats;
-  p.spin_limit = 1u << 20;
+  p.spin_limit = (unsigned)m->wait_limit;
   p.reg_base = w.xcd_calls++ * (unsigned)(m->xcd_grid / XCDS);
   p.call_id = (int)(++w.xcd_report_calls);
   p.host_report = w.xcd_report_dev;
-  // The device flags are only ever set when the kernel backs out (after which this path is switched off), but the
-  // per-layer scheduler and the persistent kernel share the word: the stream-ordered clear costs one small memset.
+  // The device flags are only ever set when the kernel backs out, but the per-layer scheduler and the persistent kernel
+  // share the word: the stream-ordered clear costs one small memset.
   HIP_TRY(hipMemsetAsync(w.flags, 0, sizeof(int), s));
   prof_mark(m, m->L + 1, false, s);
   if (m->dtype == MADE_BF16)
@@ -2840,23 +2872,14 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
   m->stats[2] += 1;
   bool backed_out = false;
   TRY(xcd_wait(m, p.call_id, s, &backed_out));
-  if (backed_out) {                              // results are incomplete: take the other path from now on
-    const int flags = w.xcd_report[64];
-    unsigned counters[2 * XCDS * XCD_LINE];
-    memset(counters, 0, sizeof counters);
-    (void)hipMemcpy(counters, w.bar, sizeof counters, hipMemcpyDeviceToHost);
-    char detail[256];
-    int off = 0;
-    for (int g = 0; g < XCDS; ++g)
-      off += snprintf(detail + off, sizeof detail - off, " %u", counters[(XCDS + g) * XCD_LINE] - p.reg_base);
-    (void)fail(MADE_OK, "xcd_sampler_kernel backed out (flags %d: 4 = more workgroups on an XCD than expected, 2 = a "
-                        "barrier's wait ran out; workgroups registered per XCD:%s; expected %d each); per-layer launches "
-                        "serve this model from now on", flags, detail, m->xcd_grid / XCDS);
-    m->xcd_grid = 0;
-    m->stats[2] = 0;
-    w.xcd_report[64] = 0;
+  if (backed_out) {                              // results are incomplete
+    if (xcd_backed_out(m, "xcd_sampler_kernel")) m->xcd_grid = 0;
+    HIP_TRY(hipMemset(w.bar, 0, (size_t)GRID_BAR * sizeof(unsigned)));
+    HIP_TRY(settle_clears());
+    w.xcd_calls = 0;
     return MADE_OK;
   }
+  m->sit_out_next = SIT_OUT_FIRST;
   *done = true;
   return xcd_results(m);
 }
@@ -2878,6 +2901,7 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_
       for (int k : ly.h_tile_kend) visible += (size_t)k * TILE * elem_size(m);
     if (visible > (size_t)XP_VISIBLE) return MADE_OK;
   }
+  if (m->sit_out > 0) return MADE_OK;
   WholeChip chip(m->device);
   if (!chip.got) return MADE_OK;
   Workspace& w = m->ws;
@@ -2913,7 +2937,7 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_
   p.slots = w.xp_slots;
   p.words = w.xp_words;
   p.flags = (int*)(w.xp_words + XCDS * 32);
-  p.spin_limit = 1u << 20;
+  p.spin_limit = (unsigned)m->wait_limit;
   p.reg_base = w.xp_calls++ * (unsigned)XP_GROUP;
   p.call_id = (int)(++w.xcd_report_calls);
   p.host_report = w.xcd_report_dev;
@@ -2925,13 +2949,14 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_
   bool backed_out = false;
   TRY(xcd_wait(m, p.call_id, s, &backed_out));
   if (backed_out) {
-    (void)fail(MADE_OK, "xcd_pass_kernel backed out (flags %d: 4 = more workgroups on an XCD than expected, 2 = a barrier's "
-                        "wait ran out); other paths serve this model from now on", (int)w.xcd_report[64]);
-    m->xp_fits = false;
-    m->stats[2] = 0;
-    w.xcd_report[64] = 0;
+    if (xcd_backed_out(m, "xcd_pass_kernel")) m->xp_fits = false;
+    HIP_TRY(hipMemset(w.xp_slots, 0, (size_t)XCDS * XP_GROUP * sizeof(unsigned long long)));
+    HIP_TRY(hipMemset(w.xp_words, 0, (size_t)(XCDS + 1) * 32 * sizeof(unsigned)));
+    HIP_TRY(settle_clears());
+    w.xp_calls = 0;
     return MADE_OK;
   }
+  m->sit_out_next = SIT_OUT_FIRST;
   *done = true;
   return xcd_results(m);
 }
@@ -3008,6 +3033,7 @@ extern "C" int jacobi_sample(made_model* m, const float* noise, int32_t N, const
   hipStream_t s = (hipStream_t)stream;
   memset(m->stats, 0, sizeof m->stats);
   m->ev_layer.clear();
+  if (m->sit_out > 0) m->sit_out -= 1;
   TRY(settle(m, s));
   TRY(ensure_workspace(m, N, true));
   const int cap = (max_iters <= 0 || max_iters > m->D) ? m->D : max_iters;
@@ -3034,6 +3060,7 @@ extern "C" int gs_jacobi_sample(made_model* m, const float* noise, int32_t N, co
   hipStream_t s = (hipStream_t)stream;
   memset(m->stats, 0, sizeof m->stats);
   m->ev_layer.clear();
+  if (m->sit_out > 0) m->sit_out -= 1;
   TRY(settle(m, s));
   TRY(ensure_workspace(m, N, true));
   bool done = false;
@@ -3120,6 +3147,7 @@ extern "C" int jacobi_sample_real(made_model* m, const float* noise, int32_t N, 
   memset(m->stats, 0, sizeof m->stats);
   m->ev_layer.clear();
   m->call_eps = eps;
+  if (m->sit_out > 0) m->sit_out -= 1;
   TRY(settle(m, s));
   TRY(ensure_workspace(m, N, true));
   const int cap = (max_iters <= 0 || max_iters > m->D) ? m->D : max_iters;

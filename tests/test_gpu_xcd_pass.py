@@ -85,6 +85,45 @@ def test_one_launch_whatever_the_stop_test_of_the_launches(real):
         B.made_free(h)
 
 
+@pytest.mark.parametrize("gs", [False, True])
+def test_a_wait_that_runs_out_switches_the_kernels_off_for_a_while(gs):
+    """MADE_OPT_WAIT_LIMIT = 0: whichever workgroup arrives first backs out.  The call's result is that of the launches, the next
+    16 calls take them, twice as many after another call that backs out, and then the kernel serves the model again."""
+    D, N = 90, 40
+    w = S.Workload("xpw", D, 1, [70, 60], "bf16", N, "random", "fan_in", S.SEED_BASE + 2185, gain=2.0)
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    noise = torch.from_numpy(np.random.default_rng(6).random((N, D)).astype(np.float32)).cuda()
+
+    def call():
+        if not gs:
+            return _call(h, False, noise, N, None, 0.0, 0, D)
+        x, it = torch.empty((N, D), dtype=torch.uint8, device="cuda"), torch.empty((N,), dtype=torch.int32, device="cuda")
+        B.gs_jacobi_sample(h, noise, N, None, 40, x, it)
+        torch.cuda.synchronize()
+        return x.cpu().numpy(), it.cpu().numpy(), 0, B.made_last_stats(h)
+
+    try:
+        B.made_set_option(h, B.MADE_OPT_RESIDENT, 0)
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+        want = call()
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 2)
+        kernels = []
+        for calls, limit in ((2, 1 << 20), (1, 0), (16, 1 << 20), (2, 1 << 20), (1, 0), (16, 0), (1, 0), (32, 0), (1, 1 << 20)):
+            B.made_set_option(h, B.MADE_OPT_WAIT_LIMIT, limit)
+            for _ in range(calls):
+                got = call()
+                assert (got[0] == want[0]).all() and (got[1] == want[1]).all()
+                kernels.append(got[3]["kernels"] == 1)
+        assert kernels == [True] * 2 + [False] * 17 + [True] * 2 + [False] * 50 + [True], kernels
+        B.made_set_option(h, B.MADE_OPT_WAIT_LIMIT, 0)
+        assert call()[3]["kernels"] > 1
+        B.made_set_option(h, B.MADE_OPT_WAIT_LIMIT, 1 << 20)
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 2)
+        assert call()[3]["kernels"] == 1
+    finally:
+        B.made_free(h)
+
+
 def test_more_samples_and_one_hot_models_take_the_other_paths():
     w = S.Workload("xpn", 40, 2, [50], "bf16", 257, "random", "fan_in", S.SEED_BASE + 2190, gain=1.5, real=True)
     h = B.model_from_network(S.make_network(w, with_bias=True))
