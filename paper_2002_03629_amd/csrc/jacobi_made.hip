@@ -181,6 +181,8 @@ struct Workspace {
   unsigned* xp_words = nullptr;             // registration and barrier counts [XCDS][32], and behind them its back-out flags
   unsigned xp_calls = 0;
   unsigned xcd_report_calls = 0;            // calls that reported through xcd_report
+  void* start = nullptr;                    // a call's x_init where x_out overlaps it (see keep_start)
+  size_t start_bytes = 0;
 };
 
 // Masked convolutional model (arch 1): first layer 3 -> F (type A), n_conv - 1 layers F -> F (type B), 1 x 1 head.
@@ -357,6 +359,7 @@ static void free_workspace(Workspace& w) {
   if (w.xp_slots) (void)hipFree(w.xp_slots);
   if (w.first_z) (void)hipFree(w.first_z);
   if (w.xp_words) (void)hipFree(w.xp_words);
+  if (w.start) (void)hipFree(w.start);
   w = Workspace();
 }
 
@@ -2798,10 +2801,28 @@ static bool xcd_backed_out(made_model* m, const char* kernel) {
   return false;
 }
 
+// When a call backs out, some XCDs may have written their results to x_out, and the path that takes over starts again: where x_out
+// overlaps x_init, from a copy of it.
+static int keep_start(made_model* m, const void** x_init, const void* x, size_t bytes, hipStream_t s) {
+  const uintptr_t from = (uintptr_t)*x_init, to = (uintptr_t)x;
+  if (!from || from + bytes <= to || to + bytes <= from) return MADE_OK;
+  Workspace& w = m->ws;
+  if (w.start_bytes < bytes) {
+    if (w.start) HIP_TRY(hipFree(w.start));
+    w.start = nullptr;
+    w.start_bytes = 0;
+    HIP_TRY(hipMalloc(&w.start, bytes));
+    w.start_bytes = bytes;
+  }
+  HIP_TRY(hipMemcpyAsync(w.start, *x_init, bytes, hipMemcpyDeviceToDevice, s));
+  *x_init = w.start;
+  return MADE_OK;
+}
+
 // The whole call in one launch, each XCD iterating its own share of the samples (see xcd_sampler_kernel).  *done = true
 // when the call was served this way; when the kernel backs out (workgroups not on the expected XCD, or not
-// co-resident) the caller takes the other paths (see xcd_backed_out).
-static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_init, uint8_t* x, int block,
+// co-resident) the caller takes the other paths (see xcd_backed_out) from *start, which this call may have replaced.
+static int run_xcd(made_model* m, const float* noise, int N, const void** start, uint8_t* x, int block,
                    int cap, bool flag_unconverged, int32_t* iters_out, hipStream_t s, bool* done) {
   *done = false;
   if (m->arch != 0 || m->real || m->C != 1 || !m->use_xcd || m->xcd_grid <= 0) return MADE_OK;
@@ -2821,6 +2842,7 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
   if (m->sit_out > 0) return MADE_OK;
   WholeChip chip(m->device);
   if (!chip.got) return MADE_OK;
+  TRY(keep_start(m, start, x, (size_t)N * m->D, s));
   Workspace& w = m->ws;
   PersistArgs p;
   memset(&p, 0, sizeof p);
@@ -2842,7 +2864,7 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
   p.enc = w.enc;
   p.enc_chunks = m->layers[0].k_chunks;
   p.noise = noise;
-  p.x_init = x_init;
+  p.x_init = (const uint8_t*)*start;
   p.x = x;
   p.N = N;
   p.D = m->D;
@@ -2891,7 +2913,7 @@ static int run_xcd(made_model* m, const float* noise, int N, const uint8_t* x_in
 // 300 / 2 x 2000 (5.2 MB) 51 / 56 / 70 / 82 against 58 / 59 / 80 / 105.  Every XCD reads all weights, so the gain shrinks once they
 // pass its L2 of 4 MB: 784 / 2 x 2000 (7.4 MB) 51 / 71 / 83 / 96 against 59 / 75 / 96 / 122.  The line is at 6 MB: wider models keep
 // the per-layer launches, whose kernels the profile of a call can tell apart.
-static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_init, void* x, float eps, int cap,
+static int run_xcd_pass(made_model* m, const float* noise, int N, const void** start, void* x, float eps, int cap,
                         int32_t* iters_out, hipStream_t s, bool* done) {
   *done = false;
   if (!m->use_xcd || !m->xp_fits || N > XCDS * XP_ROWS || m->n_chains > 1) return MADE_OK;
@@ -2921,18 +2943,19 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void* x_
     if (bytes >= ((size_t)1 << 31)) return MADE_OK;          // (the workspace of a call with far more samples)
     p.row_bytes[l] = (unsigned)bytes;
   }
+  TRY(keep_start(m, start, x, (size_t)N * m->D * (m->real ? sizeof(float) : 1), s));
   p.L = m->L;
   p.enc = w.enc;
   p.enc_chunks = m->layers[0].k_chunks;
   p.noise = noise;
-  p.x_init = x_init;
+  p.x_init = *start;
   p.x = x;
   p.eps = eps;
   p.N = N;
   p.D = m->D;
   p.cap = cap;
   p.flag_unconverged = cap < m->D;
-  p.zero_start = m->zero_start_fill && !x_init;
+  p.zero_start = m->zero_start_fill && !*start;
   p.iters = iters_out ? iters_out : w.iters;
   p.slots = w.xp_slots;
   p.words = w.xp_words;
@@ -3040,16 +3063,17 @@ extern "C" int jacobi_sample(made_model* m, const float* noise, int32_t N, const
   bool done = false;
   TRY(run_persistent(m, noise, N, x_init, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
   if (done) return MADE_OK;
-  TRY(run_xcd_pass(m, noise, N, x_init, x_out, 0.f, cap, iters_out, s, &done));
+  const void* start = x_init;
+  TRY(run_xcd_pass(m, noise, N, &start, x_out, 0.f, cap, iters_out, s, &done));
   if (done) return MADE_OK;
-  if (N <= 256) TRY(run_xcd(m, noise, N, x_init, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
+  if (N <= 256) TRY(run_xcd(m, noise, N, &start, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
   if (done) return MADE_OK;
-  TRY(run_resident(m, noise, N, x_init, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
+  TRY(run_resident(m, noise, N, (const uint8_t*)start, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
   if (done) return MADE_OK;
-  if (N > 256) TRY(run_xcd(m, noise, N, x_init, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
+  if (N > 256) TRY(run_xcd(m, noise, N, &start, x_out, m->D, cap, cap < m->D, iters_out, s, &done));
   if (done) return MADE_OK;
   std::vector<Block> blocks(1, make_block(m, 0, m->D, cap, false));
-  return run_chains(m, blocks, noise, x_init, x_out, N, cap < m->D, iters_out, s);
+  return run_chains(m, blocks, noise, (const uint8_t*)start, x_out, N, cap < m->D, iters_out, s);
 }
 
 extern "C" int gs_jacobi_sample(made_model* m, const float* noise, int32_t N, const uint8_t* x_init, int32_t block,
@@ -3070,18 +3094,19 @@ extern "C" int gs_jacobi_sample(made_model* m, const float* noise, int32_t N, co
   if (done) return MADE_OK;
   // (measured: the XCD-resident kernel is the faster of the two whole-call kernels up to ~256 samples, the
   // sample-resident one -- where the model fits it -- beyond)
-  if (N <= 256) TRY(run_xcd(m, noise, N, x_init, x_out, block, m->D, false, iters_out, s, &done));
+  const void* start = x_init;
+  if (N <= 256) TRY(run_xcd(m, noise, N, &start, x_out, block, m->D, false, iters_out, s, &done));
   if (done) return MADE_OK;
-  TRY(run_resident(m, noise, N, x_init, x_out, block, m->D, false, iters_out, s, &done));
+  TRY(run_resident(m, noise, N, (const uint8_t*)start, x_out, block, m->D, false, iters_out, s, &done));
   if (done) return MADE_OK;
-  if (N > 256) TRY(run_xcd(m, noise, N, x_init, x_out, block, m->D, false, iters_out, s, &done));
+  if (N > 256) TRY(run_xcd(m, noise, N, &start, x_out, block, m->D, false, iters_out, s, &done));
   if (done) return MADE_OK;
   std::vector<Block> blocks;
   for (int a = 0; a < m->D; a += block) {
     const int b = std::min(a + block, m->D);          // block = 0-based positions [a, b)
     blocks.push_back(make_block(m, a, b, b - a, true));
   }
-  return run_chains(m, blocks, noise, x_init, x_out, N, false, iters_out, s);
+  return run_chains(m, blocks, noise, (const uint8_t*)start, x_out, N, false, iters_out, s);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -3152,10 +3177,11 @@ extern "C" int jacobi_sample_real(made_model* m, const float* noise, int32_t N, 
   TRY(ensure_workspace(m, N, true));
   const int cap = (max_iters <= 0 || max_iters > m->D) ? m->D : max_iters;
   bool done = false;
-  TRY(run_xcd_pass(m, noise, N, x_init, x_out, eps, cap, iters_out, s, &done));
+  const void* start = x_init;
+  TRY(run_xcd_pass(m, noise, N, &start, x_out, eps, cap, iters_out, s, &done));
   if (done) return MADE_OK;
   std::vector<Block> blocks(1, make_block(m, 0, m->D, cap, false));
-  return run_chains(m, blocks, noise, (const uint8_t*)x_init, (uint8_t*)x_out, N, cap < m->D, iters_out, s);
+  return run_chains(m, blocks, noise, (const uint8_t*)start, (uint8_t*)x_out, N, cap < m->D, iters_out, s);
 }
 
 extern "C" int gs_jacobi_sample_real(made_model* m, const float* noise, int32_t N, const float* x_init, int32_t block,

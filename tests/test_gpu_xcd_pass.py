@@ -124,6 +124,53 @@ def test_a_wait_that_runs_out_switches_the_kernels_off_for_a_while(gs):
         B.made_free(h)
 
 
+@pytest.mark.parametrize("kind", ["bernoulli", "real", "gs"])
+def test_a_start_that_the_result_overwrites(kind):
+    """x_out is x_init: in one launch, and where the kernel backs out with some XCDs' results written (waits of a few polls run out
+    on some XCDs and not on others), the call's iterate, pass counts and verdict are those of its own start."""
+    real = kind == "real"
+    D, N = 90, 200
+    w = S.Workload("xpa", D, 2 if real else 1, [70, 60], "bf16", N, "random", "fan_in", S.SEED_BASE + 2187, gain=2.0, real=real)
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    gen = np.random.default_rng(9)
+    noise = torch.from_numpy((gen.logistic(size=(N, D)) if real else gen.random((N, D))).astype(np.float32)).cuda()
+    start = torch.from_numpy(gen.normal(size=(N, D)).astype(np.float32) if real else gen.integers(0, 2, size=(N, D)).astype(np.uint8)).cuda()
+
+    def call(same, cap):
+        x = start.clone() if same else torch.empty_like(start)
+        init, it, code = (x if same else start), torch.full((N,), -1, dtype=torch.int32, device="cuda"), 0
+        try:
+            if real:
+                B.jacobi_sample_real(h, noise, N, init, 0.0, cap, x, it)
+            elif kind == "gs":
+                B.gs_jacobi_sample(h, noise, N, init, 40, x, it)
+            else:
+                B.jacobi_sample(h, noise, N, init, cap, x, it)
+        except B.MadeError as e:
+            code = e.code
+            assert code == B.MADE_ERR_NOT_CONVERGED
+        torch.cuda.synchronize()
+        return x.cpu().numpy(), it.cpu().numpy(), code, B.made_last_stats(h)
+
+    try:
+        B.made_set_option(h, B.MADE_OPT_RESIDENT, 0)
+        for cap in (0, 2):
+            B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+            want = call(False, cap)
+            fell_back = 0
+            for limit in [1 << 20] + list(range(0, 30)) * 3:
+                B.made_set_option(h, B.MADE_OPT_WAIT_LIMIT, limit)
+                B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 2)
+                got = call(True, cap)
+                assert (got[0] == want[0]).all() and (got[1] == want[1]).all() and got[2] == want[2], (limit, cap)
+                assert got[3]["kernels"] == 1 or limit < 1 << 20
+                fell_back += got[3]["kernels"] > 1
+            assert fell_back >= 3, fell_back
+            print(kind, cap, "calls that fell back:", fell_back)
+    finally:
+        B.made_free(h)
+
+
 def test_more_samples_and_one_hot_models_take_the_other_paths():
     w = S.Workload("xpn", 40, 2, [50], "bf16", 257, "random", "fan_in", S.SEED_BASE + 2190, gain=1.5, real=True)
     h = B.model_from_network(S.make_network(w, with_bias=True))
