@@ -2939,9 +2939,8 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void** s
     pl.k_chunks = ly.k_chunks;
     pl.n_tiles = ly.n_tiles;
     pl.out_chunks = l < m->L ? m->layers[l + 1].k_chunks : 0;
-    const size_t bytes = (size_t)w.n_pad * ly.in_pad * elem_size(m);
-    if (bytes >= ((size_t)1 << 31)) return MADE_OK;          // (the workspace of a call with far more samples)
-    p.row_bytes[l] = (unsigned)bytes;
+    // (rows of this call, whatever batch the buffer was made for: at most 256 of 2048 inputs)
+    p.row_bytes[l] = (unsigned)((size_t)round_up(N, TILE) * ly.in_pad * elem_size(m));
   }
   TRY(keep_start(m, start, x, (size_t)N * m->D * (m->real ? sizeof(float) : 1), s));
   p.L = m->L;

@@ -33,7 +33,7 @@ struct XcdPassArgs {
   int L;                 // hidden layers; layer[L] is the output layer
   void* enc;
   int enc_chunks;
-  unsigned row_bytes[PERSIST_MAX_LAYERS];   // bytes of the buffer that layer l reads
+  unsigned row_bytes[PERSIST_MAX_LAYERS];   // bytes of the call's rows (whole tiles) in the buffer that layer l reads
   const float* noise;
   const void* x_init;    // symbols or states, NULL: zeros
   void* x;

@@ -124,6 +124,22 @@ def test_a_wait_that_runs_out_switches_the_kernels_off_for_a_while(gs):
         B.made_free(h)
 
 
+def test_one_launch_after_a_batch_that_needs_buffers_past_2_gib():
+    D, H, big, N = 4, 2048, (1 << 19) + 70, 100
+    w = S.Workload("xpb", D, 1, [H], "bf16", N, "random", "fan_in", S.SEED_BASE + 2188, gain=2.0)
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    try:
+        noise = torch.rand(big, D, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+        before = _call(h, False, noise[:N], N, None, 0.0, 0, D)
+        many = _call(h, False, noise, big, None, 0.0, 0, D)
+        after = _call(h, False, noise[:N], N, None, 0.0, 0, D)
+        assert before[3]["kernels"] == after[3]["kernels"] == 1, (before[3], after[3])
+        assert (before[0] == after[0]).all() and (before[1] == after[1]).all()
+        assert (many[0][:N] == before[0]).mean() > 0.99      # (other tiles, another order of sums)
+    finally:
+        B.made_free(h)
+
+
 @pytest.mark.parametrize("kind", ["bernoulli", "real", "gs"])
 def test_a_start_that_the_result_overwrites(kind):
     """x_out is x_init: in one launch, and where the kernel backs out with some XCDs' results written (waits of a few polls run out
