@@ -310,7 +310,9 @@ struct ColProducer {
 #pragma unroll
       for (int l = 0; l <= L; ++l) waves[l] += l == most;
     }
-    // this wave's layer, and its steps of it: [steps i / w, steps (i + 1) / w)  (w <= 8 waves, quotients rounded alike)
+    // this wave's layer, and its steps of it: [steps i / w, steps (i + 1) / w), rounded, for the i-th of its w <= 8 waves.  (One wave's
+    // end and the next one's start have to be the same number: an explicit fma, so that they are one operation on one set of
+    // values however the two are compiled.  In whole numbers the call of 784 / 2 x 2000, blocks of 16, took 278.5 us for 276.)
     int layer = 0, i = pw;
 #pragma unroll
     for (int l = 0; l < L; ++l)
@@ -324,7 +326,8 @@ struct ColProducer {
       clear();
       const int steps = steps_whole(cur.k0(l)), n = (b.rows(l) + 15) >> 4;
       const float per = (float)steps * __builtin_amdgcn_rcpf((float)max(waves[l], 1));
-      const int j = i == 0 ? 0 : (int)(per * (float)i + 0.5f), end = i + 1 >= waves[l] ? steps : (int)(per * (float)(i + 1) + 0.5f);
+      auto cut = [&](int k) { return k >= waves[l] ? steps : (int)__builtin_fmaf(per, (float)k, 0.5f); };
+      const int j = cut(i), end = cut(i + 1);
       if (n == 1) product<l, 1>(p, lds, b, j, end);
       else if (n == 2) product<l, 2>(p, lds, b, j, end);
       if constexpr (l < L) {
