@@ -117,9 +117,14 @@ __device__ __forceinline__ float col_relu(float v) {
   asm("v_max_f32 %0, 0, %1" : "=v"(r) : "v"(v));
   return r;
 }
-// u < sigmoid(z) as z > log(u / (1 - u)): the right-hand side does not wait for z (u = 0: -inf).  Rounded once or twice, it is
-// nearer to the exact line than the other kernels' sigmoid, which is within 1e-6; a draw can only differ from theirs there.
-__device__ __forceinline__ float col_threshold(float u) { return logf(u / (1.0f - u)); }
+// u < sigmoid(z) as z > log(u / (1 - u)): the right-hand side does not wait for z.  Rounded once or twice, it is nearer to the exact
+// line than the other kernels' sigmoid, which is within 1e-6; a draw can only differ from theirs there.  At the ends as they
+// decide: their sigmoid is 0 from about log(2^-126) down, which u = 0 is not below (a logit of -1e4 never draws 1); u < 0 is below
+// any, u >= 1 and a NaN below none.
+__device__ __forceinline__ float col_threshold(float u) {
+  const float t = logf((u == 0.0f ? 0x1p-126f : u) / (1.0f - u));
+  return u < 0.0f ? -__builtin_inff() : t;
+}
 
 // max(v, 0) in lanes whose `top` is infinity, 0 in those where it is 0
 __device__ __forceinline__ float col_relu_below(float v, float top) {

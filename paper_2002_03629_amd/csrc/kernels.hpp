@@ -41,8 +41,9 @@ __device__ __forceinline__ float bf16_to_f32(bf16_t h) { return __uint_as_float(
 // P(x = 1) = 1 / (1 + exp(-v)) of a binary state (the conditional a draw u < P is taken from), evaluated with the
 // hardware's exp2 and reciprocal: within 1e-6 of the exact value (|v| log2(e) 2^-24 relative in the exponential,
 // scaled by P (1 - P) <= 1/4, plus an ulp each for exp2 and the reciprocal), 0 and 1 at the extremes.  Every
-// kernel that draws binary states from logits uses this one expression, so a draw does not depend on which of
-// them made it.  (The library's full-precision expf and division cost ~80 instructions per draw.)
+// kernel that draws binary states from logits by their probability uses this one expression, so a draw does not depend on
+// which of them made it; the two that compare the logit with a threshold (col_threshold, resident_sampler_kernel) can differ
+// from it within that error.  (The library's full-precision expf and division cost ~80 instructions per draw.)
 __device__ __forceinline__ float bernoulli_probability(float v) { return __builtin_amdgcn_rcpf(1.0f + __expf(-v)); }
 
 template <typename T> struct Elem;

@@ -154,6 +154,37 @@ def test_models_that_leave_room_for_one_buffer_of_staged_weights(D, hidden, dtyp
         B.made_free(h)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_noise_and_logits_at_the_ends(dtype):
+    """Logits of any size against noise at and outside the ends of [0, 1): the symbols are those of the kernels that compute the
+    probability.  Every pair of them; none is within 1e-6 of a tie."""
+    logits = np.array([-1e30, -1e4, -200, -89, -86, -20, 0.5, 20, 86, 89, 200, 1e4, 1e30], np.float32)
+    us = np.array([0.0, -1.0, -0.0, 2.0 ** -24, 1e-30, 0.25, 0.75, 1 - 2.0 ** -24, 1.0, 2.0, np.nan, -np.inf, np.inf], np.float32)
+    D, N = logits.size, us.size * 2
+    w = S.Workload("ends", D, 1, [40], dtype, N, "random", "fan_in", S.SEED_BASE + 770, gain=0.0)
+    net = S.make_network(w, with_bias=True)
+    net.W[-1][:] = 0.0
+    net.b[-1] = logits.reshape(np.asarray(net.b[-1]).shape)
+    noise = torch.from_numpy(np.repeat(np.tile(us, 2)[:, None], D, axis=1).copy()).cuda()
+    h = B.model_from_network(net)
+    try:
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+        want = torch.empty((N, D), dtype=torch.uint8, device="cuda")
+        B.jacobi_sample(h, noise, N, None, 0, want)
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 1)
+        p = 1 / (1 + np.exp(-np.clip(logits.astype(np.float64), -700, 700)))
+        assert (want.cpu().numpy()[3:8] == (us[3:8, None] < p)).all()          # (the ordinary values, against 64 bits)
+        for call in (lambda x: B.sequential_sample(h, noise, N, 1, x), lambda x: B.gs_jacobi_sample(h, noise, N, None, 5, x)):
+            x = torch.full((N, D), 9, dtype=torch.uint8, device="cuda")
+            call(x)
+            torch.cuda.synchronize()
+            assert B.made_last_stats(h)["kernels"] == 1
+            bad = (x != want).cpu().numpy()
+            assert not bad.any(), [(float(np.tile(us, 2)[i]), float(logits[j])) for i, j in np.argwhere(bad)]
+    finally:
+        B.made_free(h)
+
+
 def test_a_smaller_model_made_later_leaves_the_larger_one_its_lds():
     """Two models of one depth and type alive, the larger (about 130 KB of LDS) called after the smaller was made."""
     models = []
