@@ -368,9 +368,10 @@ __global__ __launch_bounds__(RES_W * 64) void resident_sampler_kernel(ResidentAr
 
   static_for<RES_MAXT * 16>([&](auto I) {     // (compile-time indices: the array must stay in registers)
     const float u = nz[I % 16][I / 16];
-    // (hardware logarithms: their error, ~1e-7 absolute here, is far inside the margin the threshold form allows;
-    // u = 0 gives -inf: always 1)
-    nz[I % 16][I / 16] = u >= 1.0f ? __builtin_inff() : __logf(u) - __logf(1.0f - u);
+    // (hardware logarithms: their error, ~1e-7 absolute here, is far inside the margin the threshold form allows; at the ends
+    // as the other kernels' probability decides, see col_threshold)
+    const float t = u >= 1.0f ? __builtin_inff() : __logf(u == 0.0f ? 0x1p-126f : u) - __logf(1.0f - u);
+    nz[I % 16][I / 16] = u < 0.0f ? -__builtin_inff() : t;
   });
 
   ResCtx cx;

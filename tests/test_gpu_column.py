@@ -154,8 +154,9 @@ def test_models_that_leave_room_for_one_buffer_of_staged_weights(D, hidden, dtyp
         B.made_free(h)
 
 
+@pytest.mark.parametrize("kernel", ["column", "resident"])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_noise_and_logits_at_the_ends(dtype):
+def test_noise_and_logits_at_the_ends(dtype, kernel):
     """Logits of any size against noise at and outside the ends of [0, 1): the symbols are those of the kernels that compute the
     probability.  Every pair of them; none is within 1e-6 of a tie."""
     logits = np.array([-1e30, -1e4, -200, -89, -86, -20, 0.5, 20, 86, 89, 200, 1e4, 1e30], np.float32)
@@ -169,12 +170,18 @@ def test_noise_and_logits_at_the_ends(dtype):
     h = B.model_from_network(net)
     try:
         B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+        B.made_set_option(h, B.MADE_OPT_RESIDENT, 0)
         want = torch.empty((N, D), dtype=torch.uint8, device="cuda")
         B.jacobi_sample(h, noise, N, None, 0, want)
-        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 1)
+        if kernel == "column":
+            B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 1)
+        B.made_set_option(h, B.MADE_OPT_RESIDENT, 2 if kernel == "column" else 1)
         p = 1 / (1 + np.exp(-np.clip(logits.astype(np.float64), -700, 700)))
         assert (want.cpu().numpy()[3:8] == (us[3:8, None] < p)).all()          # (the ordinary values, against 64 bits)
-        for call in (lambda x: B.sequential_sample(h, noise, N, 1, x), lambda x: B.gs_jacobi_sample(h, noise, N, None, 5, x)):
+        calls = [lambda x: B.gs_jacobi_sample(h, noise, N, None, 5, x)]
+        calls.append((lambda x: B.sequential_sample(h, noise, N, 1, x)) if kernel == "column" else
+                     (lambda x: B.jacobi_sample(h, noise, N, None, 0, x)))
+        for call in calls:
             x = torch.full((N, D), 9, dtype=torch.uint8, device="cuda")
             call(x)
             torch.cuda.synchronize()
