@@ -319,8 +319,8 @@ def parse_args(argv=None):
                     help="MADE_OPT_FROZEN_POSITIONS (-1 = library default)")
     ap.add_argument("--call-graph", type=int, default=0, choices=[0, 1],
                     help="MADE_OPT_CALL_GRAPH (library default 0): replay each call's launches as one HIP graph where the "
-                         "library supports it (Jacobi, Bernoulli MLP, per-layer launches, up to 256 samples); recorded "
-                         "before the warm-up.  cfg2: 0.098 ms per call whatever the host's launch cost, against "
+                         "library supports it (Jacobi, Bernoulli MLP, per-layer launches, up to 256 samples: cfg2 needs --path "
+                         "layers); recorded before the warm-up.  cfg2: 0.098 ms per call whatever the host's launch cost, against "
                          "0.091 / 0.104-0.108 ms launch by launch")
     ap.add_argument("--zero-start", type=int, default=1, choices=[0, 1],
                     help="MADE_OPT_ZERO_START (library default 1): a Bernoulli MLP's call started from zeros gets the first "

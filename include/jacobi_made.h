@@ -260,8 +260,8 @@ int made_last_stats(const made_model* m, int64_t* out, int32_t n);
  * made_set_profiling -- when enabled, every masked-layer launch of the *_sample calls is bracketed by
  * HIP events on the caller's stream; made_last_profile then returns the summed duration in milliseconds
  * and the number of launches of the most recent *_sample call for: slots 0..L-1 the hidden layers, slot L
- * the output layer incl. its sampling epilogue, slot L+1 the persistent whole-call kernel (see
- * made_set_option).  n must be L+2.  Off by default (events cost time).
+ * the output layer incl. its sampling epilogue, slot L+1 the kernel of a call in one launch, which has no times of its
+ * layers (MADE_OPT_XCD_RESIDENT = 0 has the launches serve such calls; see made_set_option).  n must be L+2.  Off by default (events cost time).
  */
 int made_set_profiling(made_model* m, int32_t enable);
 int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_t n);
@@ -300,13 +300,16 @@ int made_last_profile(const made_model* m, double* ms, int64_t* launches, int32_
  *   recording fixes: a set of arguments called again and again has two recordings, made by its third and fourth call.)
  *   Same results and pass counts.  The model keeps the 128 most recently used recordings; a
  *   change of any option or of the workspace size discards them.  The caller must not capture such a call itself.
+ *   A call that another option serves in one launch (MADE_OPT_XCD_RESIDENT, MADE_OPT_PERSISTENT) is not recorded, and the
+ *   tile-batch options do not act on it.
  *   MADE_OPT_XCD_RESIDENT (default 1; 0, 1 or 2): jacobi_sample / gs_jacobi_sample of Bernoulli models, and jacobi_sample_real
  *   on up to 256 samples (one chain), in ONE launch in
  *   which every XCD (a group of compute units with an L2 of its own) iterates its own eighth of the samples through
  *   all passes, synchronising only among its own workgroups and through its own L2 -- samples are independent
  *   systems, so nothing has to cross the chip.  0 = never; 1 = where it was measured faster than one launch per layer
  *   and pass: gs_jacobi_sample up to 1024 samples (1.5-2x), jacobi_sample and jacobi_sample_real up to 256 samples on models of
- *   up to 6 MB of visible weights and 2048 units a layer (1.4-2x), jacobi_sample up to 512 samples on models whose layers are
+ *   at most 2048 units a layer (1.05-2.2x; from 1025 units on of up to 10 MB of visible weights, or from 64 samples on of up
+ *   to 24 MB), jacobi_sample up to 512 samples on models whose layers are
  *   at most 1024 units wide (1.2-1.3x); 2 = whenever
  *   the batch fits (2048 samples, jacobi_sample_real: 256).  A call that finds another such call under way on the device takes
  *   the per-layer launches.  Same symbols and pass counts as the per-layer launches.  The kernel checks that its workgroups sit on the XCDs it assumes and are

@@ -2908,11 +2908,15 @@ static int run_xcd(made_model* m, const float* noise, int N, const void** start,
 
 // jacobi_sample / jacobi_sample_real in one launch of xcd_pass_kernel: up to 32 samples per XCD.  *done as in run_xcd.
 // Where it pays (use_xcd = 1), measured in us a call against the per-layer launches, batch 1 / 16 / 128 / 256: 64 / 256 fp32 30 / 37 /
-// 42 / 43 against 43 / 52 / 64 / 65; 784 / 2 x 512 real 85 / 98 / 99 / 108 against 143 / 192 / 208 / 234; 784 / 2 x 1000 fp32 64 / 99 /
-// 99 / 103 against 83 / 135 / 143 / 150; 784 / 2 x 1500 (4.6 MB of visible weights) 51 / 54 / 62 / 65 against 70 / 71 / 90 / 97;
-// 300 / 2 x 2000 (5.2 MB) 51 / 56 / 70 / 82 against 58 / 59 / 80 / 105.  Every XCD reads all weights, so the gain shrinks once they
-// pass its L2 of 4 MB: 784 / 2 x 2000 (7.4 MB) 51 / 71 / 83 / 96 against 59 / 75 / 96 / 122.  The line is at 6 MB: wider models keep
-// the per-layer launches, whose kernels the profile of a call can tell apart.
+// 42 / 43 against 43 / 52 / 64 / 65; 784 / 2 x 512 real 85 / 98 / 99 / 108 against 143 / 192 / 208 / 234; 784 / 2 x 1500 (4.6 MB of
+// visible weights) 51 / 54 / 62 / 65 against 70 / 71 / 90 / 97; 300 / 2 x 2000 (5.2 MB) 51 / 56 / 70 / 82 against 58 / 59 / 80 / 105.
+// Every XCD reads all weights, so the gain shrinks once they pass its L2 of 4 MB, the less the more samples an XCD has, and with few
+// of them it ends: 784 / 2 x 2000 (7.4 MB) 51 / 69 / 83 / 85 against 59 / 75 / 96 / 107; 784 / 2 x 1500 fp32 (9.3 MB) 115 / 142 / 141 /
+// 167 against 123 / 160 / 170 / 230; 784 / 3 x 2048 (12 MB) 67 / 92 / 91 / 98 against 72 / 94 / 101 / 119; 2000 / 2 x 2000 (12 MB) 87 / 97 /
+// 97 / 133 against 93 / 94 / 106 / 161; 784 / 4 x 2048 (16 MB) 60 / 94 / 92 / 96 against 63 / 89 / 97 / 112; 784 / 3 x 2000 fp32 (22 MB) 155 /
+// 168 / 210 / 211 against 154 / 158 / 223 / 289; batch 64 of the last three 96 / 113 / 211 against 100 / 120 / 221.  So: up to 10 MB, and
+// from 64 samples on up to 24 MB.  Models of at most 1024 units a layer, whose calls xcd_sampler_kernel would take, come here
+// whatever their weights: 784 / 6 x 1024 fp32 (13 MB) 101 / 105 / 144 / 149 against 183 / 189 / 272 / 285.
 static int run_xcd_pass(made_model* m, const float* noise, int N, const void** start, void* x, float eps, int cap,
                         int32_t* iters_out, hipStream_t s, bool* done) {
   *done = false;
@@ -2921,7 +2925,7 @@ static int run_xcd_pass(made_model* m, const float* noise, int N, const void** s
     size_t visible = 0;
     for (const Layer& ly : m->layers)
       for (int k : ly.h_tile_kend) visible += (size_t)k * TILE * elem_size(m);
-    if (visible > (size_t)XP_VISIBLE) return MADE_OK;
+    if (m->widest_tiles > XP_GROUP && visible > (size_t)(N < XP_FEW ? XP_VISIBLE_FEW : XP_VISIBLE)) return MADE_OK;
   }
   if (m->sit_out > 0) return MADE_OK;
   WholeChip chip(m->device);

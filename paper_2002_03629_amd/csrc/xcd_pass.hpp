@@ -25,7 +25,8 @@ constexpr int XP_ROWS = TILE;            // samples of an XCD
 constexpr int XP_MAX_TILES = 2 * XP_GROUP;   // unit tiles of a layer
 constexpr int XP_B = 4, XP_A = 2;        // K chunks of a wave and tile whose weights are requested ahead: of the tile with the
                                          // longer prefix, and of the shorter one
-constexpr int XP_VISIBLE = 6 << 20;      // bytes of visible weights, one and a half times an XCD's L2 (see run_xcd_pass)
+constexpr int XP_VISIBLE = 24 << 20, XP_VISIBLE_FEW = 10 << 20;   // bytes of visible weights up to which it pays, and on batches below
+constexpr int XP_FEW = 64;                                        // this (see run_xcd_pass)
 constexpr int XP_PITCH = TILE + 2;
 
 struct XcdPassArgs {

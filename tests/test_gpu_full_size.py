@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import made_oracle as O
+from paper_2002_03629_amd import binding as B
 from paper_2002_03629_amd import synth as S
 
 from gpu_util import (LOGIT_TOL, MARGIN, GpuModel, assert_logits_close, assert_sample_parity, mlp_layer_certificate,
@@ -43,8 +44,8 @@ def library_defaults():
 
 
 def test_cfg2_full_batch_as_benchmarked(library_defaults):
-    """cfg2 in the launch configuration bench.py times (library defaults): Jacobi on per-layer launches with the
-    tail-less stop test, GS-Jacobi in the one-launch kernel."""
+    """cfg2 in the launch configuration bench.py times (library defaults): Jacobi and GS-Jacobi in one-launch kernels; and Jacobi on
+    the per-layer launches with the tail-less stop test, with the same result."""
     test_cfg2_jacobi_and_gs_jacobi_full_batch(False, expect_default_paths=True)
 
 
@@ -60,7 +61,13 @@ def test_cfg2_jacobi_and_gs_jacobi_full_batch(persistent, expect_default_paths=F
     with GpuModel(net, persistent) as g:
         x, it = g.jacobi(noise)
         if expect_default_paths:
+            assert g.stats()["kernels"] == 1, g.stats()
+            one = (x, it)
+            B.made_set_option(g.h, B.MADE_OPT_XCD_RESIDENT, 0)
+            x, it = g.jacobi(noise)
             st = g.stats()
+            B.made_set_option(g.h, B.MADE_OPT_XCD_RESIDENT, 1)
+            assert (x == one[0]).all() and (it == one[1]).all()
             assert st["tail_less_passes"] >= st["passes"] > 0 and st["kernels"] > 3, st
         exempt, _ = assert_sample_parity(same, noise, x)
         assert_sample_parity(same, noise[:sub], x[:sub], xs, mg)

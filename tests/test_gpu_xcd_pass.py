@@ -140,6 +140,25 @@ def test_one_launch_after_a_batch_that_needs_buffers_past_2_gib():
         B.made_free(h)
 
 
+@pytest.mark.parametrize("hidden,dtype,few", [([2048] * 3, "bf16", False), ([2000, 1500], "bf16", True), ([1024] * 6, "f32", True)])
+def test_where_the_library_takes_one_launch(hidden, dtype, few):
+    """By default: 12 MB of visible weights from 64 samples on, 6 MB and layers of at most 1024 units (13 MB) always."""
+    D = 784
+    w = S.Workload("xpv", D, 1, hidden, dtype, 64, "random", "fan_in", S.SEED_BASE + 2189, gain=1.5)
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    try:
+        noise = torch.from_numpy(np.random.default_rng(4).random((64, D)).astype(np.float32)).cuda()
+        for N in (63, 64):
+            B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 1)
+            a = _call(h, False, noise[:N], N, None, 0.0, 0, D)
+            B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+            b = _call(h, False, noise[:N], N, None, 0.0, 0, D)
+            assert (a[3]["kernels"] == 1) == (few or N == 64), a[3]
+            assert (a[0] == b[0]).all() and (a[1] == b[1]).all()
+    finally:
+        B.made_free(h)
+
+
 @pytest.mark.parametrize("kind", ["bernoulli", "real", "gs"])
 def test_a_start_that_the_result_overwrites(kind):
     """x_out is x_init: in one launch, and where the kernel backs out with some XCDs' results written (waits of a few polls run out
