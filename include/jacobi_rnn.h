@@ -69,7 +69,7 @@ int rnn_jacobi_max_steps(int32_t H);
  *   dW [H, H] = sum p_t h_{t-1}^T,   dU [H, I] = sum p_t x_t^T,   db [H] = sum p_t      (outputs, overwritten)
  *   h [B, T, H] hidden states of the forward pass;  h0 [B, H] or NULL (zeros)
  * Sums are taken in an order that depends on the sizes alone: equal calls give equal bits.  (With more than 512 rows,
- * B * T, partial sums are kept in static device memory: 20 MiB per GPU, held until the process ends, shared safely by
+ * B * T, partial sums are kept in static device memory: 40 MiB per GPU, held until the process ends, shared safely by
  * calls on any streams and threads; up to four calls at a time have room there, others take longer.)
  */
 int rnn_param_grads(const float* z, const float* h, const float* x, const float* d, const float* h0, int32_t B, int32_t T,

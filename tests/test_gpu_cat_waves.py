@@ -1,5 +1,7 @@
 """256 classes, workgroups of four waves and of eight: at positions and chunks on both sides of the line between them and with a
-second pair of sample tiles (whose workgroups pass it), against the oracle's decisions and the on-GPU sequential sampler."""
+second pair of sample tiles (whose workgroups pass it), against the oracle's decisions and the on-GPU sequential sampler.  Both
+forms give the same bits and nothing a call returns names the one that ran: the sizes are taken from the rule itself
+(257 .. 512 workgroups, positions times pairs of sample tiles, and 16 chunks: eight waves)."""
 import numpy as np
 import pytest
 import torch

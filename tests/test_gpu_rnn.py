@@ -301,3 +301,25 @@ def test_last_state_does_not_read_the_weights(T, bad):
     d = torch.empty((B_, T, H), dtype=torch.float32, device="cuda")
     B.rnn_backward_sequential(dev(W), dev(z), dev(g), B_, T, H, d)
     assert np.array_equal(d.cpu().numpy()[:, -1], g[:, -1])
+
+
+@pytest.mark.parametrize("H,T", [(20, 480), (20, 481), (32, 512), (1, 500), (33, 256)])
+def test_jacobi_with_one_and_two_copies_of_the_product_s_input(H, T):
+    """A pass reads one copy of X in LDS and writes the other where two fit: up to 480 steps of up to 32 units, and every
+    longer shape of more units; beyond, one copy is updated in place.  Two samples, from zeros and from a start of one's own."""
+    progress(f"rnn jacobi H={H} T={T}")
+    w = dataclasses.replace(S.rnn_workload("rnn_small"), B=2, T=T, H=H, I=2, w_std=min(0.2, 1.2 / np.sqrt(H)))
+    c = Case(w)
+    init = np.random.default_rng(2).standard_normal((w.B, T, H)).astype(np.float32)
+    for start in (None, init):
+        for n in (1, 2, 3, 10):
+            d, it, cv = c.gpu_jacobi(n, 0.0, start)
+            ref, it_ref, _, _ = c.oracle_jacobi(n, 0.0, start)
+            # (one unit of weight 0.0116: a pass moves its iterate by 0.006 of what the one before did, so that fp32 stands still
+            # after six)
+            assert n > 3 or ((it == n).all() and (it_ref == n).all() and (cv == 0).all())
+            assert rel_err(d, ref) <= SPLIT_TOL, (start is None, n)
+        d, it, cv = c.gpu_jacobi(0, 1e-3, start)
+        assert (cv == 1).all() and (it < T).all()
+        d, it, cv = c.gpu_jacobi(0, 0.0, start)
+        assert rel_err(d, c.oracle_backprop()) <= SPLIT_TOL

@@ -216,6 +216,14 @@ def test_more_samples_and_one_hot_models_take_the_other_paths():
             assert (st["kernels"] == 1) == one, st
     finally:
         B.made_free(h)
+    w = S.workload("small_cat_onehot")
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    try:
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 2)
+        st = _call(h, False, torch.from_numpy(S.make_noise(w)).cuda(), w.N, None, 0.0, 0, w.D)[3]
+        assert st["kernels"] > 1, st
+    finally:
+        B.made_free(h)
 
 
 @pytest.mark.parametrize("persistent", [0, 1])
