@@ -2758,6 +2758,7 @@ static int xcd_wait(made_model* m, int call_id, hipStream_t s, bool* backed_out)
       return give_up_waiting(m, s);
   }
   std::atomic_thread_fence(std::memory_order_acquire);
+  *backed_out = *backed_out || w.xcd_report[64] != 0;
   if (m->profiling || *backed_out) {
     HIP_TRY(hipStreamSynchronize(s));
     m->stats[3] += 1;
@@ -2767,7 +2768,6 @@ static int xcd_wait(made_model* m, int call_id, hipStream_t s, bool* backed_out)
     w.pending_stream = s;
   }
   prof_collect(m);
-  *backed_out = *backed_out || w.xcd_report[64] != 0;
   return MADE_OK;
 }
 

@@ -187,7 +187,10 @@ __global__ __launch_bounds__(NW * 64, 2) void xcd_pass_kernel(XcdPassArgs p) {
       }
   };
   // ---- barrier among the XCD's workgroups: stores performed, flags, all flags seen; returns the rows that any of them
-  // changed in the last output layer (in active_s), false when the wait ran out.  `next`: the layer behind it.
+  // changed in the last output layer (in active_s), false when the wait ran out.  `next`: the layer behind it.  A wait that runs
+  // out behind an output layer ends the call like a last pass (no rows changed): the others may have seen the barrier complete, it
+  // may be the call's last one, after which the call is served, and then this workgroup's share of the result has to be there.
+  // (Where it is not, the back-out flag has reached the host before any report of this workgroup.)
   int my_changed = 0;                                    // wave 0: the rows this workgroup changed
   auto barrier = [&](int next, bool output) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -223,8 +226,8 @@ __global__ __launch_bounds__(NW * 64, 2) void xcd_pass_kernel(XcdPassArgs p) {
       // (read outside the branch: the last OR would be done for its one lane only)
       const int all = xp_or16((int)(v >> 32)), rows = __builtin_amdgcn_readlane(all, 0) | __builtin_amdgcn_readlane(all, 16);
       if (lane == 0) {
-        ok_s = ok;
-        active_s = rows;
+        ok_s = ok | (int)output;
+        active_s = ok ? rows : 0;
       }
     }
     lds_barrier();

@@ -124,6 +124,45 @@ def test_a_wait_that_runs_out_switches_the_kernels_off_for_a_while(gs):
         B.made_free(h)
 
 
+@pytest.mark.parametrize("real", [False, True])
+def test_a_wait_that_runs_out_at_the_last_barrier(real):
+    """A workgroup may give up on a barrier that the others then see complete.  Where it is the call's last one the call is served:
+    the result has to be whole.  Waits of a few polls, one pass, so that the barriers are few and the last one is met often (whether
+    a workgroup gives up there and the call is served all the same is a matter of microseconds that nothing here can force)."""
+    D, N = 90, 256
+    w = S.Workload("xpl", D, 2 if real else 1, [70], "bf16", N, "random", "fan_in", S.SEED_BASE + 2186, gain=2.0, real=real)
+    h = B.model_from_network(S.make_network(w, with_bias=True))
+    gen = np.random.default_rng(11)
+    noise = torch.from_numpy((gen.logistic(size=(N, D)) if real else gen.random((N, D))).astype(np.float32)).cuda()
+    x = torch.empty((N, D), dtype=torch.float32 if real else torch.uint8, device="cuda")
+
+    def call():
+        x.fill_(9)
+        try:
+            B.jacobi_sample_real(h, noise, N, None, 0.0, 1, x) if real else B.jacobi_sample(h, noise, N, None, 1, x)
+        except B.MadeError as e:
+            assert e.code == B.MADE_ERR_NOT_CONVERGED
+        return B.made_last_stats(h)["kernels"] == 1
+
+    try:
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+        call()
+        want = x.clone()
+        wrong, one = [], 0
+        for limit in [n for n in range(24) for _ in range(100)]:
+            B.made_set_option(h, B.MADE_OPT_WAIT_LIMIT, limit)
+            B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 2)
+            served = call()
+            one += served
+            if not torch.equal(x, want):
+                wrong.append((limit, served, int((x != want).sum())))
+        print(real, "served in one launch:", one, "of 2400")
+        assert not wrong, (len(wrong), wrong[:5])
+        assert 0 < one < 2400, one
+    finally:
+        B.made_free(h)
+
+
 def test_one_launch_after_a_batch_that_needs_buffers_past_2_gib():
     D, H, big, N = 4, 2048, (1 << 19) + 70, 100
     w = S.Workload("xpb", D, 1, [H], "bf16", N, "random", "fan_in", S.SEED_BASE + 2188, gain=2.0)
