@@ -173,30 +173,37 @@ def cpu_baseline_conv(w, net, noise, budget_s=12.0):
                       f"{t} of {model.D} states of one image in {dt:.1f} s, scaled to a whole image"}, x[:, :t], t
 
 
-def measured_traffic(workload: str, path: str, dom_is_output: bool):
-    """HBM bytes per launch of the dominant kernel, as measured with rocprofv3 PMC counters in a separate run
+def profile_name(workload: str, one_launch: bool):
+    """cfg2's calls have a summary for either form: one launch a call, and one per layer and pass."""
+    return "cfg2_layers" if workload == "cfg2" and not one_launch else workload
+
+
+def measured_traffic(workload: str, path: str, dom_is_output: bool, one_launch: bool):
+    """(bytes per launch of the dominant kernel, file), as measured with rocprofv3 PMC counters in a separate run
     (counters cannot be read from inside this process); the summary under profiles/ holds the figure."""
-    if workload not in ("cfg2", "cfg4") or path == "persistent" or not dom_is_output:
-        return None
-    fn = os.path.join(ROOT, "profiles", f"{workload}_jacobi_pmc_traffic.txt")
+    if workload not in ("cfg2", "cfg4") or path == "persistent" or not (dom_is_output or one_launch):
+        return None, None
+    name = f"profiles/{profile_name(workload, one_launch)}_jacobi_pmc_traffic.txt"
     try:
-        for line in open(fn):
+        for line in open(os.path.join(ROOT, name)):
             if line.startswith("traffic_bytes_per_launch"):
-                return int(line.rsplit(":", 1)[1])
+                return int(line.rsplit(":", 1)[1]), name
     except OSError:
         pass
-    return None
+    return None, None
 
 
-def measured_mfma(workload: str):
+def measured_mfma(workload: str, path: str, one_launch: bool):
     """MFMA counters of the workload's kernels from a separate `rocprofv3 --pmc` run, as summarised under profiles/
     (lines `name: value` after the marker `bench_fields:`); None when no such summary exists."""
-    fn = os.path.join(ROOT, "profiles", f"{workload}_pmc_mfma.txt")
+    if path == "persistent":
+        return None
+    name = f"profiles/{profile_name(workload, one_launch)}_pmc_mfma.txt"
     try:
-        lines = open(fn).read().splitlines()
+        lines = open(os.path.join(ROOT, name)).read().splitlines()
     except OSError:
         return None
-    out, on = {"source": f"profiles/{workload}_pmc_mfma.txt"}, False
+    out, on = {"source": name}, False
     for line in lines:
         if line.startswith("bench_fields:"):
             on = True
@@ -539,7 +546,8 @@ def run_one(args, torch, B, S, light=False):
         full = {"avg_launch_us": full_us, "achieved": full_ach, "frac": full_ach / peak,
                 "launches": int(first_launches[dom]),
                 "what": "the same kernel on a pass over the full batch (first pass of a call with pass limit 1)"}
-    pmc = measured_mfma(w.name)
+    pmc = measured_mfma(w.name, args.path, dom == n_layers)
+    traffic, traffic_file = measured_traffic(w.name, args.path, dom == n_layers - 1, dom == n_layers)
 
     result = {
         "metric": "samples/s (Jacobi vs sequential, same output); iters to converge; MFMA util",
@@ -570,12 +578,12 @@ def run_one(args, torch, B, S, light=False):
         **({"image_evaluations_per_step": conv_rows / w.H / args.steps} if conv else {}),
         "roofline": {
             "bound": bound, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
-            "traffic": measured_traffic(w.name, args.path, dom == n_layers - 1), "kernel": layer_name, "avg_launch_us": dom_avg_us,
+            "traffic": traffic, "kernel": layer_name, "avg_launch_us": dom_avg_us,
             "launches": int(layer_launches[dom]),
             "per_slot_avg_us": [float(m / max(1, c) * 1e3) for m, c in zip(layer_ms, layer_launches)],
             "mfma_tflops": layer_flops[dom] / (layer_ms[dom] * 1e-3) / 1e12 if layer_ms[dom] > 0 else 0.0,
             "full_batch_launch": full,
-            "traffic_source": "profiles/%s_jacobi_pmc_traffic.txt (two separate rocprofv3 --pmc runs)" % w.name,
+            "traffic_source": f"{traffic_file} (two separate rocprofv3 --pmc runs)" if traffic else None,
             "rocprof": pmc,
             "note": "frac uses durations from HIP events around each launch on the launch stream, measured live in a "
                     "second pass over the same steps, averaged over ALL launches of the kernel in a call (late "
