@@ -699,10 +699,12 @@ static int column_units(const made_model* m, int a, int b) {
 }
 
 // Whether and how column_sampler_kernel can hold this model: LDS layout, and the blocks of sequential sampling (as many
-// positions as the lanes of a wave have units for).  A model it cannot hold keeps the other paths.
+// positions as the lanes of a wave have units for).  A model it cannot hold keeps the other paths, and so does one of whose visible
+// weights some are infinite or NaN: the kernel multiplies staged weights of other blocks with 0 and would carry those on.
+static bool column_model(const made_model* m) { return m->C == 1 && !m->real && m->L <= COL_MAX_L; }
 static void plan_column(made_model* m) {
   const int L = m->L, D = m->D;
-  if (m->C != 1 || m->real || L > COL_MAX_L) return;
+  if (!column_model(m)) return;
   const int es = (int)elem_size(m);
   const int limit = 160 * 1024 - 256;                    // LDS of a gfx950 compute unit, less the kernel's own small arrays
   for (int seq = 0; seq < 2; ++seq) {
@@ -805,6 +807,7 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
   for (int d = 0; d < D; ++d) { in_deg[d] = d + 1; perm_prev[d] = d; }
   m->layers.resize(L + 1);
   m->cnt_lt.resize(L);
+  std::atomic<bool> all_finite{true};
 
   int rc = MADE_OK;
   try {
@@ -878,9 +881,12 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
       // mask, permute, convert and lay out in fragment-major order; rows are independent, so large layers
       // (the 2 GiB output layer of a 256-class model) are filled by several host threads
       auto fill_rows = [&](int j0, int j1) {
+        bool finite = true;
         for (int j = j0; j < j1; ++j) {
           const float* src = Wl + (size_t)perm[j] * ly.in_dim;
           const int kl = klen[j];
+          if (column_model(m))
+            for (int i = 0; i < kl; ++i) finite &= std::fabs(src[perm_prev[i]]) <= 0x1.fep127f;   // (the largest bf16)
           if (m->dtype == MADE_BF16) {
             uint16_t* dst = (uint16_t*)host.data();
             for (int i = 0; i < kl; ++i) dst[frag_offset<bf16_t>(j, i, ly.k_chunks)] = host_f32_to_bf16(src[perm_prev[i]]);
@@ -889,6 +895,7 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
             for (int i = 0; i < kl; ++i) dst[frag_offset<float>(j, i, ly.k_chunks)] = src[perm_prev[i]];
           }
         }
+        if (!finite) all_finite.store(false, std::memory_order_relaxed);
       };
       const int n_threads = n_w > ((size_t)1 << 24) ? 16 : 1;
       if (gather) {
@@ -1015,7 +1022,7 @@ extern "C" int made_init(const made_config* cfg, const int32_t* const* degrees, 
     }
     (void)hipGetLastError();
   }
-  plan_column(m);
+  if (all_finite.load()) plan_column(m);
   *out = m;
   return MADE_OK;
 }

@@ -192,6 +192,39 @@ def test_noise_and_logits_at_the_ends(dtype, kernel):
         B.made_free(h)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_weights_that_are_no_numbers_stay_where_they_are(dtype):
+    """The kernel multiplies what is staged past a block's last unit, an earlier block's weights, with 0.  A NaN among them must not
+    reach the units of another block: ReLU ends it in its own unit."""
+    D, N = 90, 24
+    w = S.Workload("nonum", D, 1, [150, 130], dtype, N, "random", "fan_in", S.SEED_BASE + 760, gain=2.5)
+    net = S.make_network(w, with_bias=True)
+    deg = [np.arange(1, D + 1)] + [np.asarray(d) for d in net.degrees]
+    for l, unit_deg, limit in ((0, 9, 9), (0, 12, 10), (1, 13, 12), (1, 17, 15)):          # unit of a degree, input up to one
+        i = int(np.argmin(np.abs(deg[l + 1] - unit_deg)))
+        j = int(np.argmin(np.where(deg[l] <= deg[l + 1][i], np.abs(deg[l] - limit), 10 ** 6)))
+        net.W[l][i, j] = np.nan
+    noise = S.make_noise(w)
+    h = B.model_from_network(net)
+    try:
+        u = torch.from_numpy(noise).cuda()
+        B.made_set_option(h, B.MADE_OPT_XCD_RESIDENT, 0)
+        B.made_set_option(h, B.MADE_OPT_RESIDENT, 0)
+        want = torch.empty((N, D), dtype=torch.uint8, device="cuda")
+        B.sequential_sample(h, u, N, 0, want)
+        B.made_set_option(h, B.MADE_OPT_RESIDENT, 2)
+        for block in (0, 8, 13, 32):
+            x = torch.full((N, D), 9, dtype=torch.uint8, device="cuda")
+            if block:
+                B.gs_jacobi_sample(h, u, N, None, block, x)
+            else:
+                B.sequential_sample(h, u, N, 1, x)
+            torch.cuda.synchronize()
+            assert torch.equal(x, want), (block, int((x != want).sum()), B.made_last_stats(h)["kernels"])
+    finally:
+        B.made_free(h)
+
+
 def test_a_smaller_model_made_later_leaves_the_larger_one_its_lds():
     """Two models of one depth and type alive, the larger (about 130 KB of LDS) called after the smaller was made."""
     models = []
