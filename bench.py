@@ -72,7 +72,7 @@ def cpu_baseline(w, net, noises, budget_s=12.0, single_thread_s=0.0):
 def own_stream(torch):
     """The benchmark runs on a stream of its own (default priority), made current so that torch's work is ordered with the
     library's.  Measured on the MI355X boxes: back-to-back calls of the launch-bound configurations take 1-3 % less on
-    such a stream than on the default stream (0.095 against 0.0975 ms per call on cfg2)."""
+    such a stream than on the default stream (0.095 against 0.0975 ms per call on cfg2, --path layers)."""
     torch.cuda.synchronize()
     stream = torch.cuda.Stream()
     torch.cuda.set_stream(stream)
